@@ -74,17 +74,23 @@ inline size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 struct Layout {
     size_t status;
     size_t zbuf, hole, hole2, bcount, rmask, bbox, pflag, pbox, wpart, gpart;
-    size_t ranges, colcum, mprefix, tlist, torder, mask16;
+    size_t ranges, torder, cmask, ctot, cstart, cpre, ttot;
     size_t xrgb;  // view-colour transfer: the dominant pass's affiliated-view colours [3][H][W]
-    size_t recs, zkeys, rects, counts, nseg, dkeys_b, dvals_a, dvals_b, offs, surf_scan;
+    size_t recs, zkeys, rects, dkeys_b, dvals_a, dvals_b, matrix, kpart;
     size_t recs2, zkeys2, rects2;  // the affiliated eye's surfels, from the dominant pass of a stereo frame
-    size_t tkeys_a, tkeys_b, tvals_a, tvals_b;
+    size_t emask, eid, tcount, vals;
     size_t radix;
     size_t trace;  // per-tile blend trace of the last counting-mode dominant pass
     size_t cdesc, citem, cst1, cpart;  // blend continuation
     uint32_t cslots;
     size_t total;
 };
+
+// Cells of 8x8 tiles.
+inline int64_t n_cells_of(int64_t W, int64_t H) {
+    const int64_t c = 8 * kTile;
+    return ((W + c - 1) / c) * ((H + c - 1) / c);
+}
 
 Layout make_layout(int64_t n, int64_t W, int64_t H, int64_t kc) {
     Layout L{};
@@ -109,32 +115,33 @@ Layout make_layout(int64_t n, int64_t W, int64_t H, int64_t kc) {
     L.wpart = take(16 * H);                                   // one per row
     L.gpart = take(8 * ((W + 63) / 64) * ((H + 15) / 16));   // one per gap-fill block
     L.ranges = take(8 * nt);
-    L.colcum = take(4 * (nt + (H + kTile - 1) / kTile));
-    L.mprefix = take(4 * (nt + 1));
-    L.tlist = take(4 * nt);
     L.torder = take(4 * nt);
-    L.mask16 = take(nt);  // rasteriser-tile mask of an ROI mask with 8- or 32-pixel tiles
+    const int64_t nc = n_cells_of(W, H);
+    L.cmask = take(8 * nc);
+    L.ctot = take(4 * nc);
+    L.cstart = take(4 * (nc + 1));
+    L.cpre = take(4 * (nc + 1));
+    L.ttot = take(4 * nt);
     L.xrgb = take(12 * np);
     L.recs = take(sizeof(SurfelRec) * n);
     L.zkeys = take(4 * n);
     L.rects = take(8 * n);
-    L.counts = take(4 * n);
-    L.nseg = take(4 * n);
     L.dkeys_b = take(4 * n);
     L.dvals_a = take(4 * n);
     L.dvals_b = take(4 * n);
-    L.offs = take(4 * (n + 1));
-    // Scan scratch: the count scan's block sums, or the per-256 totals of the
-    // ROI pass's ordered counts (ceil(n / 256) words), whichever is larger.
-    L.surf_scan = take(4 * std::max<size_t>(scan_tmp_elems(n), (size_t)((n + 255) / 256) + 64));
+    // A smaller image has fewer cells and may take more chunks of the order:
+    // the table is sized for the most that any image up to this size needs.
+    L.matrix = take(4 * bin_table_words(n, nc));
+    L.kpart = take(8 * (size_t)kBinMaxChunks);
     L.recs2 = take(sizeof(SurfelRec) * n);
     L.zkeys2 = take(4 * n);
     L.rects2 = take(8 * n);
-    L.tkeys_a = take(4 * kc);
-    L.tkeys_b = take(4 * kc);
-    L.tvals_a = take(4 * kc);
-    L.tvals_b = take(4 * kc);
-    L.radix = take(radix_tmp_bytes(kc > n ? kc : n));
+    // An entry holds at least one key, so there are no more of them than keys.
+    L.emask = take(8 * kc);
+    L.eid = take(4 * kc);
+    L.tcount = take(256 * (size_t)bin_max_expand_chunks((uint64_t)kc, (uint64_t)nc));
+    L.vals = take(4 * kc);
+    L.radix = take(radix_tmp_bytes(n));
     L.trace = take(6 * 8 * nt);
     L.cslots = (uint32_t)(nt < kContSlots ? nt : kContSlots);
     L.cdesc = take(16 * (size_t)L.cslots);
@@ -280,12 +287,6 @@ WarpCam make_warpcam(const bgs_camera& c) {
     return w;
 }
 
-int tile_bits(int64_t n_tiles) {
-    int b = 1;
-    while (((int64_t)1 << b) < n_tiles) ++b;
-    return b;
-}
-
 // Records the start (end = 0) or end (end = 1) of a stage when timing is on.
 // Fold one ring slot's finished stages into the totals.
 hipError_t drain_slot(bgs_ctx* ctx, int r) {
@@ -349,25 +350,18 @@ struct RasterOut {
     uint8_t* cls;
 };
 
-// Stage 1 for one camera, optionally restricted to the tiles of tile_mask.
+// Stage 1 for one camera, optionally restricted to the tiles of an ROI tile
+// mask (roi_tile-pixel tiles).
 // reuse_order: the compositing order of an earlier pass whose centre-depth
 // keys are bit-identical to this camera's (null: sort here).  *order_out
 // receives the order used.
 // cam_next: also preprocess the surfels for this camera (the affiliated eye
 // of a stereo frame) into the second record set; precomputed: this pass's
-// camera is that one, so it takes those records and only counts the keys
-// inside tile_mask.
-// The sorted per-tile surfel lists of a pass: surfel = vals[i] & vmask.
-struct SortedVals {
-    const uint32_t* vals;
-    uint32_t vmask;
-};
-
+// camera is that one, so it takes those records.
 int raster_pass(bgs_ctx* ctx, const Layout& L, void* ws, int64_t kc, const bgs_scene& scene, const bgs_camera& cam,
-                const bgs_raster_params& rp, const uint8_t* tile_mask, float a_min, const RasterOut& out, int which,
-                const uint32_t* reuse_order = nullptr, const uint32_t** order_out = nullptr,
-                const bgs_camera* cam_next = nullptr, bool precomputed = false, SortedVals* vals_out = nullptr,
-                const uint8_t* qmask = nullptr, int qmask_w = 0, BatchBlendDesc* defer = nullptr,
+                const bgs_raster_params& rp, const uint8_t* tile_mask, int roi_tile, float a_min, const RasterOut& out,
+                int which, const uint32_t* reuse_order = nullptr, const uint32_t** order_out = nullptr,
+                const bgs_camera* cam_next = nullptr, bool precomputed = false, BatchBlendDesc* defer = nullptr,
                 bool xfer = false) {
     hipStream_t s = ctx->stream;
     const int n = (int)scene.n;
@@ -376,105 +370,73 @@ int raster_pass(bgs_ctx* ctx, const Layout& L, void* ws, int64_t kc, const bgs_s
     DevStatus* st = at<DevStatus>(ws, L.status);
     const int sb = which ? BGS_STAGE_PREPROCESS_ROI : BGS_STAGE_PREPROCESS_DOM;
     mark(ctx, sb + 0, 0);
-    MaskArgs mask{nullptr, nullptr, pc.tiles_x, 0};
+    CellMask mask{nullptr, (pc.tiles_x + 7) / 8};
     if (tile_mask) {
-        HIP_CHECK(launch_mask_tables(tile_mask, n_tiles, pc.tiles_x, at<uint32_t>(ws, L.mprefix),
-                                     at<uint32_t>(ws, L.tlist), at<uint32_t>(ws, L.colcum), st, s),
-                  "mask tables");
-        mask.prefix = at<uint32_t>(ws, L.mprefix);
-        mask.colcum = at<uint32_t>(ws, L.colcum);
-        mask.enabled = 1;
+        uint64_t* cells = at<uint64_t>(ws, L.cmask);
+        HIP_CHECK(launch_cell_masks(tile_mask, roi_tile, cam.width, cam.height, cells, s), "cell masks");
+        mask.cells = cells;
     }
     SurfelRec* recs = at<SurfelRec>(ws, precomputed ? L.recs2 : L.recs);
     uint32_t* zkeys = at<uint32_t>(ws, precomputed ? L.zkeys2 : L.zkeys);
     uint2* rects = at<uint2>(ws, precomputed ? L.rects2 : L.rects);
-    uint32_t* counts = at<uint32_t>(ws, L.counts);
-    uint32_t* nseg = at<uint32_t>(ws, L.nseg);  // rows with keys per surfel, from the counting kernel
-    int nseg_by_pos = 0;
-    uint32_t* offs = at<uint32_t>(ws, L.offs);
-    // Precomputed records: the masked key counts are taken in compositing
-    // order together with the first step of their scan, once the order is
-    // known (below), when the flat scan covers n.
-    const bool fused_counts = precomputed && scan_is_flat(n);
-    if (precomputed) {
-        if (!tile_mask) return fail(ctx, BGS_ERR_INVALID_ARG, "precomputed records need a tile mask");
-        if (!fused_counts)
-            HIP_CHECK(launch_masked_counts(rects, recs, n, n_tiles, mask, counts, nseg, s), "masked counts");
-    } else {
+    if (!precomputed) {
         const SceneArgs sa{scene.pos, scene.quat, scene.scale, scene.opacity, scene.sh, n, scene.sh_degree};
         PreCam pn{};
         if (cam_next) pn = make_precam(*cam_next);
-        HIP_CHECK(launch_preprocess(sa, pc, rp.alpha_min, rp.lowpass, mask, recs, zkeys, rects, counts,
+        HIP_CHECK(launch_preprocess(sa, pc, rp.alpha_min, rp.lowpass, mask, recs, zkeys, rects, nullptr,
                                     cam_next ? &pn : nullptr, at<SurfelRec>(ws, L.recs2), at<uint32_t>(ws, L.zkeys2),
-                                    at<uint2>(ws, L.rects2), nseg, s),
+                                    at<uint2>(ws, L.rects2), s),
                   "preprocess");
     }
     mark(ctx, sb + 0, 1);
     // Compositing order: surfels sorted by (fp32 centre-depth bits, index).
     mark(ctx, sb + 1, 0);
-    bool in_b = false;
     const uint32_t* order = reuse_order;
     if (!order) {
+        bool in_b = false;
         uint32_t* dva = at<uint32_t>(ws, L.dvals_a);
         uint32_t* dvb = at<uint32_t>(ws, L.dvals_b);
-        HIP_CHECK(radix_sort(zkeys, dva, at<uint32_t>(ws, L.dkeys_b), dvb, nullptr, n, 32, true,
-                             at<void>(ws, L.radix), s, &in_b),
+        HIP_CHECK(radix_sort(zkeys, dva, at<uint32_t>(ws, L.dkeys_b), dvb, n, 32, true, at<void>(ws, L.radix), s, &in_b),
                   "depth sort");
         order = in_b ? dvb : dva;
     }
     if (order_out) *order_out = order;
     mark(ctx, sb + 1, 1);
-    mark(ctx, sb + 2, 0);
-    hipError_t se = hipSuccess;
+    // Tile lists: the entries by cell, the tiles' ranges and dispatch order,
+    // then the lists.
+    BinArgs b{};
+    b.order = order;
+    b.rects = rects;
+    b.recs = recs;
+    b.n = n;
+    b.tiles_x = pc.tiles_x;
+    b.tiles_y = pc.tiles_y;
+    b.cells_x = mask.cells_x;
+    b.n_cells = (uint32_t)n_cells_of(cam.width, cam.height);
+    bin_split(n, b.n_cells, &b.chunks, &b.fine, &b.per);
+    b.cap = (uint32_t)kc;
+    b.mask = mask;
+    b.matrix = at<uint32_t>(ws, L.matrix);
+    b.kpart = at<uint2>(ws, L.kpart);
+    b.ctot = at<uint32_t>(ws, L.ctot);
+    b.cstart = at<uint32_t>(ws, L.cstart);
+    b.cpre = at<uint32_t>(ws, L.cpre);
+    b.emask = at<uint64_t>(ws, L.emask);
+    b.eid = at<uint32_t>(ws, L.eid);
+    b.tcount = at<uint32_t>(ws, L.tcount);
+    b.ttot = at<uint32_t>(ws, L.ttot);
+    b.vals = at<uint32_t>(ws, L.vals);
     uint2* ranges = at<uint2>(ws, L.ranges);
-    uint32_t* surf_scan = at<uint32_t>(ws, L.surf_scan);
-    const KeyCount kcnt{st, (uint32_t)kc, which, ranges, (uint32_t)n_tiles};
-    bool scanned;
-    if (fused_counts) {
-        nseg_by_pos = 1;
-        HIP_CHECK(launch_masked_counts_ordered(rects, recs, order, n, n_tiles, mask, counts, surf_scan, nseg, s),
-                  "masked counts");
-        scanned = scan_counts_presummed(counts, offs, n, surf_scan, kcnt, s, &se);  // the flat form covers n
-    } else {
-        scanned = scan_counts(counts, order, offs, n, surf_scan, kcnt, s, &se);
-    }
-    if (scanned) {
-        HIP_CHECK(se, "count scan");
-    } else {
-        HIP_CHECK(exclusive_scan(counts, order, offs, nullptr, n, at<uint32_t>(ws, L.surf_scan), s), "count scan");
-        HIP_CHECK(launch_status_keys(offs, n, st, (uint32_t)kc, which, s), "key count");
-        HIP_CHECK(launch_clear_ranges(ranges, n_tiles, s), "range clear");
-    }
-    uint32_t* tka = at<uint32_t>(ws, L.tkeys_a);
-    uint32_t* tva = at<uint32_t>(ws, L.tvals_a);
-    uint32_t* tkb = at<uint32_t>(ws, L.tkeys_b);
-    uint32_t* tvb = at<uint32_t>(ws, L.tvals_b);
-    // A key and its surfel share one word (tile << vbits | surfel) when both
-    // fit in 32 bits: the sort then moves half the bytes.
-    const int tbits = tile_bits(n_tiles), sbits = tile_bits(n);
-    const int vbits = tbits + sbits <= 32 ? sbits : 0;
-    HIP_CHECK(launch_emit(order, offs, rects, recs, n, pc.tiles_x, n_tiles, mask, (uint32_t)kc, vbits, tka, tva, nseg,
-                          nseg_by_pos, s),
-              "emit");
-    mark(ctx, sb + 2, 1);
-    // Stable sort by tile: within a tile the emission (= compositing) order stays.
-    mark(ctx, sb + 3, 0);
-    // An ROI pass's key count is known only on the device and ranges from a
-    // few thousand keys to most of a full pass's: the sort runs both of its
-    // forms, each gated on that count.
-    HIP_CHECK(radix_sort(tka, vbits ? nullptr : tva, tkb, vbits ? nullptr : tvb, &st->n_sort, kc, tbits, false,
-                         at<void>(ws, L.radix), s, &in_b, tile_mask ? -1 : 0, vbits),
-              "tile sort");
-    const uint32_t* skeys = in_b ? tkb : tka;
-    const uint32_t* svals = vbits ? skeys : in_b ? tvb : tva;
-    const uint32_t vmask = vbits ? (1u << vbits) - 1u : 0xFFFFFFFFu;
-    if (vals_out) *vals_out = SortedVals{svals, vmask};
-    mark(ctx, sb + 3, 1);
-    mark(ctx, sb + 4, 0);
-    HIP_CHECK(launch_ranges(skeys, &st->n_sort, kc, ranges, n_tiles, vbits, s), "ranges");
     uint32_t* torder = at<uint32_t>(ws, L.torder);
-    HIP_CHECK(launch_tile_order(ranges, tile_mask ? &st->n_masked : nullptr, n_tiles, torder, s), "tile order");
+    mark(ctx, sb + 2, 0);
+    HIP_CHECK(launch_bin_entries(b, st, which, s), "binning");
+    mark(ctx, sb + 2, 1);
+    mark(ctx, sb + 4, 0);
+    HIP_CHECK(launch_tile_plan(b, ranges, torder, st, s), "tile ranges");
     mark(ctx, sb + 4, 1);
+    mark(ctx, sb + 3, 0);
+    HIP_CHECK(launch_tile_write(b, ranges, s), "tile lists");
+    mark(ctx, sb + 3, 1);
     BlendArgs ba{};
     ba.W = cam.width;
     ba.H = cam.height;
@@ -489,9 +451,11 @@ int raster_pass(bgs_ctx* ctx, const Layout& L, void* ws, int64_t kc, const bgs_s
     ba.a_min = a_min;
     ba.z_near = (float)cam.z_near;
     ba.patch = tile_mask ? 1 : 0;
-    ba.vmask = vmask;
-    ba.qmask = qmask;
-    ba.qmask_w = qmask_w;
+    if (tile_mask && roi_tile == 8) {
+        // The blend honours the ROI mask per 8x8 quadrant of a tile.
+        ba.qmask = tile_mask;
+        ba.qmask_w = (cam.width + 7) / 8;
+    }
     if (xfer) {
         // The affiliated eye's records hold every binned surfel's colour seen
         // from that eye (written by the two-eye preprocess of this pass).
@@ -508,9 +472,8 @@ int raster_pass(bgs_ctx* ctx, const Layout& L, void* ws, int64_t kc, const bgs_s
         // the other frames of the batch (no continuation there).
         BatchBlendDesc d{};
         d.recs = recs;
-        d.vals = svals;
+        d.vals = b.vals;
         d.ranges = ranges;
-        d.tile_list = tile_mask ? at<uint32_t>(ws, L.tlist) : nullptr;
         d.order = torder;
         d.n_live = tile_mask ? &st->n_masked : nullptr;
         d.n_tiles = (uint32_t)n_tiles;
@@ -523,32 +486,12 @@ int raster_pass(bgs_ctx* ctx, const Layout& L, void* ws, int64_t kc, const bgs_s
         return BGS_OK;
     }
     mark(ctx, sb + 5, 0);
-    HIP_CHECK(launch_blend(recs, svals, ranges, tile_mask ? at<uint32_t>(ws, L.tlist) : nullptr, torder,
-                           tile_mask ? &st->n_masked : nullptr, n_tiles, ba, ca, out.rgb, out.dz, out.alpha, out.cls,
+    HIP_CHECK(launch_blend(recs, b.vals, ranges, torder, tile_mask ? &st->n_masked : nullptr, n_tiles, ba, ca, out.rgb, out.dz, out.alpha, out.cls,
                            ctx->count_pairs ? &st->pairs[6 * which] : nullptr,
                            (ctx->count_pairs && which == 0) ? at<long long>(ws, L.trace) : nullptr, s),
               "blend");
     mark(ctx, sb + 5, 1);
     return BGS_OK;
-}
-
-// The rasteriser-tile (16x16) mask an ROI pass bins, and the 8x8 quadrant
-// mask its blend honours, for an ROI tile mask with roi.tile-pixel tiles.
-struct PatchMasks {
-    const uint8_t* mask16;
-    const uint8_t* qmask;
-    int qmask_w;
-};
-
-hipError_t patch_masks(bgs_ctx* ctx, const Layout& L, void* ws, const bgs_camera& dst, int T, const uint8_t* tile_mask,
-                       PatchMasks* pm) {
-    if (T == kTile) {
-        *pm = PatchMasks{tile_mask, nullptr, 0};
-        return hipSuccess;
-    }
-    uint8_t* m16 = at<uint8_t>(ws, L.mask16);
-    *pm = PatchMasks{m16, T == 8 ? tile_mask : nullptr, (dst.width + 7) / 8};
-    return launch_mask_to16(tile_mask, T, dst.width, dst.height, m16, ctx->stream);
 }
 
 // Start-of-frame status reset: zero the block, keeping the overflow bits of
@@ -729,7 +672,8 @@ int32_t bgs_render_dominant(bgs_ctx* ctx, const bgs_scene* scene, const bgs_came
     const Layout L = make_layout(scene->n, cam->width, cam->height, kc);
     DevStatus* st = at<DevStatus>(ws, L.status);
     HIP_CHECK(reset_status(ctx, ws, st), "status reset");
-    rc = raster_pass(ctx, L, ws, kc, *scene, *cam, *raster, nullptr, 0.f, RasterOut{rgb, depth_raw, alpha, nullptr}, 0);
+    rc = raster_pass(ctx, L, ws, kc, *scene, *cam, *raster, nullptr, 0, 0.f, RasterOut{rgb, depth_raw, alpha, nullptr},
+                     0);
     if (rc) return rc;
     if (!ctx->sync) return BGS_OK;
     DevStatus h{};
@@ -834,11 +778,8 @@ int32_t bgs_patch_rois(bgs_ctx* ctx, const bgs_scene* scene, const bgs_camera* d
     const Layout L = make_layout(scene->n, dst->width, dst->height, kc);
     DevStatus* st = at<DevStatus>(ws, L.status);
     HIP_CHECK(reset_status(ctx, ws, st), "status reset");
-    PatchMasks pm{};
-    HIP_CHECK(patch_masks(ctx, L, ws, *dst, roi->tile, tile_mask, &pm), "ROI tile mask");
-    rc = raster_pass(ctx, L, ws, kc, *scene, *dst, *raster, pm.mask16, roi->a_min,
-                     RasterOut{rgb_dst, z_dst, alpha_dst, cls}, 1, nullptr, nullptr, nullptr, false, nullptr, pm.qmask,
-                     pm.qmask_w);
+    rc = raster_pass(ctx, L, ws, kc, *scene, *dst, *raster, tile_mask, roi->tile, roi->a_min,
+                     RasterOut{rgb_dst, z_dst, alpha_dst, cls}, 1);
     if (rc) return rc;
     if (!ctx->sync) return BGS_OK;
     DevStatus h{};
@@ -877,9 +818,9 @@ int32_t bgs_render_stereo(bgs_ctx* ctx, const bgs_scene* scene, const bgs_camera
     // view's colours under the same weights).
     const uint32_t* dom_order = nullptr;
     const bool xfer = roi->view_colour != 0 && scene->sh_degree > 0;
-    rc = raster_pass(ctx, L, ws, kc, *scene, *cam_dom, *raster, nullptr, 0.f,
+    rc = raster_pass(ctx, L, ws, kc, *scene, *cam_dom, *raster, nullptr, 0, 0.f,
                      RasterOut{rgb_dom, depth_raw_dom, alpha_dom, nullptr}, 0, nullptr, &dom_order, cam_aff, false,
-                     nullptr, nullptr, 0, nullptr, xfer);
+                     nullptr, xfer);
     if (rc) return rc;
     const float* rgb_src = xfer ? at<float>(ws, L.xrgb) : rgb_dom;
     // The affiliated eye's compositing order equals the dominant one when
@@ -910,11 +851,9 @@ int32_t bgs_render_stereo(bgs_ctx* ctx, const bgs_scene* scene, const bgs_camera
               "classify");
     mark(ctx, BGS_STAGE_CLASSIFY, 1);
     // Stage 4: ROI re-rasterisation of the affiliated eye.
-    PatchMasks pm{};
-    HIP_CHECK(patch_masks(ctx, L, ws, *cam_aff, roi->tile, tile_mask, &pm), "ROI tile mask");
-    rc = raster_pass(ctx, L, ws, kc, *scene, *cam_aff, *raster, pm.mask16, roi->a_min,
+    rc = raster_pass(ctx, L, ws, kc, *scene, *cam_aff, *raster, tile_mask, roi->tile, roi->a_min,
                      RasterOut{rgb_aff, z_aff, alpha_aff, cls_aff}, 1, same_keys ? dom_order : nullptr, nullptr,
-                     nullptr, true, nullptr, pm.qmask, pm.qmask_w);
+                     nullptr, true);
     if (rc) return rc;
     if (!ctx->sync && !stats) return BGS_OK;
     DevStatus h{};
@@ -991,9 +930,9 @@ int batch_issue(bgs_ctx* ctx, int32_t n, const bgs_batch_pair* pairs, const bgs_
         const bgs_batch_pair& q = pairs[i];
         void* ws = q.ws;
         HIP_CHECK(reset_status_batch(ctx, ws, at<DevStatus>(ws, lays[i].status)), "status reset");
-        rc = raster_pass(ctx, lays[i], ws, kcs[i], *q.scene, q.cam_dom, *raster, nullptr, 0.f,
+        rc = raster_pass(ctx, lays[i], ws, kcs[i], *q.scene, q.cam_dom, *raster, nullptr, 0, 0.f,
                          RasterOut{q.rgb_dom, q.depth_raw_dom, q.alpha_dom, nullptr}, 0, nullptr, &dom_order[i],
-                         &q.cam_aff, false, nullptr, nullptr, 0, dd + i);
+                         &q.cam_aff, false, dd + i);
         if (rc) return rc;
     }
     HIP_CHECK(launch_blend_batch(dd, n, qd, grid, false, s), "batched blend");
@@ -1018,11 +957,9 @@ int batch_issue(bgs_ctx* ctx, int32_t n, const bgs_batch_pair* pairs, const bgs_
         HIP_CHECK(launch_classify(wd, wa, P, q.roi, raster->bg, nullptr, q.rgb_aff, q.z_aff, q.alpha_aff, q.cls_aff,
                                   q.labels, q.boxes, q.box_capacity, q.n_boxes, q.tile_mask, b, st, s),
                   "classify");
-        PatchMasks pm{};
-        HIP_CHECK(patch_masks(ctx, L, ws, q.cam_aff, q.roi.tile, q.tile_mask, &pm), "ROI tile mask");
-        rc = raster_pass(ctx, L, ws, kcs[i], *q.scene, q.cam_aff, *raster, pm.mask16, q.roi.a_min,
+        rc = raster_pass(ctx, L, ws, kcs[i], *q.scene, q.cam_aff, *raster, q.tile_mask, q.roi.tile, q.roi.a_min,
                          RasterOut{q.rgb_aff, q.z_aff, q.alpha_aff, q.cls_aff}, 1, same_keys ? dom_order[i] : nullptr,
-                         nullptr, nullptr, true, nullptr, pm.qmask, pm.qmask_w, dr + i);
+                         nullptr, nullptr, true, dr + i);
         if (rc) return rc;
     }
     HIP_CHECK(launch_blend_batch(dr, n, qr, grid, true, s), "batched ROI blend");
@@ -1127,7 +1064,7 @@ int32_t bgs_sort_pairs(bgs_ctx* ctx, uint32_t* keys, uint32_t* values, int64_t n
     uint32_t* vb = at<uint32_t>(ws, up(sizeof(DevStatus)) + up(4 * (size_t)n));
     void* tmp = at<void>(ws, up(sizeof(DevStatus)) + 2 * up(4 * (size_t)n));
     bool in_b = false;
-    HIP_CHECK(radix_sort(keys, values, kb, vb, nullptr, n, key_bits, false, tmp, ctx->stream, &in_b), "sort");
+    HIP_CHECK(radix_sort(keys, values, kb, vb, n, key_bits, false, tmp, ctx->stream, &in_b), "sort");
     if (in_b) {
         HIP_CHECK(hipMemcpyAsync(keys, kb, 4 * (size_t)n, hipMemcpyDeviceToDevice, ctx->stream), "copy");
         HIP_CHECK(hipMemcpyAsync(values, vb, 4 * (size_t)n, hipMemcpyDeviceToDevice, ctx->stream), "copy");
@@ -1161,10 +1098,9 @@ int32_t bgs_preprocess_debug(bgs_ctx* ctx, const bgs_scene* scene, const bgs_cam
     const SceneArgs sa{scene->pos, scene->quat, scene->scale, scene->opacity, scene->sh, (int)scene->n,
                        scene->sh_degree};
     const int n = (int)scene->n;
-    const MaskArgs no_mask{nullptr, nullptr, pc.tiles_x, 0};
+    const CellMask no_mask{nullptr, 0};
     HIP_CHECK(launch_preprocess(sa, pc, raster->alpha_min, raster->lowpass, no_mask, at<SurfelRec>(ws, L.recs), zkey,
-                                at<uint2>(ws, L.rects), counts, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                ctx->stream),
+                                at<uint2>(ws, L.rects), counts, nullptr, nullptr, nullptr, nullptr, ctx->stream),
               "preprocess");
     // Unpack the tile rectangles for the caller.
     if (n > 0) {
@@ -1208,10 +1144,8 @@ int32_t bgs_tile_lists_debug(bgs_ctx* ctx, const bgs_scene* scene, const bgs_cam
     // Scratch outputs: rgb in the piece-box region (16 B/px), depth and
     // alpha in the z-buffer (8 B/px).
     float* scratch = at<float>(ws, L.pbox);
-    SortedVals sv{};
-    rc = raster_pass(ctx, L, ws, kc, *scene, *cam, *raster, nullptr, 0.f,
-                     RasterOut{scratch, at<float>(ws, L.zbuf), at<float>(ws, L.zbuf) + np, nullptr}, 0, nullptr,
-                     nullptr, nullptr, false, &sv);
+    rc = raster_pass(ctx, L, ws, kc, *scene, *cam, *raster, nullptr, 0, 0.f,
+                     RasterOut{scratch, at<float>(ws, L.zbuf), at<float>(ws, L.zbuf) + np, nullptr}, 0);
     if (rc) return rc;
     DevStatus h{};
     if ((rc = finish(ctx, ws, L, &h))) return rc;
@@ -1222,7 +1156,8 @@ int32_t bgs_tile_lists_debug(bgs_ctx* ctx, const bgs_scene* scene, const bgs_cam
     const int n_tiles = pc.tiles_x * pc.tiles_y;
     HIP_CHECK(hipMemcpyAsync(ranges, at<uint2>(ws, L.ranges), 8 * (size_t)n_tiles, hipMemcpyDeviceToDevice, ctx->stream),
               "copy");
-    HIP_CHECK(launch_mask_copy(sv.vals, values, (int64_t)h.n_sort, sv.vmask, ctx->stream), "copy");
+    HIP_CHECK(hipMemcpyAsync(values, at<uint32_t>(ws, L.vals), 4 * (size_t)h.n_sort, hipMemcpyDeviceToDevice, ctx->stream),
+              "copy");
     HIP_CHECK(hipStreamSynchronize(ctx->stream), "sync");
     return BGS_OK;
 }

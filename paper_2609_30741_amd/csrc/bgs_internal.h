@@ -12,8 +12,9 @@
 namespace bgs {
 
 constexpr int kTile = 16;            // rasteriser tile edge (pixels)
-constexpr int kScanItems = 8;        // elements per thread in a scan block
-constexpr int kScanBlock = 256 * kScanItems;    // 2048 elements per block
+constexpr int kBinChunk = 256;       // entries a wave expands at a time
+constexpr int kBinMaxChunks = 4096;  // chunks of the compositing order
+constexpr int kBinFine = 64;         // surfels per chunk at the front of the order
 
 // Per-surfel record written by the preprocess and staged through LDS by the
 // blend kernel.  64 bytes.
@@ -53,17 +54,64 @@ struct SceneArgs {
     int sh_degree;
 };
 
-// Optional ROI restriction of the binning: only tiles with mask = 1 are
-// emitted, under compact ids (row-major rank among masked tiles).
-// prefix[t] = number of masked tiles before tile t in row-major order
-// (n_tiles + 1 entries), so a tile's compact id is prefix[t] and the masked
-// tiles of row ty in columns [a, b] number prefix[ty*tx+b+1] - prefix[ty*tx+a].
-struct MaskArgs {
-    const uint32_t* prefix;  // masked tiles before each tile (n_tiles + 1)
-    const uint32_t* colcum;  // column sums of prefix over rows (tiles_y x (tiles_x + 1))
-    int tiles_x;
-    int enabled;
+// Optional ROI restriction of the binning: bit 8 (ty & 7) + (tx & 7) of
+// cells[cell] says whether the tile is masked (cell = (ty / 8) * cells_x +
+// tx / 8); null: every tile.
+struct CellMask {
+    const uint64_t* cells;
+    int cells_x;
 };
+
+// Binning of one pass (raster.hip): scene, image and scratch.
+struct BinArgs {
+    const uint32_t* order;  // surfels in compositing order
+    const uint2* rects;     // tile rects (x | y << 16, inclusive), empty when .x > .y
+    const SurfelRec* recs;
+    int n;
+    uint32_t chunks;   // chunks of the order, at most kBinMaxChunks:
+    uint32_t fine;     //   the first `fine` hold kBinFine surfels each,
+    int per;           //   the others this many (a multiple of 256)
+    int tiles_x, tiles_y, cells_x;
+    uint32_t n_cells;
+    uint32_t cap;      // key capacity: list words, and at most as many entries
+    CellMask mask;
+    uint32_t* matrix;  // [n_cells][chunks] entries, then their exclusive scan over the chunks
+    uint2* kpart;      // per chunk: keys, entries
+    uint32_t* ctot;    // per cell: entries
+    uint32_t* cstart;  // n_cells + 1: first entry
+    uint32_t* cpre;    // n_cells + 1: first expansion chunk (kBinChunk entries each)
+    uint64_t* emask;   // per entry: its tiles within the cell
+    uint32_t* eid;     // per entry: its surfel
+    uint32_t* tcount;  // [expansion chunk][64]: keys per tile, then their scan over the cell's chunks
+    uint32_t* ttot;    // per tile: keys
+    uint32_t* vals;    // the tile lists
+};
+
+// The split of n surfels over n_cells cells.  The nearest surfels span the
+// image and carry most of the entries, so the front of the order goes in
+// small chunks (which also gives small scenes enough workgroups).  The
+// count table is bounded: 4 MiB, or 256 chunks where the cells alone exceed
+// that.
+inline void bin_split(int64_t n, int64_t n_cells, uint32_t* chunks, uint32_t* fine, int* per) {
+    const int64_t most = n_cells * kBinMaxChunks <= (1 << 20) ? kBinMaxChunks : (1 << 20) / n_cells;
+    const int64_t limit = most < 256 ? 256 : most;
+    const int64_t all_fine = (n + kBinFine - 1) / kBinFine;
+    const int64_t f = all_fine < limit / 8 ? all_fine : limit / 8;
+    const int64_t subs = n > f * kBinFine ? (n - f * kBinFine + 255) / 256 : 0;
+    const int64_t p = subs ? 256 * ((subs + (limit - f) - 1) / (limit - f)) : 256;
+    const int64_t c = f + (subs * 256 + p - 1) / p;
+    *chunks = (uint32_t)(c < 1 ? 1 : c);
+    *fine = (uint32_t)f;
+    *per = (int)p;
+}
+// Words of the count table for images of up to n_cells cells.
+inline size_t bin_table_words(int64_t n, int64_t n_cells) {
+    const int64_t all_fine = (n + kBinFine - 1) / kBinFine;  // no more chunks than this
+    const int64_t c = all_fine < 1 ? 1 : all_fine < kBinMaxChunks ? all_fine : kBinMaxChunks;
+    const int64_t w = n_cells * c, b = n_cells * 256 > (1 << 20) ? n_cells * 256 : (1 << 20);
+    return (size_t)(w < b ? w : b);
+}
+inline uint64_t bin_max_expand_chunks(uint64_t cap, uint64_t n_cells) { return cap / kBinChunk + n_cells; }
 
 struct BlendArgs {
     int W, H, tiles_x;
@@ -73,7 +121,6 @@ struct BlendArgs {
     float a_min;     // patch mode: depth proxy written only when A >= a_min
     float z_near;
     int patch;       // 0: write rgb/depth_raw/alpha; 1: write rgb/z/alpha/cls
-    uint32_t vmask;  // surfel index = sorted value & vmask (values that also carry the tile key)
     // ROI patch with 8-pixel ROI tiles: the 8x8 ROI tile mask (qmask_w tiles
     // per row); an 8x8 quadrant of a 16x16 tile that it leaves out is neither
     // composited nor written.  Null otherwise.
@@ -99,7 +146,7 @@ struct ContArgs {
     uint32_t min_far;      // continue a tile only if some pixel is expected to composite this many more records
     uint32_t* n_slots;     // counters (DevStatus), cleared before each pass
     uint32_t* n_items;
-    uint4* slot_desc;      // per slot: compact tile id, first continued record, end record, item base | nseg << kContSegShift
+    uint4* slot_desc;      // per slot: tile id, first continued record, end record, item base | nseg << kContSegShift
     uint32_t* item_slot;   // per item: its slot
     float4* st1;           // per slot: 256 pixels x 2 float4 after the capped walk
     float4* part;          // per item: 256 pixels x 2 float4, the segment's walk from the slot's transmittance
@@ -111,7 +158,7 @@ constexpr uint32_t kContSegShift = 26;  // item base in the low 26 bits, segment
 // Device status block kept in the workspace.
 struct DevStatus {
     uint32_t n_keys;       // keys of the last binning (may exceed capacity)
-    uint32_t n_sort;       // min(n_keys, capacity): keys actually sorted
+    uint32_t n_sort;       // min(n_keys, capacity): keys in the tile lists
     uint32_t n_masked;     // masked tiles of the last ROI patch
     uint32_t n_keys_dom;
     uint32_t n_keys_roi;
@@ -144,95 +191,40 @@ hipError_t launch_status_reset(DevStatus* st, int full, hipStream_t s);
 // dst[i] = value for i < n, by a kernel.
 hipError_t launch_fill_u32(uint32_t* dst, int64_t n, uint32_t value, hipStream_t s);
 
-// ---- scan / sort (sort.hip) -------------------------------------------------
-size_t scan_tmp_elems(int64_t n);
-// out[i] = sum_{j < i} in[idx ? idx[j] : j] for i = 0..n, with n = *n_dev when
-// n_dev is given (at most n_cap), else n_cap.  Elements past n count as 0.
-hipError_t exclusive_scan(const uint32_t* in, const uint32_t* idx, uint32_t* out, const uint32_t* n_dev,
-                          int64_t n_cap, uint32_t* tmp, hipStream_t s);
-// Key count of a binning pass, recorded in the status block by the scan of
-// the per-surfel key counts (which: 0 dominant, 1 ROI; cap: key capacity).
-// It also clears the blend-continuation counters of the pass.
-struct KeyCount {
-    DevStatus* st;
-    uint32_t cap;
-    int which;
-    uint2* ranges;     // tile ranges to clear to empty (n_tiles of them)
-    uint32_t n_tiles;
-};
-// Exclusive scan of n per-surfel counts (gathered through idx) into out[0..n]
-// with the key count recorded, in two launches.  Returns false, launching
-// nothing, when n is beyond its size limit (use exclusive_scan and
-// launch_status_keys then); *err gets the launch status otherwise.
-bool scan_counts(const uint32_t* in, const uint32_t* idx, uint32_t* out, int64_t n, uint32_t* tmp,
-                 const KeyCount& kcnt, hipStream_t s, hipError_t* err);
-// scan_counts' down-sweep alone, over counts in order whose totals per 256
-// consecutive elements are already in partials; false when n needs more
-// than the flat form's blocks.
-bool scan_counts_presummed(const uint32_t* in, uint32_t* out, int64_t n, const uint32_t* partials,
-                           const KeyCount& kcnt, hipStream_t s, hipError_t* err);
-// Whether the flat, two-launch scan covers n elements.
-bool scan_is_flat(int64_t n);
+// ---- sort (sort.hip) --------------------------------------------------------
 size_t radix_tmp_bytes(int64_t n_cap);
-// Stable LSD radix sort of (keys, values) by bits [key_shift, key_shift +
-// key_bits) of the keys, with digits of up to 8 bits.  (ka, va) is the
-// input, (kb, vb) the ping-pong buffer; iota = true ignores the input
-// values and uses the input positions instead; va = vb = null (and iota
-// false) sorts the keys alone (keys that carry their value in the bits
-// below key_shift).  The element count is *n_dev (<= n_cap), or n_cap when
-// n_dev is null.
-// Returns in *in_b whether the result is in (kb, vb).  n_hint (optional):
-// the expected element count when it is far below n_cap, or -1 when only
-// the device knows it (both kernel forms are then launched, each gated on
-// *n_dev); it only chooses the kernels' sub-chunk size, never the result.
-hipError_t radix_sort(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, const uint32_t* n_dev,
-                      int64_t n_cap, int key_bits, bool iota, void* tmp, hipStream_t s, bool* in_b,
-                      int64_t n_hint = 0, int key_shift = 0);
+// Stable LSD radix sort of n (key, value) pairs by the low key_bits bits of
+// the keys, with digits of up to 8 bits.  (ka, va) is the input, (kb, vb)
+// the ping-pong buffer; iota = true ignores the input values and uses the
+// input positions instead.  Returns in *in_b whether the result is in
+// (kb, vb).
+hipError_t radix_sort(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, int64_t n, int key_bits, bool iota,
+                      void* tmp, hipStream_t s, bool* in_b);
 
 // ---- rasteriser (raster.hip) --------------------------------------------------
-// cam2 (optional): also the keys, rects and records of a second camera (no
-// key counts: see launch_masked_counts).  nseg (optional, per surfel): the
-// rows of the surfel's band that hold keys, which the emission lists.
+// cam2 (optional): also the keys, rects and records of a second camera.
+// counts (optional, without cam2): the tiles of each surfel's band.  With a
+// mask, surfels whose rect holds no masked tile get an empty rect.
 hipError_t launch_preprocess(const SceneArgs& sc, const PreCam& cam, float alpha_min, int lowpass,
-                             const MaskArgs& mask, SurfelRec* recs, uint32_t* zkeys, uint2* rects,
+                             const CellMask& mask, SurfelRec* recs, uint32_t* zkeys, uint2* rects,
                              uint32_t* counts, const PreCam* cam2, SurfelRec* recs2, uint32_t* zkeys2,
-                             uint2* rects2, uint32_t* nseg, hipStream_t s);
-// Key counts within the mask's tiles from precomputed tile rects and records,
-// and the rows that hold them (nseg), per surfel.
-hipError_t launch_masked_counts(const uint2* rects, const SurfelRec* recs, int n, int n_tiles, const MaskArgs& mask,
-                                uint32_t* counts, uint32_t* nseg, hipStream_t s);
-// The same counts in compositing order (counts[i] and nseg[i] for surfel
-// order[i]), with the total of every 256 consecutive positions in partials
-// (ceil(n / 256) of them): the scan then needs only its down-sweep
-// (scan_counts_presummed).
-hipError_t launch_masked_counts_ordered(const uint2* rects, const SurfelRec* recs, const uint32_t* order, int n,
-                                        int n_tiles, const MaskArgs& mask, uint32_t* counts, uint32_t* partials,
-                                        uint32_t* nseg, hipStream_t s);
-// Keys of every surfel in compositing order: the tiles of its rect that its
-// strip band meets (and the mask holds, when enabled), row by row.
-// vbits > 0: one word per key, tile << vbits | surfel (tvals unused);
-// vbits = 0: the tile in tkeys and the surfel in tvals.
-// nseg (optional): each surfel's rows with keys as its counting pass left
-// them, indexed by position in the order (nseg_by_pos) or by surfel; null:
-// the emission counts them itself.
-hipError_t launch_emit(const uint32_t* order, const uint32_t* offs, const uint2* rects, const SurfelRec* recs, int n,
-                       int tiles_x, int n_tiles, const MaskArgs& mask, uint32_t cap, int vbits, uint32_t* tkeys,
-                       uint32_t* tvals, const uint32_t* nseg, int nseg_by_pos, hipStream_t s);
-// Tile ranges of the sorted keys (tile = key >> key_shift); the ranges must
-// have been cleared (by scan_counts, or launch_clear_ranges).
-hipError_t launch_ranges(const uint32_t* tkeys, const uint32_t* n_dev, int64_t cap, uint2* ranges,
-                         int n_tiles, int key_shift, hipStream_t s);
-// dst[i] = src[i] & mask for i < n.
-hipError_t launch_mask_copy(const uint32_t* src, uint32_t* dst, int64_t n, uint32_t mask, hipStream_t s);
-hipError_t launch_clear_ranges(uint2* ranges, int n_tiles, hipStream_t s);
-// Dispatch order of the (compact) tiles for the blend, heaviest first.
-hipError_t launch_tile_order(const uint2* ranges, const uint32_t* n_live, int n_tiles, uint32_t* order,
-                             hipStream_t s);
-// One block per (compact) tile, in `order`; n_live (device, optional) limits
+                             uint2* rects2, hipStream_t s);
+// The cells' masks of an ROI tile mask with T x T tiles (T = 8, 16 or 32)
+// for a W x H image: a 16-tile is set iff it overlaps a set T-tile.
+hipError_t launch_cell_masks(const uint8_t* tmask, int T, int W, int H, uint64_t* cells, hipStream_t s);
+// Entries of the pass's surfels by cell, in compositing order; the key count
+// goes to the status block (which: 0 dominant, 1 ROI).
+hipError_t launch_bin_entries(const BinArgs& a, DevStatus* st, int which, hipStream_t s);
+// Tile ranges, and the dispatch order of the (masked) tiles, heaviest first;
+// with a mask also their number, in the status block.
+hipError_t launch_tile_plan(const BinArgs& a, uint2* ranges, uint32_t* order, DevStatus* st, hipStream_t s);
+// The tile lists (a.vals).
+hipError_t launch_tile_write(const BinArgs& a, const uint2* ranges, hipStream_t s);
+// One block per tile, in `order`; n_live (device, optional) limits
 // the blocks that do work when the tile count is only known on the device.
 // pair_counts (optional): the six blend counters of DevStatus::pairs.
-hipError_t launch_blend(const SurfelRec* recs, const uint32_t* vals, const uint2* ranges,
-                        const uint32_t* tile_list, const uint32_t* order, const uint32_t* n_live, int n_blocks,
+hipError_t launch_blend(const SurfelRec* recs, const uint32_t* vals, const uint2* ranges, const uint32_t* order,
+                        const uint32_t* n_live, int n_blocks,
                         const BlendArgs& a, const ContArgs& ca, float* rgb, float* d_or_z, float* alpha, uint8_t* cls,
                         unsigned long long* pair_counts, long long* trace, hipStream_t s);
 // One frame's blend of a batch (one eye of one stereo pair), in device
@@ -242,9 +234,8 @@ struct BatchBlendDesc {
     const SurfelRec* recs;
     const uint32_t* vals;
     const uint2* ranges;
-    const uint32_t* tile_list;  // compact id -> tile id (masked passes); null: identity
-    const uint32_t* order;      // dispatch order of the compact tiles, heaviest first
-    const uint32_t* n_live;     // live compact tiles (masked passes); null: n_tiles
+    const uint32_t* order;      // dispatch order of the (masked) tiles, heaviest first
+    const uint32_t* n_live;     // masked tiles (masked passes); null: n_tiles
     uint32_t n_tiles;
     uint32_t reserved;
     BlendArgs a;
@@ -261,18 +252,6 @@ hipError_t launch_put_desc(const BatchBlendDesc& d, BatchBlendDesc* dst, hipStre
 // scratch: n + 2 words (prefix and counter).  patch: the frames are ROI
 // passes (the patch writes).
 hipError_t launch_blend_batch(const BatchBlendDesc* descs, int n, uint32_t* scratch, int grid, bool patch,
-                              hipStream_t s);
-
-// Tables of an ROI tile mask (n_tiles = tiles_x * tiles_y): prefix[n_tiles +
-// 1], the compact list of masked tile ids, the masked count in DevStatus, and
-// colcum[tiles_y][tiles_x + 1], the column sums of prefix over rows.
-// The 16x16 rasteriser-tile mask of an ROI tile mask with T x T tiles (T =
-// 8 or 32) for a W x H image: a 16-tile is set iff it overlaps a set T-tile.
-hipError_t launch_mask_to16(const uint8_t* tmask, int T, int W, int H, uint8_t* mask16, hipStream_t s);
-hipError_t launch_mask_tables(const uint8_t* tile_mask, int n_tiles, int tiles_x, uint32_t* prefix,
-                              uint32_t* tile_list, uint32_t* colcum, DevStatus* st, hipStream_t s);
-// Record the key count offs[n] of a binning (which: 0 dominant, 1 ROI).
-hipError_t launch_status_keys(const uint32_t* offs, int n, DevStatus* st, uint32_t cap, int which,
                               hipStream_t s);
 
 // ---- reprojection and classification (warp.hip, no fp contraction) -------

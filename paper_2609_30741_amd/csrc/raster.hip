@@ -1,9 +1,10 @@
-// 2DGS tile rasteriser for gfx950: per-surfel preprocess, load-balanced
-// (surfel, tile) key emission, tile ranges and front-to-back blending with
+// 2DGS tile rasteriser for gfx950: per-surfel preprocess, binning of the
+// depth-ordered surfels into tile lists and front-to-back blending with
 // the joint depth proxy (Sec. 3.1 Stage 1, Sec. 3.3 Eq. 1-2).
 #include <cmath>
 
 #include <algorithm>
+#include <climits>
 
 #include "bgs_internal.h"
 
@@ -52,21 +53,6 @@ __device__ inline void sh_basis(int deg, float x, float y, float z, float* Y) {
     Y[13] = -0.4570457994644658f * x * (4.f * zz - xx - yy);
     Y[14] = 1.445305721320277f * z * (xx - yy);
     Y[15] = -0.5900435899266435f * x * (xx - 3.f * yy);
-}
-
-// Masked tiles of the rect's rows ty0..ty of columns tx0..tx1, from the
-// column sums of the mask prefix: colcum[ty][x] = sum over rows <= ty of
-// prefix[row * tiles_x + x].
-__device__ inline uint32_t masked_rows(const MaskArgs& m, int tx0, int ty0, int tx1, int ty) {
-    const int w = m.tiles_x + 1;
-    const uint32_t* c = m.colcum;
-    uint32_t s = c[(int64_t)ty * w + tx1 + 1] - c[(int64_t)ty * w + tx0];
-    if (ty0 > 0) s -= c[(int64_t)(ty0 - 1) * w + tx1 + 1] - c[(int64_t)(ty0 - 1) * w + tx0];
-    return s;
-}
-
-__device__ inline uint32_t masked_count(const MaskArgs& m, int tx0, int ty0, int tx1, int ty1) {
-    return masked_rows(m, tx0, ty0, tx1, ty1);
 }
 
 // ---------------------------------------------------------------------------
@@ -230,57 +216,45 @@ struct BandRows {
     }
 };
 
-// The rows ty0..ty1 of a surfel's rect, in order: for each row whose band
-// interval [a, b] is not empty, f(c, first) gets its key count c (masked
-// tiles of [a, b] with the mask enabled, else b - a + 1) and the key of its
-// first tile (the compact id with the mask, else the tile id); f returns
-// false to stop.  Rows go four at a time, so their mask-prefix loads are in
-// flight together: a surfel across a whole image's rows otherwise waits on
-// two dependent loads per row.
-template <typename F>
-__device__ inline void for_band_rows(const BandRows& br, const MaskArgs& m, const uint32_t* pref, int tx0, int ty0,
-                                     int tx1, int ty1, F&& f) {
-    for (int y0 = ty0; y0 <= ty1; y0 += 4) {
-        int a[4], b[4];
-        uint32_t lo[4], hi[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            a[u] = 1;
-            b[u] = 0;
-            if (y0 + u <= ty1) br.row(y0 + u, tx0, tx1, &a[u], &b[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t rb = (int64_t)(y0 + u) * m.tiles_x;
-            const bool load = m.enabled && b[u] >= a[u];
-            lo[u] = load ? pref[rb + a[u]] : 0u;
-            hi[u] = load ? pref[rb + b[u] + 1] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (b[u] < a[u]) continue;
-            const int64_t rb = (int64_t)(y0 + u) * m.tiles_x;
-            const uint32_t c = m.enabled ? hi[u] - lo[u] : (uint32_t)(b[u] - a[u] + 1);
-            const uint32_t first = m.enabled ? lo[u] : (uint32_t)(rb + a[u]);
-            if (!f(c, first)) return;
-        }
+// Tiles of a surfel's rect that its band meets.
+__device__ inline uint32_t band_count(const BandRows& br, int tx0, int ty0, int tx1, int ty1) {
+    uint32_t cnt = 0;
+    for (int y = ty0; y <= ty1; ++y) {
+        int a, b;
+        br.row(y, tx0, tx1, &a, &b);
+        if (b >= a) cnt += (uint32_t)(b - a + 1);
     }
+    return cnt;
 }
 
-// Keys of a surfel: the band's tiles of its rect, only masked ones when the
-// mask is enabled.
-// segs (optional) receives the number of rows with keys: the segments the
-// emission lists for this surfel.
-__device__ inline uint32_t band_count(const BandRows& br, const MaskArgs& m, int tx0, int ty0, int tx1, int ty1,
-                                      uint32_t* segs = nullptr) {
-    uint32_t cnt = 0, ns = 0;
-    for_band_rows(br, m, m.prefix, tx0, ty0, tx1, ty1, [&](uint32_t c, uint32_t) {
-        cnt += c;
-        ns += c ? 1u : 0u;
-        return true;
-    });
-    if (segs) *segs = ns;
-    return cnt;
+// The band's tiles in cell row cr (tile rows 8 cr .. 8 cr + 7) of a surfel's
+// rect: f(cx, m) for every cell cx of the row from the first tile to the
+// last, m the cell's tiles as a mask (bit 8 (row & 7) + (column & 7)), which
+// may be empty.
+template <typename F>
+__device__ inline void cell_masks(const BandRows& br, int tx0, int ty0, int tx1, int ty1, int cr, F&& f) {
+    int a[8], b[8], lo = INT_MAX, hi = -1;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        const int y = 8 * cr + u;
+        a[u] = 1;
+        b[u] = 0;
+        if (y >= ty0 && y <= ty1) br.row(y, tx0, tx1, &a[u], &b[u]);
+        if (b[u] >= a[u]) {
+            lo = min(lo, a[u]);
+            hi = max(hi, b[u]);
+        }
+    }
+    if (hi < 0) return;
+    for (int cx = lo >> 3; cx <= hi >> 3; ++cx) {
+        uint32_t w[2] = {0u, 0u};
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int s = max(a[u] - 8 * cx, 0), e = min(b[u] - 8 * cx, 7);  // e < s for an empty row
+            w[u >> 2] |= ((1u << max(e + 1 - s, 0)) - 1u) << ((min(s, 8) + 8 * u) & 31);
+        }
+        f(cx, (uint64_t)w[0] | ((uint64_t)w[1] << 32));
+    }
 }
 
 // A surfel seen from one camera: its tile rect and every record word but
@@ -416,18 +390,33 @@ __device__ __forceinline__ void sh_dir(const PreCam& cam, float px, float py, fl
     d[2] = dirz * inv;
 }
 
-// Per surfel: the centre-depth key, tile rect, key count and record for
-// `cam`; with kTwo also the key, rect and record for cam2 (the other eye of
-// a stereo frame, whose key counts depend on a tile mask known only later).
+// Does a tile rect hold a masked tile?
+__device__ inline bool rect_masked(const CellMask& m, int tx0, int ty0, int tx1, int ty1) {
+    for (int cy = ty0 >> 3; cy <= ty1 >> 3; ++cy) {
+        const int y0 = max(ty0 - 8 * cy, 0), y1 = min(ty1 - 8 * cy, 7);
+        const uint64_t rows = (~0ull >> (8 * (7 - y1))) & (~0ull << (8 * y0));
+        for (int cx = tx0 >> 3; cx <= tx1 >> 3; ++cx) {
+            const int x0 = max(tx0 - 8 * cx, 0), x1 = min(tx1 - 8 * cx, 7);
+            const uint64_t cols = (uint64_t)((0xFFu >> (7 - x1)) & (0xFFu << x0)) * 0x0101010101010101ull;
+            if (m.cells[cy * m.cells_x + cx] & rows & cols) return true;
+        }
+    }
+    return false;
+}
+
+// Per surfel: the centre-depth key, tile rect and record for `cam` (and with
+// kCounts the tiles its band meets, which only bgs_preprocess_debug asks
+// for); with kTwo also the key, rect and record for cam2, the other eye of
+// a stereo frame.  With a mask, a surfel whose rect holds no masked tile is
+// dropped before its colour is read.
 // The scene is read once; the colours of both eyes come from one pass over
 // the SH coefficients, each toward its own camera centre.
-template <bool kTwo>
+template <bool kTwo, bool kCounts>
 __global__ __launch_bounds__(256) void k_preprocess(SceneArgs sc, PreCam cam, PreCam cam2, float alpha_min,
-                                                    int lowpass, MaskArgs mask, SurfelRec* __restrict__ recs,
+                                                    int lowpass, CellMask mask, SurfelRec* __restrict__ recs,
                                                     uint32_t* __restrict__ zkeys, uint2* __restrict__ rects,
                                                     uint32_t* __restrict__ counts, SurfelRec* __restrict__ recs2,
-                                                    uint32_t* __restrict__ zkeys2, uint2* __restrict__ rects2,
-                                                    uint32_t* __restrict__ nseg) {
+                                                    uint32_t* __restrict__ zkeys2, uint2* __restrict__ rects2) {
     const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= sc.n) return;
     const int n = sc.n;
@@ -459,20 +448,16 @@ __global__ __launch_bounds__(256) void k_preprocess(SceneArgs sc, PreCam cam, Pr
         if (in1) surfel_view(cam, px, py, pz, op, tu, tv, su, sv, alpha_min, lowpass, v1);
         if (kTwo && in2) surfel_view(cam2, px, py, pz, op, tu, tv, su, sv, alpha_min, lowpass, v2);
     }
-    uint32_t cnt = 0, segs = 0;
-    if (v1.drawn) {
-        cnt = band_count(BandRows(v1.rec), mask, v1.tx0, v1.ty0, v1.tx1, v1.ty1, &segs);
-        rects[k] = make_uint2((uint32_t)v1.tx0 | ((uint32_t)v1.ty0 << 16), (uint32_t)v1.tx1 | ((uint32_t)v1.ty1 << 16));
-    } else {
-        rects[k] = empty;
-    }
-    counts[k] = cnt;
-    if (nseg) nseg[k] = segs;
+    if (mask.cells && v1.drawn) v1.drawn = rect_masked(mask, v1.tx0, v1.ty0, v1.tx1, v1.ty1);
+    rects[k] = v1.drawn ? make_uint2((uint32_t)v1.tx0 | ((uint32_t)v1.ty0 << 16),
+                                     (uint32_t)v1.tx1 | ((uint32_t)v1.ty1 << 16))
+                        : empty;
+    if (kCounts) counts[k] = v1.drawn ? band_count(BandRows(v1.rec), v1.tx0, v1.ty0, v1.tx1, v1.ty1) : 0u;
     if (kTwo)
         rects2[k] = v2.drawn ? make_uint2((uint32_t)v2.tx0 | ((uint32_t)v2.ty0 << 16),
                                           (uint32_t)v2.tx1 | ((uint32_t)v2.ty1 << 16))
                              : empty;
-    const bool col1 = cnt > 0, col2 = kTwo && v2.drawn;
+    const bool col1 = v1.drawn, col2 = kTwo && v2.drawn;
     if (!col1 && !col2) return;
     // ---- colour: SH towards the surfel from each camera's centre ----
     // (With two eyes, the second eye's colour is also kept for every surfel
@@ -512,564 +497,494 @@ __global__ __launch_bounds__(256) void k_preprocess(SceneArgs sc, PreCam cam, Pr
     }
 }
 
-// Surfels whose rect spans more than kCoopRows tile rows are counted (ROI
-// pass) and have their segments listed (emission, up to kCoopMax per
-// workgroup) by a whole wave, a row per lane: the nearest surfels span the
-// image's rows, and one thread walking them set these kernels' tails.
-constexpr int kCoopRows = 16;
-constexpr int kCoopMax = 32;
-
-// Key counts of surfels whose tile rects and records were computed
-// earlier, restricted to the tiles of a mask.
-// The mask prefix is staged in LDS (dynamic shared memory, mask_lds words)
-// when it fits: the band rows read it twice a row.
-__global__ __launch_bounds__(256) void k_masked_counts(const uint2* __restrict__ rects,
-                                                       const SurfelRec* __restrict__ recs, int n, MaskArgs mask,
-                                                       int mask_lds, uint32_t* __restrict__ counts,
-                                                       uint32_t* __restrict__ nseg) {
-    extern __shared__ uint32_t s_mpre[];
-    if (mask_lds > 0) {  // uniform over the grid
-        for (int i = threadIdx.x; i < mask_lds; i += 256) s_mpre[i] = mask.prefix[i];
-        __syncthreads();
-        mask.prefix = s_mpre;
-    }
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= n) return;
-    const uint2 r = rects[k];
-    if (r.x > r.y || masked_count(mask, (int)(r.x & 0xFFFFu), (int)(r.x >> 16), (int)(r.y & 0xFFFFu),
-                                  (int)(r.y >> 16)) == 0) {
-        counts[k] = 0;
-        nseg[k] = 0;
-        return;
-    }
-    uint32_t segs = 0;
-    counts[k] = band_count(BandRows(recs[k]), mask, (int)(r.x & 0xFFFFu), (int)(r.x >> 16), (int)(r.y & 0xFFFFu),
-                           (int)(r.y >> 16), &segs);
-    nseg[k] = segs;
-}
-
-// The ROI pass's key counts in compositing order, fused with the first step
-// of their scan: one thread per position i of the order writes the masked
-// key count of surfel order[i] at i, and each block of 256 positions writes
-// its total to partials[block], so only the scan's down-sweep remains (it
-// adds kScanItems of these partials per block of its own).
-__global__ __launch_bounds__(256) void k_masked_counts_ordered(const uint2* __restrict__ rects,
-                                                               const SurfelRec* __restrict__ recs,
-                                                               const uint32_t* __restrict__ order, int n,
-                                                               MaskArgs mask, int mask_lds,
-                                                               uint32_t* __restrict__ counts,
-                                                               uint32_t* __restrict__ partials,
-                                                               uint32_t* __restrict__ nseg) {
-    extern __shared__ uint32_t s_mpre[];
-    __shared__ uint32_t s4[4];
-    if (mask_lds > 0) {  // uniform over the grid
-        for (int i = threadIdx.x; i < mask_lds; i += 256) s_mpre[i] = mask.prefix[i];
-        __syncthreads();
-        mask.prefix = s_mpre;
-    }
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    uint32_t c = 0, segs = 0, k = 0;
-    uint2 r = make_uint2(1u, 0u);
-    bool tall = false;
-    if (i < n) {
-        k = order[i];
-        r = rects[k];
-        if (!(r.x > r.y)) {
-            const int tx0 = (int)(r.x & 0xFFFFu), ty0 = (int)(r.x >> 16), tx1 = (int)(r.y & 0xFFFFu),
-                      ty1 = (int)(r.y >> 16);
-            if (masked_count(mask, tx0, ty0, tx1, ty1) != 0) {
-                if (ty1 - ty0 + 1 > kCoopRows)
-                    tall = true;  // counted by the whole wave below
-                else
-                    c = band_count(BandRows(recs[k]), mask, tx0, ty0, tx1, ty1, &segs);
-            }
-        }
-    }
-    // Surfels across many tile rows (the nearest ones span the image): the
-    // wave counts each one's rows together, a row per lane.
-    const int lane = (int)(threadIdx.x & 63);
-    for (uint64_t tb = __ballot(tall); tb; tb &= tb - 1) {
-        const int src = __ffsll((unsigned long long)tb) - 1;
-        const uint32_t kk = (uint32_t)__shfl((int)k, src, 64);
-        const uint32_t rx = (uint32_t)__shfl((int)r.x, src, 64), ry = (uint32_t)__shfl((int)r.y, src, 64);
-        const int hx0 = (int)(rx & 0xFFFFu), hy0 = (int)(rx >> 16), hx1 = (int)(ry & 0xFFFFu), hy1 = (int)(ry >> 16);
-        const BandRows hb(recs[kk]);
-        uint32_t cc = 0, ss = 0;
-        for (int y = hy0 + lane; y <= hy1; y += 64) {
-            int a, b;
-            hb.row(y, hx0, hx1, &a, &b);
-            if (b < a) continue;
-            const int64_t rb = (int64_t)y * mask.tiles_x;
-            const uint32_t cy = mask.prefix[rb + b + 1] - mask.prefix[rb + a];
-            cc += cy;
-            ss += cy ? 1u : 0u;
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            cc += (uint32_t)__shfl_xor((int)cc, off, 64);
-            ss += (uint32_t)__shfl_xor((int)ss, off, 64);
-        }
-        if (lane == src) {
-            c = cc;
-            segs = ss;
-        }
-    }
-    if (i < n) {
-        counts[i] = c;
-        nseg[i] = segs;  // by position in the order, as the counts
-    }
-    uint32_t sum = c;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += (uint32_t)__shfl_xor((int)sum, off, 64);
-    if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) partials[blockIdx.x] = s4[0] + s4[1] + s4[2] + s4[3];
-}
-
 // ---------------------------------------------------------------------------
-// Key emission, per block of up to 256 surfels in compositing order: one thread
-// per surfel lists the non-empty rows of its band within its rect as
-// segments (start of the segment's keys in the block, the first tile's key
-// and the surfel), in LDS.  The block's keys are then taken in windows: each
-// segment marks its keys of the window with its index in an owner table,
-// and each key is written from its owner's segment, with consecutive
-// threads on consecutive keys, so a surfel that covers many tiles does not
-// serialise one thread.  A block with more segments than the table holds
-// takes them in turns of the table's size.  With a tile mask, its prefix
-// table is staged in LDS (dynamic shared memory) when it fits.
+// Binning: the surfels of every tile in compositing order, from the depth
+// order.  The image's tiles are grouped in cells of 8x8 tiles.  A surfel has
+// one entry per cell that its band meets: its index and the cell's tiles it
+// meets as a 64-bit mask.  Entries are placed cell by cell in compositing
+// order (k_bin_count, k_bin_scan, k_bin_emit), and each cell's entries are
+// then expanded into its 64 tile lists with one lane per entry: a ballot of one
+// mask bit gives the entries of a tile (k_tile_count, k_tile_scan,
+// k_tile_plan, k_tile_write).
+//
+// Bound by memory on large frames and by launch latency on small ones.  A
+// (surfel, tile) key costs its 4 bytes in the list and a share of a 12-byte
+// entry, which several tiles share.  Emitting the keys one by one and
+// sorting them by tile id wrote them, read them for a histogram and moved
+// them once per digit, 16 bytes a key and pass: binning took 1220 us of the
+// 1.2M-surfel 1920x1080 frame (8.7e7 keys) and takes 310.
 // ---------------------------------------------------------------------------
-constexpr int kEmitSegs = 2048;
-constexpr int kEmitWin = 2048;
-constexpr int kEmitMaskLds = 8192;  // mask prefix words staged in LDS at most (32 KiB)
+constexpr int kBinWin = 1024;   // cells per bitmap window of the emission (32 KiB of LDS)
+constexpr int kBinKeep = 1536;  // entries of 256 surfels that the emission keeps in LDS between its two steps
+// Words of the count table up to which the emission scans it itself: 16
+// loads a thread, about what the launch that it saves costs.
+constexpr uint64_t kBinSmallTable = 4096;
+constexpr int kChunk = kBinChunk;  // entries a wave expands at a time
 
-__global__ __launch_bounds__(256) void k_emit(const uint32_t* __restrict__ order, const uint32_t* __restrict__ offs,
-                                              const uint2* __restrict__ rects, const SurfelRec* __restrict__ recs,
-                                              int n, int spb, int tiles_x, MaskArgs mask, int mask_lds,
-                                              uint32_t cap, int vbits, uint32_t* __restrict__ tkeys,
-                                              uint32_t* __restrict__ tvals, const uint32_t* __restrict__ nseg,
-                                              int nseg_by_pos) {
-    extern __shared__ uint32_t s_mpre[];  // mask_lds words: the mask prefix, when staged
-    __shared__ uint32_t sk[256];
-    __shared__ uint32_t seg_start[kEmitSegs + 1];
-    __shared__ uint32_t seg_tile[kEmitSegs];  // first tile's key | surfel << 24 (keys < 2^20: sides <= 16384 px)
-    __shared__ uint16_t owner[kEmitWin];
-    __shared__ uint32_t lds[4];
-    __shared__ uint32_t s_nh;                // surfels listed by a wave
-    __shared__ float4 s_hrec[kCoopMax];      // their band words: centre x, y and the two packed band words
-    __shared__ uint4 s_hinfo[kCoopMax];      // rect (two packed words), first key in the block, first segment
-    __shared__ uint2 s_howner[kCoopMax];     // owning thread, segment count
-    const int r0 = blockIdx.x * spb;  // spb <= 256 surfels, one thread each; all 256 threads write keys
-    const int m = min(spb, n - r0);
-    const uint32_t base = offs[r0];
-    // A block whose surfels have no key (culled ones sort last; most of a
-    // masked pass's surfels miss its tiles) leaves before staging anything.
-    if (offs[r0 + m] == base) return;
-    const int t = threadIdx.x;
-    const uint32_t* pref = mask.prefix;
-    if (mask_lds > 0) {  // uniform over the block
-        for (int i = t; i < mask_lds; i += 256) s_mpre[i] = mask.prefix[i];
-        __syncthreads();
-        pref = s_mpre;
-    }
-    uint2 rc = make_uint2(0xFFFFFFFFu, 0u);
-    uint32_t cnt = 0, loc = 0, ns_given = 0;
-    SurfelRec rec;
-    if (t < m) {
-        const uint32_t k = order[r0 + t];
-        loc = offs[r0 + t] - base;
-        cnt = offs[r0 + t + 1] - offs[r0 + t];
-        sk[t] = k;
-        if (cnt) {
-            rc = rects[k];
-            rec = recs[k];
-            if (nseg) ns_given = nseg[nseg_by_pos ? (uint32_t)(r0 + t) : k];
-        }
-    }
-    const int tx0 = rc.x & 0xFFFF, ty0 = rc.x >> 16, tx1 = rc.y & 0xFFFF, ty1 = rc.y >> 16;
-    const BandRows br = cnt ? BandRows(rec) : BandRows();
-    // Segments of this thread's surfel: counted by the pass that counted
-    // its keys, or here.
-    uint32_t ns = ns_given;
-    MaskArgs mk = mask;
-    mk.tiles_x = tiles_x;
-    if (cnt && !nseg) {
-        for_band_rows(br, mk, pref, tx0, ty0, tx1, ty1, [&](uint32_t c, uint32_t) {
-            ns += c ? 1u : 0u;
-            return true;
-        });
-    }
-    // Exclusive scan of the segment counts over the block.
-    uint32_t v = ns;
-    const int lane = t & 63, w = t >> 6;
+// 256 surfels of the order, staged for the cell loops: their bands and
+// rects, and the running number of their cell rows.  The unit of work is a
+// (surfel, cell row) item, so that the nearest surfels, which span the
+// image, are spread over the workgroup.
+struct BinStage {
+    double k0[256], k16[256], r[256], inv[256];
+    uint2 rect[256];
+    uint32_t id[256];
+    uint32_t item[257];
+    uint32_t wsum[4];
+};
+
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v, int lane) {
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const uint32_t y = __shfl_up(v, off, 64);
         if (lane >= off) v += y;
     }
-    if (t == 0) s_nh = 0;
-    if (lane == 63) lds[w] = v;
+    return v;
+}
+
+// Exclusive scan over a 256-thread block (w4: 4 words of LDS, free again
+// after the next barrier); *total gets the sum.
+__device__ __forceinline__ uint32_t block_scan_256(uint32_t v, uint32_t* w4, uint32_t* total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t x = wave_scan_u32(v, lane);
+    if (lane == 63) w4[w] = x;
     __syncthreads();
-    uint32_t sbase = v - ns;
-    for (int q = 0; q < w; ++q) sbase += lds[q];
-    const uint32_t tot_seg = lds[0] + lds[1] + lds[2] + lds[3];
-    bool coop = false;
-    if (ns && ty1 - ty0 + 1 > kCoopRows) {
-        const uint32_t h = atomicAdd(&s_nh, 1u);
-        if (h < (uint32_t)kCoopMax) {
-            coop = true;
-            s_hrec[h] = make_float4(rec.a.x, rec.a.y, rec.c.w, rec.d.w);
-            s_hinfo[h] = make_uint4(rc.x, rc.y, loc, sbase);
-            s_howner[h] = make_uint2((uint32_t)t, ns);
-        }
-    }
-    __syncthreads();
-    const uint32_t n_coop = min(s_nh, (uint32_t)kCoopMax);
-    for (uint32_t w0 = 0; w0 < tot_seg; w0 += kEmitSegs) {
-        const uint32_t w1 = min(tot_seg, w0 + (uint32_t)kEmitSegs);
-        if (ns && !coop && sbase < w1 && sbase + ns > w0) {
-            uint32_t si = sbase, kpos = loc;
-            for_band_rows(br, mk, pref, tx0, ty0, tx1, ty1, [&](uint32_t c, uint32_t first) {
-                if (si >= w1) return false;
-                if (!c) return true;
-                if (si >= w0) {
-                    seg_start[si - w0] = kpos;
-                    seg_tile[si - w0] = first | ((uint32_t)t << 24);
-                    if (si + 1 == w1) seg_start[w1 - w0] = kpos + c;  // end of the turn's keys
-                }
-                kpos += c;
-                ++si;
-                return true;
-            });
-        }
-        // The wave-listed surfels: 64 rows at a time, the row's segment slot
-        // from a ballot of the rows with keys and its first key from a
-        // prefix sum of the row counts.
-        for (uint32_t h = (uint32_t)w; h < n_coop; h += 4) {
-            const uint4 hi = s_hinfo[h];
-            const uint2 ho = s_howner[h];
-            if (!(hi.w < w1 && hi.w + ho.y > w0)) continue;  // uniform over the wave
-            const float4 hr = s_hrec[h];
-            SurfelRec q{};
-            q.a.x = hr.x;
-            q.a.y = hr.y;
-            q.c.w = hr.z;
-            q.d.w = hr.w;
-            const BandRows hb(q);
-            const int hx0 = (int)(hi.x & 0xFFFFu), hy0 = (int)(hi.x >> 16), hx1 = (int)(hi.y & 0xFFFFu),
-                      hy1 = (int)(hi.y >> 16);
-            uint32_t seg_carry = 0, key_carry = 0;
-            for (int y0 = hy0; y0 <= hy1 && hi.w + seg_carry < w1; y0 += 64) {
-                const int y = y0 + lane;
-                int a = 1, b = 0;
-                if (y <= hy1) hb.row(y, hx0, hx1, &a, &b);
-                uint32_t c = 0, first = 0;
-                if (b >= a) {
-                    const int64_t rb = (int64_t)y * tiles_x;
-                    if (mask.enabled) {
-                        first = pref[rb + a];
-                        c = pref[rb + b + 1] - first;
-                    } else {
-                        first = (uint32_t)(rb + a);
-                        c = (uint32_t)(b - a + 1);
-                    }
-                }
-                const uint64_t bal = __ballot(c != 0);
-                const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-                uint32_t kin = c;  // inclusive prefix of the row counts over the wave
+    uint32_t before = 0, sum = 0;
 #pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const uint32_t yv = __shfl_up(kin, off, 64);
-                    if (lane >= off) kin += yv;
-                }
-                const uint32_t si = hi.w + seg_carry + before;
-                const uint32_t kpos = hi.z + key_carry + kin - c;
-                if (c != 0 && si >= w0 && si < w1) {
-                    seg_start[si - w0] = kpos;
-                    seg_tile[si - w0] = first | (ho.x << 24);
-                    if (si + 1 == w1) seg_start[w1 - w0] = kpos + c;  // end of the turn's keys
-                }
-                seg_carry += (uint32_t)__popcll(bal);
-                key_carry += __shfl(kin, 63, 64);
+    for (int q = 0; q < 4; ++q) {
+        const uint32_t y = w4[q];
+        before += q < w ? y : 0u;
+        sum += y;
+    }
+    *total = sum;
+    return before + x - v;
+}
+
+// The positions of the order that chunk c holds.
+__device__ __forceinline__ void bin_chunk(const BinArgs& a, uint32_t c, int64_t* p0, int64_t* p1) {
+    const bool fine = c < a.fine;
+    const int64_t b = fine ? (int64_t)c * kBinFine : (int64_t)a.fine * kBinFine + (int64_t)(c - a.fine) * a.per;
+    *p0 = min((int64_t)a.n, b);
+    *p1 = min((int64_t)a.n, b + (fine ? kBinFine : a.per));
+}
+
+// Stages surfels order[p0 .. p0 + m) and returns the number of items.  Has
+// block barriers; the stage may be read after it.
+__device__ __forceinline__ uint32_t bin_stage(const BinArgs& a, int64_t p0, int m, BinStage& s) {
+    const int t = threadIdx.x;
+    uint32_t rows = 0;
+    if (t < m) {
+        const uint32_t k = a.order[p0 + t];
+        const uint2 rc = a.rects[k];
+        if (!(rc.x > rc.y)) {
+            const int tx0 = rc.x & 0xFFFF, ty0 = rc.x >> 16, tx1 = rc.y & 0xFFFF, ty1 = rc.y >> 16;
+            if (!a.mask.cells || rect_masked(a.mask, tx0, ty0, tx1, ty1)) {
+                const BandRows br(a.recs[k]);
+                s.k0[t] = br.k0;
+                s.k16[t] = br.k16;
+                s.r[t] = br.r;
+                s.inv[t] = br.inv;
+                s.rect[t] = rc;
+                s.id[t] = k;
+                rows = (uint32_t)((ty1 >> 3) - (ty0 >> 3) + 1);
             }
         }
+    }
+    uint32_t total;
+    s.item[t] = block_scan_256(rows, s.wsum, &total);
+    if (t == 0) s.item[256] = total;
+    __syncthreads();
+    return total;
+}
+
+// f(surfel of the stage, cell, mask) for every entry of item `it`.
+template <typename F>
+__device__ __forceinline__ void bin_item(const BinArgs& a, const BinStage& s, uint32_t it, F&& f) {
+    int lo = 0, hi = 255;  // the last surfel whose first item is not past `it`
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (s.item[mid] <= it) lo = mid;
+        else hi = mid - 1;
+    }
+    BandRows br;
+    br.k0 = s.k0[lo];
+    br.k16 = s.k16[lo];
+    br.r = s.r[lo];
+    br.inv = s.inv[lo];
+    br.vertical = br.inv == 0.0;
+    const uint2 rc = s.rect[lo];
+    const int tx0 = rc.x & 0xFFFF, ty0 = rc.x >> 16, tx1 = rc.y & 0xFFFF, ty1 = rc.y >> 16;
+    const int cr = (ty0 >> 3) + (int)(it - s.item[lo]);
+    cell_masks(br, tx0, ty0, tx1, ty1, cr, [&](int cx, uint64_t m) {
+        const uint32_t cell = (uint32_t)(cr * a.cells_x + cx);
+        if (a.mask.cells) m &= a.mask.cells[cell];
+        if (m) f(lo, cell, m);
+    });
+}
+
+// Entries per (cell, chunk of the order), and the keys and entries of each
+// chunk.  One workgroup per chunk.
+__global__ __launch_bounds__(256) void k_bin_count(BinArgs a) {
+    extern __shared__ uint32_t s_cnt[];  // a.n_cells words
+    __shared__ BinStage s;
+    const int t = threadIdx.x;
+    for (uint32_t c = t; c < a.n_cells; c += 256) s_cnt[c] = 0u;
+    int64_t p0, p1;
+    bin_chunk(a, blockIdx.x, &p0, &p1);
+    uint32_t keys = 0;
+    for (int64_t p = p0; p < p1; p += 256) {
         __syncthreads();
-        const int nw = (int)(w1 - w0);
-        const uint32_t p0 = seg_start[0], p1 = seg_start[nw];
-        for (uint32_t kw = p0; kw < p1; kw += kEmitWin) {
-            const uint32_t ke = min(p1, kw + (uint32_t)kEmitWin);
-            // Owner of every key of the window: each segment marks where its
-            // keys start in the window (segment index + 1; the segment that
-            // covers the window's first key marks position 0), and an
-            // inclusive max-scan carries each mark over its segment's keys.
-            // A segment's keys are not filled by one thread in turn: a
-            // surfel across a whole row of tiles would serialise it.
-            static_assert(kEmitWin == 8 * 256, "eight window positions per thread");
-            const uint32_t len = ke - kw;
-            for (uint32_t i = t; i < len; i += 256) owner[i] = 0;
-            __syncthreads();
-            for (int j = t; j < nw; j += 256) {
-                const uint32_t s0 = seg_start[j], s1 = seg_start[j + 1];
-                if (s0 < ke && s1 > kw) owner[(s0 > kw ? s0 : kw) - kw] = (uint16_t)(j + 1);
-            }
-            __syncthreads();
-            uint32_t run[8], mx = 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t i = 8u * (uint32_t)t + (uint32_t)e;
-                mx = max(mx, i < len ? (uint32_t)owner[i] : 0u);
-                run[e] = mx;
-            }
-            uint32_t xm = mx;  // inclusive max over the wave's threads, then over the waves before
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t y = __shfl_up(xm, off, 64);
-                if (lane >= off) xm = max(xm, y);
-            }
-            __syncthreads();  // every mark is read before the LDS word below is reused
-            if (lane == 63) lds[w] = xm;
-            __syncthreads();
-            uint32_t before = __shfl_up(xm, 1, 64);
-            if (lane == 0) before = 0;
-            for (int q = 0; q < w; ++q) before = max(before, lds[q]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t i = 8u * (uint32_t)t + (uint32_t)e;
-                if (i < len) owner[i] = (uint16_t)(max(run[e], before) - 1u);
-            }
-            __syncthreads();
-            for (uint32_t p = kw + t; p < ke; p += 256) {
-                const int j = owner[p - kw];
-                const uint32_t st = seg_tile[j];
-                const uint32_t g = base + p;
-                if (g < cap) {
-                    const uint32_t tile = (st & 0xFFFFFFu) + (p - seg_start[j]);
-                    if (vbits) {
-                        tkeys[g] = tile << vbits | sk[st >> 24];
-                    } else {
-                        tkeys[g] = tile;
-                        tvals[g] = sk[st >> 24];
-                    }
-                }
-            }
-            __syncthreads();
-        }
+        const uint32_t items = bin_stage(a, p, (int)min((int64_t)256, p1 - p), s);
+        for (uint32_t it = t; it < items; it += 256)
+            bin_item(a, s, it, [&](int, uint32_t cell, uint64_t m) {
+                atomicAdd(&s_cnt[cell], 1u);
+                keys += (uint32_t)__popcll(m);
+            });
     }
+    __syncthreads();
+    uint32_t ents = 0;
+    for (uint32_t c = t; c < a.n_cells; c += 256) {
+        const uint32_t v = s_cnt[c];
+        a.matrix[(size_t)c * a.chunks + blockIdx.x] = v;
+        ents += v;
+    }
+    uint32_t nk, ne;
+    (void)block_scan_256(keys, s.wsum, &nk);
+    __syncthreads();
+    (void)block_scan_256(ents, s.wsum, &ne);
+    if (t == 0) a.kpart[blockIdx.x] = make_uint2(nk, ne);
 }
 
-// [start, end) of every tile in the sorted keys: a key that differs from
-// its predecessor starts its tile's range and ends the predecessor's.  The
-// ranges were cleared to empty beforehand (by the count scan), so a tile
-// with no key keeps an empty range.  Grid-stride over the *n_dev keys.
-// Each thread takes four consecutive keys (one 16-byte load; the keys
-// buffer is 16-byte aligned) and the key before them.
-__global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ n_dev,
-                                                uint2* __restrict__ ranges, uint32_t n_tiles, int shift) {
-    const uint32_t n = *n_dev;
-    for (uint64_t q = (uint64_t)blockIdx.x * 256 + threadIdx.x; 4 * q < n; q += (uint64_t)gridDim.x * 256) {
-        const uint32_t i0 = (uint32_t)(4 * q);
-        uint32_t k[4];
-        if (i0 + 3 < n) {
-            const uint4 v = *reinterpret_cast<const uint4*>(keys + i0);
-            k[0] = v.x >> shift; k[1] = v.y >> shift; k[2] = v.z >> shift; k[3] = v.w >> shift;
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) k[u] = i0 + u < n ? keys[i0 + u] >> shift : 0xFFFFFFFFu;
-        }
-        uint32_t prev = i0 > 0 ? keys[i0 - 1] >> shift : 0xFFFFFFFFu;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t i = i0 + u;
-            if (i >= n) break;
-            if (k[u] != prev) {
-                if (k[u] < n_tiles) ranges[k[u]].x = i;
-                if (i > 0 && prev < n_tiles) ranges[prev].y = i;
-            }
-            if (i + 1 == n && k[u] < n_tiles) ranges[k[u]].y = n;
-            prev = k[u];
-        }
-    }
-}
-
-__global__ void k_status_keys(const uint32_t* __restrict__ offs, int n, DevStatus* st, uint32_t cap, int which) {
+// The pass's key count (one thread) and the counters that a pass starts
+// from.
+__device__ __forceinline__ void bin_status(const BinArgs& a, DevStatus* st, int which, uint32_t total) {
     st->n_slots = 0;
     st->n_items = 0;
-    const uint32_t K = offs[n];
-    st->n_keys = K;
-    st->n_sort = K < cap ? K : cap;
-    if (K > cap) st->overflow |= 1u;
-    if (which == 0) st->n_keys_dom = K;
-    else st->n_keys_roi = K;
+    st->n_keys = total;
+    st->n_sort = total < a.cap ? total : a.cap;
+    if (total > a.cap) st->overflow |= 1u;
+    if (which == 0) st->n_keys_dom = total;
+    else st->n_keys_roi = total;
 }
 
-constexpr int kMaskLds = 15360;  // tile-mask prefix words staged in LDS (60 KiB)
-
-// Bit j set iff byte j of w is nonzero (j = 0..3).
-__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t w) {
-    const uint32_t h = (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u;
-    return ((h >> 7) & 1u) | ((h >> 14) & 2u) | ((h >> 21) & 4u) | ((h >> 28) & 8u);
-}
-
-// Tables of an ROI tile mask, one workgroup: prefix[t] = masked tiles before
-// tile t (t = 0..n_tiles), the compact list of masked tile ids, their count,
-// and colcum[ty][x] = sum over rows <= ty of prefix[row * tiles_x + x] for
-// x = 0..tiles_x, from which any rect's masked count takes four loads.
-// A mask of fewer than kMaskLds tiles is read in one step (16 tiles a
-// thread, loads issued together), its prefix built in LDS, and the column
-// sums taken by (column, band of rows) pairs: each pair sums its band, the
-// bands before it give its start, and it writes its rows.  Larger masks
-// take 4096 tiles per step and one wave per column.
-__global__ __launch_bounds__(1024) void k_mask_tables(const uint8_t* __restrict__ m, int n_tiles, int tiles_x,
-                                                      uint32_t* __restrict__ prefix, uint32_t* __restrict__ list,
-                                                      uint32_t* __restrict__ colcum, DevStatus* st) {
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t s_run;
-    __shared__ uint32_t s_pre[kMaskLds];
-    __shared__ uint32_t s_band[1024];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tiles_y = n_tiles / tiles_x;
-    const bool staged = n_tiles + 1 <= kMaskLds;
-    static_assert(kMaskLds <= 16 * 1024, "one step of 16 tiles a thread covers a staged mask");
-    if (staged) {
-        const int t0 = 16 * tid;
-        uint32_t bits = 0;  // bit j: tile t0 + j is masked
-        if (t0 + 16 <= n_tiles && ((reinterpret_cast<uintptr_t>(m) & 15u) == 0)) {
-            const uint4 w = *reinterpret_cast<const uint4*>(m + t0);
-            bits = nonzero_bytes(w.x) | (nonzero_bytes(w.y) << 4) | (nonzero_bytes(w.z) << 8) |
-                   (nonzero_bytes(w.w) << 12);
-        } else {
-            uint8_t b[16];
-#pragma unroll
-            for (int j = 0; j < 16; ++j) b[j] = t0 + j < n_tiles ? m[t0 + j] : 0;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) bits |= (b[j] != 0 ? 1u : 0u) << j;
-        }
-        const uint32_t sum = __popc(bits);
-        uint32_t x = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = __shfl_up(x, off, 64);
-            if (lane >= off) x += y;
-        }
-        if (lane == 63) wsum[wave] = x;
-        __syncthreads();
-        uint32_t acc = x - sum, total = 0;
-        for (int w = 0; w < 16; ++w) {
-            const uint32_t ws = wsum[w];
-            if (w < wave) acc += ws;
-            total += ws;
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int t = t0 + j;
-            if (t < n_tiles) {
-                s_pre[t] = acc;
-                if ((bits >> j) & 1u) list[acc] = (uint32_t)t;
-            }
-            acc += (bits >> j) & 1u;
-        }
-        if (tid == 0) {
-            s_pre[n_tiles] = total;
-            st->n_masked = total;
-            st->n_roi_tiles = total;
-        }
-        __syncthreads();
-        for (int t = tid; t <= n_tiles; t += 1024) prefix[t] = s_pre[t];  // coalesced
-        // Column x = tiles_x reads the next row's first entry (the last
-        // row's is the total).
-        const int C = tiles_x + 1;
-        if (C <= 1024) {
-            const int K = max(1, min(tiles_y, 1024 / C)), R = (tiles_y + K - 1) / K;
-            const int k = tid / C, xc = tid - k * C;
-            const bool on = k < K;
-            const int r0 = on ? min(tiles_y, k * R) : 0, r1 = on ? min(tiles_y, r0 + R) : 0;
-            uint32_t bs = 0;
-            for (int r = r0; r < r1; ++r) bs += s_pre[r * tiles_x + xc];
-            s_band[tid] = bs;
-            __syncthreads();
-            uint32_t run = 0;
-            for (int q = 0; q < k && on; ++q) run += s_band[q * C + xc];
-            for (int r = r0; r < r1; ++r) {
-                run += s_pre[r * tiles_x + xc];
-                colcum[(int64_t)r * C + xc] = run;
-            }
-        } else {
-            for (int xc = tid; xc < C; xc += 1024) {
-                uint32_t run = 0;
-                for (int r = 0; r < tiles_y; ++r) {
-                    run += s_pre[r * tiles_x + xc];
-                    colcum[(int64_t)r * C + xc] = run;
-                }
-            }
-        }
+// Block c < n_cells: exclusive scan of the cell's row of the matrix over the
+// chunks, in place, and the cell's total.  The last block: the key count of
+// the pass into the status block.
+__global__ __launch_bounds__(256) void k_bin_scan(BinArgs a, DevStatus* st, int which) {
+    __shared__ uint32_t w4[4];
+    const int t = threadIdx.x;
+    constexpr int kPer = kBinMaxChunks / 256;
+    uint32_t total;
+    if (blockIdx.x == a.n_cells) {
+        uint32_t k = 0;
+        for (uint32_t c = t; c < a.chunks; c += 256) k += a.kpart[c].x;
+        (void)block_scan_256(k, w4, &total);
+        if (t == 0) bin_status(a, st, which, total);
         return;
     }
-    if (tid == 0) s_run = 0;
-    __syncthreads();
-    for (int base = 0; base < n_tiles; base += 1024 * 4) {
-        uint32_t v[4], sum = 0;
+    uint32_t* row = a.matrix + (size_t)blockIdx.x * a.chunks;
+    const uint32_t per = (a.chunks + 255) / 256, c0 = t * per;
+    uint32_t v[kPer], sum = 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = base + tid * 4 + j;
-            v[j] = (t < n_tiles && m[t]) ? 1u : 0u;
-            sum += v[j];
-        }
-        uint32_t x = sum;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = __shfl_up(x, off, 64);
-            if (lane >= off) x += y;
-        }
-        if (lane == 63) wsum[wave] = x;
-        __syncthreads();
-        uint32_t acc = s_run;
-        for (int w = 0; w < wave; ++w) acc += wsum[w];
-        acc += x - sum;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int t = base + tid * 4 + j;
-            if (t < n_tiles) {
-                prefix[t] = acc;
-                if (v[j]) list[acc] = (uint32_t)t;
-            }
-            acc += v[j];
-        }
-        __syncthreads();
-        if (tid == 1023) s_run = acc;
-        __syncthreads();
+    for (int j = 0; j < kPer; ++j) {
+        v[j] = ((uint32_t)j < per && c0 + j < a.chunks) ? row[c0 + j] : 0u;
+        sum += v[j];
     }
-    if (tid == 0) {
-        prefix[n_tiles] = s_run;
-        st->n_masked = s_run;
-        st->n_roi_tiles = s_run;
-    }
-    __syncthreads();  // prefix is read back below by other threads of this block
-    // Column sums: a wave takes a column and scans it down the rows 64 at a
-    // time with shuffles.
-    for (int xc = wave; xc <= tiles_x; xc += 16) {
-        uint32_t carry = 0;
-        for (int y0 = 0; y0 < tiles_y; y0 += 64) {
-            const int ty = y0 + lane;
-            const int q = ty * tiles_x + xc;  // xc = tiles_x reads the next row's first entry
-            uint32_t x = ty < tiles_y ? prefix[q] : 0u;
+    uint32_t run = block_scan_256(sum, w4, &total);
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t y = __shfl_up(x, off, 64);
-                if (lane >= off) x += y;
+    for (int j = 0; j < kPer; ++j) {
+        if ((uint32_t)j < per && c0 + j < a.chunks) row[c0 + j] = run;
+        run += v[j];
+    }
+    if (t == 0) a.ctot[blockIdx.x] = total;
+}
+
+// Places the entries.  One workgroup per chunk of the order: 256 surfels at a
+// time, a bitmap per cell of the surfels that have an entry there, from
+// which an entry's rank follows, so that a cell's entries keep the
+// compositing order without a sort.  The first workgroup also writes the
+// cells' first entries and first expansion chunks.  Entries past the
+// capacity are dropped (the key count then exceeds it too, and the pass
+// reports the overflow).  kScan: a small count table is read whole by every
+// workgroup, which takes what it needs of k_bin_scan's sums itself, so that
+// small frames save that launch.
+template <bool kScan>
+__global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int which) {
+    extern __shared__ uint32_t s_dyn[];
+    __shared__ BinStage s;
+    __shared__ uint64_t s_mask[kBinKeep];
+    __shared__ uint32_t s_at[kBinKeep];  // cell << 8 | surfel of the stage
+    __shared__ uint32_t s_n;
+    uint32_t* s_base = s_dyn;              // n_cells
+    uint32_t* s_bits = s_dyn + a.n_cells;  // min(n_cells, kBinWin) x 8 words
+    const int t = threadIdx.x;
+    if (blockIdx.x != 0 && a.kpart[blockIdx.x].y == 0) return;
+    // ctot[c]: the entries of cell c; pre(c): those of earlier chunks.
+    const uint32_t* ctot = a.ctot;
+    if (kScan) {
+        if (blockIdx.x == 0) {
+            uint32_t k = 0, total;
+            for (uint32_t c = t; c < a.chunks; c += 256) k += a.kpart[c].x;
+            (void)block_scan_256(k, s.wsum, &total);
+            if (t == 0) bin_status(a, st, which, total);
+        }
+        uint32_t* s_tot = s_dyn + a.n_cells;  // the bitmap's words, not in use yet
+        for (uint32_t c = t >> 6; c < a.n_cells; c += 4) {
+            const uint32_t* row = a.matrix + (size_t)c * a.chunks;
+            uint32_t pre = 0, tot = 0;
+            for (uint32_t q = t & 63; q < a.chunks; q += 64) {
+                const uint32_t v = row[q];
+                pre += q < blockIdx.x ? v : 0u;
+                tot += v;
             }
-            if (ty < tiles_y) colcum[(int64_t)ty * (tiles_x + 1) + xc] = carry + x;
-            carry += __shfl(x, 63, 64);
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                pre += (uint32_t)__shfl_xor((int)pre, off, 64);
+                tot += (uint32_t)__shfl_xor((int)tot, off, 64);
+            }
+            if ((t & 63) == 0) {
+                s_base[c] = pre;
+                s_tot[c] = tot;
+            }
+        }
+        __syncthreads();
+        ctot = s_tot;
+    }
+    {
+        const uint32_t per = (a.n_cells + 255) / 256, c0 = min(a.n_cells, t * per), c1 = min(a.n_cells, c0 + per);
+        uint32_t sum = 0, total;
+        for (uint32_t c = c0; c < c1; ++c) sum += ctot[c];
+        uint32_t run = block_scan_256(sum, s.wsum, &total);
+        if (blockIdx.x == 0) {
+            uint32_t at = run, nq = 0, all;
+            for (uint32_t c = c0; c < c1; ++c) {
+                const uint32_t e = at + ctot[c];
+                nq += (min(e, a.cap) - min(at, a.cap) + kChunk - 1) / kChunk;
+                at = e;
+            }
+            __syncthreads();
+            uint32_t q = block_scan_256(nq, s.wsum, &all);
+            at = run;
+            for (uint32_t c = c0; c < c1; ++c) {
+                const uint32_t e = at + ctot[c];
+                a.cstart[c] = min(at, a.cap);
+                a.cpre[c] = q;
+                q += (min(e, a.cap) - min(at, a.cap) + kChunk - 1) / kChunk;
+                at = e;
+            }
+            if (t == 0) {
+                a.cstart[a.n_cells] = min(total, a.cap);
+                a.cpre[a.n_cells] = all;
+            }
+        }
+        for (uint32_t c = c0; c < c1; ++c) {
+            s_base[c] = run + (kScan ? s_base[c] : a.matrix[(size_t)c * a.chunks + blockIdx.x]);
+            run += ctot[c];
+        }
+    }
+    int64_t p0, p1;
+    bin_chunk(a, blockIdx.x, &p0, &p1);
+    for (int64_t p = p0; p < p1; p += 256) {
+        __syncthreads();
+        const uint32_t items = bin_stage(a, p, (int)min((int64_t)256, p1 - p), s);
+        if (items == 0) continue;  // uniform
+        for (uint32_t w0 = 0; w0 < a.n_cells; w0 += kBinWin) {
+            const uint32_t nw = min((uint32_t)kBinWin, a.n_cells - w0);
+            for (uint32_t i = t; i < 8 * nw; i += 256) s_bits[i] = 0u;
+            if (t == 0) s_n = 0u;
+            __syncthreads();
+            for (uint32_t it = t; it < items; it += 256)
+                bin_item(a, s, it, [&](int j, uint32_t cell, uint64_t m) {
+                    if (cell - w0 >= nw) return;
+                    atomicOr(&s_bits[8 * (cell - w0) + (j >> 5)], 1u << (j & 31));
+                    const uint32_t e = atomicAdd(&s_n, 1u);
+                    if (e < (uint32_t)kBinKeep) {
+                        s_mask[e] = m;
+                        s_at[e] = cell << 8 | (uint32_t)j;
+                    }
+                });
+            __syncthreads();
+            const auto place = [&](int j, uint32_t cell, uint64_t m) {
+                const uint32_t* b = s_bits + 8 * (cell - w0);
+                uint32_t pos = s_base[cell] + (uint32_t)__popc(b[j >> 5] & ((1u << (j & 31)) - 1u));
+                for (int q = 0; q < (j >> 5); ++q) pos += (uint32_t)__popc(b[q]);
+                if (pos < a.cap) {
+                    a.emask[pos] = m;
+                    a.eid[pos] = s.id[j];
+                }
+            };
+            const uint32_t n = s_n;
+            if (n <= (uint32_t)kBinKeep) {
+                for (uint32_t e = t; e < n; e += 256) place((int)(s_at[e] & 255u), s_at[e] >> 8, s_mask[e]);
+            } else {  // the nearest surfels: more entries than are kept, so their masks are formed again
+                for (uint32_t it = t; it < items; it += 256)
+                    bin_item(a, s, it, [&](int j, uint32_t cell, uint64_t m) {
+                        if (cell - w0 < nw) place(j, cell, m);
+                    });
+            }
+            __syncthreads();
+            if (p + 256 < p1)
+                for (uint32_t c = t; c < nw; c += 256) {
+                    uint32_t k = 0;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) k += (uint32_t)__popc(s_bits[8 * c + q]);
+                    s_base[w0 + c] += k;
+                }
         }
     }
 }
 
-// ---------------------------------------------------------------------------
+// The cell that expansion chunk q belongs to: the last with cp[cell] <= q
+// (cells without entries share their successor's and are never chosen).
+__device__ __forceinline__ uint32_t chunk_cell(const uint32_t* cp, uint32_t n_cells, uint32_t q) {
+    uint32_t lo = 0, hi = n_cells - 1;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi + 1) >> 1;
+        if (cp[mid] <= q) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// Expansion of a chunk of a cell's entries (lane = entry), in four quarters
+// of two rows of the cell's tiles: the same 16 bits of every entry's mask.
+// Where there are many chunks a wave takes a whole chunk; where there are
+// few (small frames) the four waves of a workgroup take a quarter each,
+// which is four times sooner done.  The chunks are taken grid-stride: their
+// number is known only on the device.
+constexpr uint32_t kManyChunks = 4096;
+
+struct ExpandStage {
+    uint32_t i0, i1, cell;
+    uint64_t m[kChunk / 64];  // the masks of the lane's entries
+};
+
+struct ExpandPlan {
+    uint32_t nq, q0, step;  // chunks, the wave's first, the stride
+    int t0, t1;             // the wave's quarters
+    __device__ __forceinline__ ExpandPlan(uint32_t n) : nq(n) {
+        const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const bool many = nq > kManyChunks;
+        q0 = many ? blockIdx.x * 4 + (uint32_t)w : blockIdx.x;
+        step = many ? gridDim.x * 4 : gridDim.x;
+        t0 = many ? 0 : w;
+        t1 = many ? 4 : w + 1;
+    }
+};
+
+__device__ __forceinline__ void expand_load(const BinArgs& a, const uint32_t* cp, uint32_t q, int lane, ExpandStage& s) {
+    s.cell = chunk_cell(cp, a.n_cells, q);
+    s.i0 = a.cstart[s.cell] + (q - cp[s.cell]) * kChunk;
+    s.i1 = min(s.i0 + kChunk, a.cstart[s.cell + 1]);
+#pragma unroll
+    for (int g = 0; g < kChunk / 64; ++g) {
+        const uint32_t e = s.i0 + 64 * g + lane;
+        s.m[g] = e < s.i1 ? a.emask[e] : 0ull;
+    }
+}
+
+__device__ __forceinline__ void expand_quarter(const ExpandStage& s, int t, uint32_t (&m)[kChunk / 64]) {
+#pragma unroll
+    for (int g = 0; g < kChunk / 64; ++g) m[g] = (uint32_t)(s.m[g] >> (16 * t));
+}
+
+// The lanes whose mask has bit l.
+__device__ __forceinline__ uint64_t tile_lanes(uint32_t m, int l) { return __ballot((m & (1u << l)) != 0u); }
+
+// Keys of each tile in each chunk.
+__global__ __launch_bounds__(256) void k_tile_count(BinArgs a) {
+    extern __shared__ uint32_t s_cp[];  // n_cells + 1 words
+    const int lane = threadIdx.x & 63;
+    const ExpandPlan pl(a.cpre[a.n_cells]);
+    if (blockIdx.x >= pl.nq) return;
+    for (uint32_t c = threadIdx.x; c <= a.n_cells; c += 256) s_cp[c] = a.cpre[c];
+    __syncthreads();
+    for (uint32_t q = pl.q0; q < pl.nq; q += pl.step) {
+        ExpandStage s;
+        expand_load(a, s_cp, q, lane, s);
+        for (int t = pl.t0; t < pl.t1; ++t) {
+            uint32_t m[kChunk / 64], cnt = 0;
+            expand_quarter(s, t, m);
+#pragma unroll
+            for (int l = 0; l < 16; ++l) {
+                uint32_t k = 0;
+#pragma unroll
+                for (int g = 0; g < kChunk / 64; ++g) k += (uint32_t)__popcll(tile_lanes(m[g], l));
+                if (lane == l) cnt = k;
+            }
+            if (lane < 16) a.tcount[(size_t)q * 64 + 16 * t + lane] = cnt;
+        }
+    }
+}
+
+__device__ __forceinline__ void write_tile_total(const BinArgs& a, uint32_t cell, int lane, uint32_t total) {
+    const int tx = (int)(cell % a.cells_x) * 8 + (lane & 7), ty = (int)(cell / a.cells_x) * 8 + (lane >> 3);
+    if (tx < a.tiles_x && ty < a.tiles_y) a.ttot[(int64_t)ty * a.tiles_x + tx] = total;
+}
+
+// One workgroup per cell: exclusive scan of its tiles' counts (lane = tile)
+// over its chunks, in place (a wave takes eight chunks of 128 per round),
+// and the tiles' totals.
+__global__ __launch_bounds__(1024) void k_tile_scan(BinArgs a) {
+    __shared__ uint32_t s_sum[2][16][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t q0 = a.cpre[blockIdx.x], q1 = a.cpre[blockIdx.x + 1];
+    uint32_t carry = 0;
+    int buf = 0;
+    for (uint32_t base = q0; base < q1; base += 128, buf ^= 1) {
+        uint32_t v[8], sum = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t q = base + 8 * w + j;
+            v[j] = q < q1 ? a.tcount[(size_t)q * 64 + lane] : 0u;
+            sum += v[j];
+        }
+        s_sum[buf][w][lane] = sum;
+        __syncthreads();  // two buffers: the next round's writes need no barrier of their own
+        uint32_t run = carry;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const uint32_t x = s_sum[buf][k][lane];
+            run += k < w ? x : 0u;
+            carry += x;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t q = base + 8 * w + j;
+            if (q < q1) a.tcount[(size_t)q * 64 + lane] = run;
+            run += v[j];
+        }
+    }
+    if (w == 0) write_tile_total(a, blockIdx.x, lane, carry);
+}
+
+// The same for one cell by a single wave, without barriers.
+__device__ __forceinline__ void tile_scan_wave(const BinArgs& a, uint32_t cell, int lane) {
+    const uint32_t q0 = a.cpre[cell], q1 = a.cpre[cell + 1];
+    uint32_t run = 0;
+    for (uint32_t base = q0; base < q1; base += 16) {
+        uint32_t v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = base + j < q1 ? a.tcount[(size_t)(base + j) * 64 + lane] : 0u;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            if (base + j < q1) a.tcount[(size_t)(base + j) * 64 + lane] = run;
+            run += v[j];
+        }
+    }
+    write_tile_total(a, cell, lane, run);
+}
+
+// The plan scans the cells itself, one wave each, up to this many cells and
+// surfels (so at most 64 chunks of a cell): small frames save a launch.
+constexpr uint32_t kPlanCells = 16;
+constexpr int kPlanSurfels = 16384;
+
 // Tile order for the blend: tiles by decreasing key count, bucketed by the
 // leading bit and the next four bits of the count (about 6% resolution), so
 // that the heaviest tiles are dispatched first and spread over all CUs.
 // The order only decides which block renders which tile; every tile's
 // pixels are computed the same way whatever the order.
-// ---------------------------------------------------------------------------
 constexpr int kOrderBuckets = 32 * 16 + 1;  // (octave, 4 mantissa bits), then empty tiles
 
 __device__ __forceinline__ uint32_t order_bucket(uint32_t len) {
@@ -1079,67 +994,183 @@ __device__ __forceinline__ uint32_t order_bucket(uint32_t len) {
     return (31u - e) * 16u + (15u - m);
 }
 
-// Up to kOrderHeld tiles: each thread loads its ranges at once (bounded by
-// n_tiles, so the loads need not wait for the live count) and keeps their
-// buckets in registers for both passes.
-constexpr uint32_t kOrderRegs = 8, kOrderHeld = 1024 * kOrderRegs;
+// One workgroup: the tiles' list ranges (their totals scanned in tile order,
+// clamped to the capacity), and the dispatch order of the live tiles (the
+// masked ones with a mask, whose number goes to the status block).  Latency
+// bound: up to kPlanHeld tiles are read once and kept in registers, and
+// every bucket has kPlanSub counters, taken by lane, because the returning
+// LDS atomics of a wave on one counter run one after the other.
+constexpr int kPlanSub = 8;
+constexpr int kPlanCounters = kOrderBuckets * kPlanSub;
 
-__global__ __launch_bounds__(1024) void k_tile_order(const uint2* __restrict__ ranges, const uint32_t* n_live,
-                                                     uint32_t n_tiles, uint32_t* __restrict__ order) {
-    __shared__ uint32_t hist[kOrderBuckets];
-    __shared__ uint32_t wsum[16];
+template <int kPlanRegs, bool kScan>
+__global__ __launch_bounds__(1024) void k_tile_plan(BinArgs a, uint32_t n_tiles, uint2* __restrict__ ranges,
+                                                    uint32_t* __restrict__ order, DevStatus* st) {
+    constexpr int kPlanHeld = 1024 * kPlanRegs;
+    constexpr int kPer = (kPlanCounters + 1023) / 1024;  // counters per thread of their scan
+    __shared__ uint32_t hist[1024 * kPer];
+    __shared__ uint32_t wsum[2][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool held = n_tiles <= kOrderHeld;
-    uint32_t bk[kOrderRegs];
-    if (held) {
-        uint2 r[kOrderRegs];
+    const uint32_t sub = (uint32_t)tid & (kPlanSub - 1);
+    for (int i = tid; i < 1024 * kPer; i += 1024) hist[i] = 0;
+    if (kScan && (uint32_t)wave < a.n_cells) tile_scan_wave(a, (uint32_t)wave, lane);  // the barrier below publishes it
+    const auto live = [&](uint32_t t) {
+        if (t >= n_tiles) return false;
+        if (!a.mask.cells) return true;
+        const uint32_t ty = t / (uint32_t)a.tiles_x, tx = t - ty * (uint32_t)a.tiles_x;
+        return ((a.mask.cells[(ty >> 3) * a.cells_x + (tx >> 3)] >> (8 * (ty & 7) + (tx & 7))) & 1ull) != 0;
+    };
+    uint32_t bk[kPlanRegs];  // the order bucket of each held tile, or none
+    uint32_t carry = 0;
+    int buf = 0;
+    __syncthreads();
+    for (uint32_t base = 0; base < n_tiles; base += kPlanHeld, buf ^= 1) {
+        uint32_t v[kPlanRegs], sum = 0;
+        const uint32_t t0 = base + (uint32_t)tid * kPlanRegs;
 #pragma unroll
-        for (uint32_t u = 0; u < kOrderRegs; ++u) {
-            const uint32_t t = tid + 1024u * u;
-            r[u] = t < n_tiles ? ranges[t] : make_uint2(0u, 0u);
+        for (int u = 0; u < kPlanRegs; ++u) {
+            v[u] = t0 + u < n_tiles ? a.ttot[t0 + u] : 0u;
+            sum += v[u];
+        }
+        const uint32_t x = wave_scan_u32(sum, lane);
+        if (lane == 63) wsum[buf][wave] = x;
+        __syncthreads();
+        uint32_t run = carry + x - sum;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const uint32_t y = wsum[buf][w];
+            run += w < wave ? y : 0u;
+            carry += y;
         }
 #pragma unroll
-        for (uint32_t u = 0; u < kOrderRegs; ++u) bk[u] = order_bucket(r[u].y - r[u].x);
+        for (int u = 0; u < kPlanRegs; ++u) {
+            const uint32_t r0 = min(run, a.cap), r1 = min(run + v[u], a.cap);
+            run += v[u];
+            bk[u] = 0xFFFFFFFFu;
+            if (t0 + u < n_tiles) {
+                ranges[t0 + u] = make_uint2(r0, r1);
+                if (live(t0 + u)) {
+                    bk[u] = order_bucket(r1 - r0) * kPlanSub + sub;
+                    atomicAdd(&hist[bk[u]], 1u);
+                }
+            }
+        }
     }
-    const uint32_t n = n_live ? min(*n_live, n_tiles) : n_tiles;
-    for (int i = tid; i < kOrderBuckets; i += 1024) hist[i] = 0;
     __syncthreads();
-    if (held) {
+    // Exclusive scan of the counters.
+    uint32_t hv[kPer], sum = 0;
 #pragma unroll
-        for (uint32_t u = 0; u < kOrderRegs; ++u)
-            if (tid + 1024u * u < n) atomicAdd(&hist[bk[u]], 1u);
+    for (int j = 0; j < kPer; ++j) {
+        hv[j] = hist[tid * kPer + j];
+        sum += hv[j];
+    }
+    const uint32_t x = wave_scan_u32(sum, lane);
+    if (lane == 63) wsum[buf][wave] = x;
+    __syncthreads();
+    uint32_t before = x - sum, n_live = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        const uint32_t y = wsum[buf][w];
+        before += w < wave ? y : 0u;
+        n_live += y;
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        hist[tid * kPer + j] = before;
+        before += hv[j];
+    }
+    if (tid == 0 && a.mask.cells) {
+        st->n_masked = n_live;
+        st->n_roi_tiles = n_live;
+    }
+    __syncthreads();
+    if (n_tiles <= (uint32_t)kPlanHeld) {
+#pragma unroll
+        for (int u = 0; u < kPlanRegs; ++u)
+            if (bk[u] != 0xFFFFFFFFu) order[atomicAdd(&hist[bk[u]], 1u)] = (uint32_t)tid * kPlanRegs + u;
     } else {
-        for (uint32_t t = tid; t < n; t += 1024) {
-            const uint2 r = ranges[t];
-            atomicAdd(&hist[order_bucket(r.y - r.x)], 1u);
-        }
+        // The counter of a tile is that of the thread that counted it.
+        for (uint32_t base = 0; base < n_tiles; base += kPlanHeld)
+            for (int u = 0; u < kPlanRegs; ++u) {
+                const uint32_t t = base + (uint32_t)tid * kPlanRegs + u;
+                if (!live(t)) continue;
+                const uint2 r = ranges[t];  // written above by this thread
+                order[atomicAdd(&hist[order_bucket(r.y - r.x) * kPlanSub + sub], 1u)] = t;
+            }
     }
+}
+
+// Writes the tile lists.  A tile's lanes are a ballot of its mask bit; they
+// store their surfels at consecutive places of the tile's list, so a store
+// leaves as one run of a line or two, without a pass through LDS (appending
+// through an LDS buffer, 17 KiB a wave, took 242 us where this takes 89, on
+// 8.7e7 keys of a 1920x1080 frame: 3.9 TB/s written).
+__global__ __launch_bounds__(256) void k_tile_write(BinArgs a, const uint2* __restrict__ ranges) {
+    extern __shared__ uint32_t s_cp[];  // n_cells + 1 words
+    const int lane = threadIdx.x & 63;
+    const ExpandPlan pl(a.cpre[a.n_cells]);
+    if (blockIdx.x >= pl.nq) return;
+    for (uint32_t c = threadIdx.x; c <= a.n_cells; c += 256) s_cp[c] = a.cpre[c];
     __syncthreads();
-    // Exclusive scan of the buckets (one per thread).
-    uint32_t v = tid < kOrderBuckets ? hist[tid] : 0u, x = v;
+    for (uint32_t q = pl.q0; q < pl.nq; q += pl.step) {
+        ExpandStage s;
+        expand_load(a, s_cp, q, lane, s);
+        uint32_t id[kChunk / 64];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(x, off, 64);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) wsum[wave] = x;
-    __syncthreads();
-    uint32_t wbase = 0;
-    for (int w = 0; w < wave; ++w) wbase += wsum[w];
-    if (tid < kOrderBuckets) hist[tid] = wbase + x - v;
-    __syncthreads();
-    if (held) {
+        for (int g = 0; g < kChunk / 64; ++g) {
+            const uint32_t e = s.i0 + 64 * g + lane;
+            id[g] = e < s.i1 ? a.eid[e] : 0u;
+        }
+        // Lane = tile: where the chunk's run of its list begins.
+        const int tx = (int)(s.cell % a.cells_x) * 8 + (lane & 7), ty = (int)(s.cell / a.cells_x) * 8 + (lane >> 3);
+        const bool in = tx < a.tiles_x && ty < a.tiles_y;
+        const uint32_t base = in ? ranges[(int64_t)ty * a.tiles_x + tx].x + a.tcount[(size_t)q * 64 + lane] : 0u;
+        for (int t = pl.t0; t < pl.t1; ++t) {
+            uint32_t m[kChunk / 64];
+            expand_quarter(s, t, m);
 #pragma unroll
-        for (uint32_t u = 0; u < kOrderRegs; ++u) {
-            const uint32_t t = tid + 1024u * u;
-            if (t < n) order[atomicAdd(&hist[bk[u]], 1u)] = t;
-        }
-    } else {
-        for (uint32_t t = tid; t < n; t += 1024) {
-            const uint2 r = ranges[t];
-            order[atomicAdd(&hist[order_bucket(r.y - r.x)], 1u)] = t;
+            for (int l = 0; l < 16; ++l) {
+                uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)base, 16 * t + l);
+#pragma unroll
+                for (int g = 0; g < kChunk / 64; ++g) {
+                    const uint64_t has = tile_lanes(m[g], l);
+                    if (has) {  // uniform
+                        const uint32_t pos = b + __builtin_amdgcn_mbcnt_hi(
+                                                     (uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
+                        if (__builtin_amdgcn_inverse_ballot_w64(has) && pos < a.cap) a.vals[pos] = id[g];
+                        b += (uint32_t)__popcll(has);
+                    }
+                }
+            }
         }
     }
+}
+
+// The masked tiles of each cell, from an ROI tile mask of T x T pixel tiles
+// (a 16-pixel tile is masked iff it overlaps a masked T-tile).  A wave per
+// cell, a lane per tile.
+__global__ __launch_bounds__(256) void k_cell_masks(const uint8_t* __restrict__ tm, int T, int tw, int th, int tiles_x,
+                                                    int tiles_y, int cells_x, int n_cells,
+                                                    uint64_t* __restrict__ cells) {
+    const int lane = threadIdx.x & 63, cell = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (cell >= n_cells) return;  // whole wave
+    const int tx = cell % cells_x * 8 + (lane & 7), ty = cell / cells_x * 8 + (lane >> 3);
+    bool v = false;
+    if (tx < tiles_x && ty < tiles_y) {
+        if (T == 16) {
+            v = tm[ty * tw + tx] != 0;
+        } else if (T == 32) {
+            v = tm[(ty >> 1) * tw + (tx >> 1)] != 0;
+        } else {  // T == 8: any of the (up to) four 8x8 tiles of this 16x16 tile
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int qx = 2 * tx + (u & 1), qy = 2 * ty + (u >> 1);
+                v = v || (qx < tw && qy < th && tm[qy * tw + qx] != 0);
+            }
+        }
+    }
+    const uint64_t m = __ballot(v);
+    if (lane == 0) cells[cell] = m;
 }
 
 // ---------------------------------------------------------------------------
@@ -1311,9 +1342,9 @@ __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uin
 }
 
 __device__ __forceinline__ void load_rec(const SurfelRec* __restrict__ recs, const uint32_t* __restrict__ vals,
-                                         uint32_t pos, uint32_t vmask, float4& q0, float4& q1, float4& q2,
+                                         uint32_t pos, float4& q0, float4& q1, float4& q2,
                                          float4& q3) {
-    const SurfelRec* r = recs + (vals[pos] & vmask);
+    const SurfelRec* r = recs + vals[pos];
     q0 = r->a;
     q1 = r->b;
     q2 = r->c;
@@ -1326,7 +1357,7 @@ template <bool kXfer>
 __device__ __forceinline__ void load_rec(const SurfelRec* __restrict__ recs, const uint32_t* __restrict__ vals,
                                          uint32_t pos, const BlendArgs& a, float4& q0, float4& q1, float4& q2,
                                          float4& q3, float4& qx) {
-    const uint32_t k = vals[pos] & a.vmask;
+    const uint32_t k = vals[pos];
     const SurfelRec* r = recs + k;
     q0 = r->a;
     q1 = r->b;
@@ -1348,13 +1379,13 @@ __device__ __forceinline__ void walk_range(const SurfelRec* __restrict__ recs, c
                                            uint32_t b, uint32_t e, float4* s_rec, uint16_t* s_list,
                                            const TileGeom& g, const BlendArgs& a, PixelState& p, WalkCounts& wc) {
     float4 q0, q1, q2, q3;
-    if (b + g.tid < e) load_rec(recs, vals, b + g.tid, a.vmask, q0, q1, q2, q3);
+    if (b + g.tid < e) load_rec(recs, vals, b + g.tid, q0, q1, q2, q3);
     for (uint32_t base = b; base < e; base += kBatch) {
         const uint32_t nb = min((uint32_t)kBatch, e - base);
         __syncthreads();
         if ((uint32_t)g.tid < nb) stage_rec(s_rec, g.tid, q0, q1, q2, q3);
         __syncthreads();
-        if (base + kBatch + g.tid < e) load_rec(recs, vals, base + kBatch + g.tid, a.vmask, q0, q1, q2, q3);
+        if (base + kBatch + g.tid < e) load_rec(recs, vals, base + kBatch + g.tid, q0, q1, q2, q3);
         walk_batch<kCount>(s_rec, nb, s_list, g, a, p, wc);
         if (__syncthreads_count(live(p)) == 0) break;
     }
@@ -1423,13 +1454,11 @@ __device__ __forceinline__ void count_flush(const WalkCounts& wc, int lane, int 
     }
 }
 
-// One block per tile (compact id blk, taken in the order given, heaviest
-// lists first): composite the whole list, then write the pixels.  kPatch:
+// One block per tile (taken in the order given, heaviest lists first): composite the whole list, then write the pixels.  kPatch:
 // ROI patch of the affiliated eye (writes the depth proxy and the class).
 template <bool kCount, bool kPatch, bool kXfer = false>
 __global__ __launch_bounds__(256) void k_blend(const SurfelRec* __restrict__ recs, const uint32_t* __restrict__ vals,
-                                               const uint2* __restrict__ ranges, const uint32_t* __restrict__ tile_list,
-                                               const uint32_t* __restrict__ order,
+                                               const uint2* __restrict__ ranges, const uint32_t* __restrict__ order,
                                                const uint32_t* __restrict__ n_live, BlendArgs a, ContArgs ca,
                                                float* __restrict__ rgb, float* __restrict__ dz,
                                                float* __restrict__ alpha, uint8_t* __restrict__ cls,
@@ -1444,12 +1473,11 @@ __global__ __launch_bounds__(256) void k_blend(const SurfelRec* __restrict__ rec
     const long long t_begin = kCount ? wall_clock64() : 0;
     const uint32_t blk = blockIdx.x;
     if (n_live && blk >= *n_live) return;
-    const uint32_t cid = order ? order[blk] : blk;
-    const uint32_t tile = tile_list ? tile_list[cid] : cid;
+    const uint32_t tile = order[blk];
     bool inside;
     int px, py;
     const TileGeom g = tile_geom(tile, (int)threadIdx.x, a, &inside, &px, &py);
-    const uint2 rg = ranges[cid];
+    const uint2 rg = ranges[tile];
     PixelState p{inside ? 1.f : 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     WalkCounts wc{0, 0, 0, 0};
     if (g.tid < 4) s_rec[4 * kDummy + g.tid] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1515,7 +1543,7 @@ __global__ __launch_bounds__(256) void k_blend(const SurfelRec* __restrict__ rec
                 if (slot < ca.max_slots) {
                     const uint32_t nseg = min(kContMaxSeg, max(1u, (rem + ca.seg_len - 1) / ca.seg_len));
                     const uint32_t ibase = atomicAdd(ca.n_items, nseg);
-                    ca.slot_desc[slot] = make_uint4(cid, cap_end, rg.y, ibase | (nseg << kContSegShift));
+                    ca.slot_desc[slot] = make_uint4(tile, cap_end, rg.y, ibase | (nseg << kContSegShift));
                     s_slot = slot;
                     s_ibase = ibase;
                     s_nseg = nseg;
@@ -1602,7 +1630,7 @@ __device__ __forceinline__ void item_segment(const uint4& d, uint32_t k, uint32_
 template <bool kCount>
 __global__ __launch_bounds__(256) void k_blend_seg(const SurfelRec* __restrict__ recs,
                                                    const uint32_t* __restrict__ vals,
-                                                   const uint32_t* __restrict__ tile_list, BlendArgs a, ContArgs ca,
+                                                   BlendArgs a, ContArgs ca,
                                                    int round, unsigned long long* __restrict__ pair_counts) {
     __shared__ float4 s_rec[(kBatch + 1) * 4];
     __shared__ __align__(8) uint16_t s_list[4 * kListLen];
@@ -1621,7 +1649,7 @@ __global__ __launch_bounds__(256) void k_blend_seg(const SurfelRec* __restrict__
         item_segment(d, k, &sb, &se);
         bool inside;
         int px, py;
-        const TileGeom g = tile_geom(tile_list ? tile_list[d.x] : d.x, tid, a, &inside, &px, &py);
+        const TileGeom g = tile_geom(d.x, tid, a, &inside, &px, &py);
         const float4 s1 = ca.st1[(size_t)slot * 512 + 2 * tid + 1];
         Chain c{s1.y, 0.f, 0.f, 0.f, 0.f, 0.f};
         bool live = s1.z != 0.f;
@@ -1661,7 +1689,7 @@ __global__ __launch_bounds__(256) void k_blend_seg(const SurfelRec* __restrict__
 // segment j and j + 1 replace the slot's state after the capped walk, for
 // k_blend_fix.
 template <bool kPatch>
-__global__ __launch_bounds__(256) void k_blend_chain(const uint32_t* __restrict__ tile_list, BlendArgs a, ContArgs ca,
+__global__ __launch_bounds__(256) void k_blend_chain(BlendArgs a, ContArgs ca,
                                                      float* __restrict__ rgb, float* __restrict__ dz,
                                                      float* __restrict__ alpha, uint8_t* __restrict__ cls) {
     const uint32_t n_slots = min(*ca.n_slots, ca.max_slots);
@@ -1671,7 +1699,7 @@ __global__ __launch_bounds__(256) void k_blend_chain(const uint32_t* __restrict_
         const uint32_t ibase = d.w & ((1u << kContSegShift) - 1u), nseg = d.w >> kContSegShift;
         bool inside;
         int px, py;
-        (void)tile_geom(tile_list ? tile_list[d.x] : d.x, tid, a, &inside, &px, &py);
+        (void)tile_geom(d.x, tid, a, &inside, &px, &py);
         float4* st = ca.st1 + (size_t)slot * 512 + 2 * tid;
         const float4 s0 = st[0], s1 = st[1];
         if (s1.z == 0.f) continue;  // done before the cap and written then
@@ -1725,7 +1753,7 @@ __global__ __launch_bounds__(256) void k_blend_chain(const uint32_t* __restrict_
 template <bool kCount, bool kPatch>
 __global__ __launch_bounds__(256) void k_blend_fix(const SurfelRec* __restrict__ recs,
                                                    const uint32_t* __restrict__ vals,
-                                                   const uint32_t* __restrict__ tile_list, BlendArgs a, ContArgs ca,
+                                                   BlendArgs a, ContArgs ca,
                                                    float* __restrict__ rgb, float* __restrict__ dz,
                                                    float* __restrict__ alpha, uint8_t* __restrict__ cls,
                                                    unsigned long long* __restrict__ pair_counts) {
@@ -1747,7 +1775,7 @@ __global__ __launch_bounds__(256) void k_blend_fix(const SurfelRec* __restrict__
         item_segment(d, k, &sb, &se);
         bool inside;
         int px, py;
-        const TileGeom g = tile_geom(tile_list ? tile_list[d.x] : d.x, tid, a, &inside, &px, &py);
+        const TileGeom g = tile_geom(d.x, tid, a, &inside, &px, &py);
         PixelState q{need ? s1.y : 0.f, s0.x, s0.y, s0.z, s0.w, s1.x};
         walk_range<kCount>(recs, vals, sb, se, s_rec, s_list + (tid >> 6) * kListLen, g, a, q, wc);
         // A pixel still compositing at the segment's end (whose crossing of
@@ -1763,56 +1791,76 @@ __global__ __launch_bounds__(256) void k_blend_fix(const SurfelRec* __restrict__
 }  // namespace
 
 hipError_t launch_preprocess(const SceneArgs& sc, const PreCam& cam, float alpha_min, int lowpass,
-                             const MaskArgs& mask, SurfelRec* recs, uint32_t* zkeys, uint2* rects,
+                             const CellMask& mask, SurfelRec* recs, uint32_t* zkeys, uint2* rects,
                              uint32_t* counts, const PreCam* cam2, SurfelRec* recs2, uint32_t* zkeys2,
-                             uint2* rects2, uint32_t* nseg, hipStream_t s) {
+                             uint2* rects2, hipStream_t s) {
     if (sc.n <= 0) return hipSuccess;
     const dim3 g((sc.n + 255) / 256);
+    if (cam2 && counts) return hipErrorInvalidValue;  // counts are of a single camera
     if (cam2)
-        hipLaunchKernelGGL(k_preprocess<true>, g, dim3(256), 0, s, sc, cam, *cam2, alpha_min, lowpass, mask, recs, zkeys,
-                           rects, counts, recs2, zkeys2, rects2, nseg);
+        hipLaunchKernelGGL((k_preprocess<true, false>), g, dim3(256), 0, s, sc, cam, *cam2, alpha_min, lowpass, mask,
+                           recs, zkeys, rects, nullptr, recs2, zkeys2, rects2);
+    else if (counts)
+        hipLaunchKernelGGL((k_preprocess<false, true>), g, dim3(256), 0, s, sc, cam, cam, alpha_min, lowpass, mask,
+                           recs, zkeys, rects, counts, nullptr, nullptr, nullptr);
     else
-        hipLaunchKernelGGL(k_preprocess<false>, g, dim3(256), 0, s, sc, cam, cam, alpha_min, lowpass, mask, recs, zkeys,
-                           rects, counts, nullptr, nullptr, nullptr, nseg);
+        hipLaunchKernelGGL((k_preprocess<false, false>), g, dim3(256), 0, s, sc, cam, cam, alpha_min, lowpass, mask,
+                           recs, zkeys, rects, nullptr, nullptr, nullptr, nullptr);
     return hipGetLastError();
 }
 
-hipError_t launch_masked_counts_ordered(const uint2* rects, const SurfelRec* recs, const uint32_t* order, int n,
-                                        int n_tiles, const MaskArgs& mask, uint32_t* counts, uint32_t* partials,
-                                        uint32_t* nseg, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    // The mask prefix is read from global memory (it stays in L2): staging it
-    // in LDS per workgroup cost more than the lookups (emission and counts of
-    // a 1M-surfel, 6700-tile ROI pass: 111 -> 94 us).
-    const int mask_lds = 0;
-    hipLaunchKernelGGL(k_masked_counts_ordered, dim3((unsigned)((n + 255) / 256)), dim3(256),
-                       (size_t)mask_lds * sizeof(uint32_t), s, rects, recs, order, n, mask, mask_lds, counts,
-                       partials, nseg);
+hipError_t launch_cell_masks(const uint8_t* tmask, int T, int W, int H, uint64_t* cells, hipStream_t s) {
+    if (T != 8 && T != 16 && T != 32) return hipErrorInvalidValue;
+    const int tiles_x = (W + kTile - 1) / kTile, tiles_y = (H + kTile - 1) / kTile;
+    const int cells_x = (tiles_x + 7) / 8, n_cells = cells_x * ((tiles_y + 7) / 8);
+    hipLaunchKernelGGL(k_cell_masks, dim3((unsigned)((n_cells + 3) / 4)), dim3(256), 0, s, tmask, T, (W + T - 1) / T,
+                       (H + T - 1) / T, tiles_x, tiles_y, cells_x, n_cells, cells);
     return hipGetLastError();
 }
 
-hipError_t launch_masked_counts(const uint2* rects, const SurfelRec* recs, int n, int n_tiles, const MaskArgs& mask,
-                                uint32_t* counts, uint32_t* nseg, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int mask_lds = n_tiles + 1 <= kEmitMaskLds ? n_tiles + 1 : 0;
-    hipLaunchKernelGGL(k_masked_counts, dim3((n + 255) / 256), dim3(256), (size_t)mask_lds * sizeof(uint32_t), s,
-                       rects, recs, n, mask, mask_lds, counts, nseg);
+hipError_t launch_bin_entries(const BinArgs& a, DevStatus* st, int which, hipStream_t s) {
+    // One workgroup per chunk of the order; the LDS holds a word per cell
+    // (64 KiB at 16384x16384) and the emission's bitmap window.
+    const size_t cells = 4 * (size_t)a.n_cells;
+    const size_t bits = 32 * (size_t)std::min<uint32_t>(a.n_cells, kBinWin);
+    if (a.chunks < 1 || a.chunks > (uint32_t)kBinMaxChunks || a.fine > a.chunks || a.per < 256 || a.per % 256) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_bin_count, dim3(a.chunks), dim3(256), cells, s, a);
+    if ((uint64_t)a.n_cells * a.chunks <= kBinSmallTable) {
+        hipLaunchKernelGGL(k_bin_emit<true>, dim3(a.chunks), dim3(256), cells + bits, s, a, st, which);
+    } else {
+        hipLaunchKernelGGL(k_bin_scan, dim3(a.n_cells + 1), dim3(256), 0, s, a, st, which);
+        hipLaunchKernelGGL(k_bin_emit<false>, dim3(a.chunks), dim3(256), cells + bits, s, a, st, which);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_emit(const uint32_t* order, const uint32_t* offs, const uint2* rects, const SurfelRec* recs, int n,
-                       int tiles_x, int n_tiles, const MaskArgs& mask, uint32_t cap, int vbits, uint32_t* tkeys,
-                       uint32_t* tvals, const uint32_t* nseg, int nseg_by_pos, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    if (vbits < 0 || vbits > 31 || (vbits && (int64_t)n > ((int64_t)1 << vbits))) return hipErrorInvalidValue;
-    const int mask_lds = 0;  // the mask prefix is read from global memory (see launch_masked_counts_ordered)
-    // Unmasked, the surfels nearest the camera (first in compositing order)
-    // carry several times the mean key count: 128 surfels per workgroup
-    // halve the heaviest workgroups (65 -> 49 us on a 5.9M-key frame).
-    // Masked, most surfels have no key and 256 per workgroup cost less.
-    const int spb = mask.enabled ? 256 : 128;
-    hipLaunchKernelGGL(k_emit, dim3((n + spb - 1) / spb), dim3(256), (size_t)mask_lds * sizeof(uint32_t), s, order,
-                       offs, rects, recs, n, spb, tiles_x, mask, mask_lds, cap, vbits, tkeys, tvals, nseg, nseg_by_pos);
+// Grid of the chunk-strided kernels: enough workgroups for the chunks that
+// the key capacity allows, at most eight per CU.
+static unsigned expand_grid(const BinArgs& a) {
+    return (unsigned)std::min<uint64_t>(2048, bin_max_expand_chunks(a.cap, a.n_cells));
+}
+
+hipError_t launch_tile_plan(const BinArgs& a, uint2* ranges, uint32_t* order, DevStatus* st, hipStream_t s) {
+    const size_t cp = 4 * ((size_t)a.n_cells + 1);
+    hipLaunchKernelGGL(k_tile_count, dim3(expand_grid(a)), dim3(256), cp, s, a);
+    const uint32_t n_tiles = (uint32_t)(a.tiles_x * a.tiles_y);
+    const dim3 one(1), wg(1024);
+    if (a.n_cells <= kPlanCells && a.n <= kPlanSurfels) {  // at most 1024 tiles
+        hipLaunchKernelGGL((k_tile_plan<1, true>), one, wg, 0, s, a, n_tiles, ranges, order, st);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_tile_scan, dim3(a.n_cells), dim3(1024), 0, s, a);
+    if (n_tiles <= 4 * 1024)
+        hipLaunchKernelGGL((k_tile_plan<4, false>), one, wg, 0, s, a, n_tiles, ranges, order, st);
+    else if (n_tiles <= 8 * 1024)
+        hipLaunchKernelGGL((k_tile_plan<8, false>), one, wg, 0, s, a, n_tiles, ranges, order, st);
+    else
+        hipLaunchKernelGGL((k_tile_plan<20, false>), one, wg, 0, s, a, n_tiles, ranges, order, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_write(const BinArgs& a, const uint2* ranges, hipStream_t s) {
+    hipLaunchKernelGGL(k_tile_write, dim3(expand_grid(a)), dim3(256), 4 * ((size_t)a.n_cells + 1), s, a, ranges);
     return hipGetLastError();
 }
 
@@ -1871,12 +1919,11 @@ __global__ __launch_bounds__(256) void k_blend_batch(const BatchBlendDesc* __res
         }
         const BatchBlendDesc d = descs[lo];
         const uint32_t blk = item - prefix[lo];
-        const uint32_t cid = d.order ? d.order[blk] : blk;
-        const uint32_t tile = d.tile_list ? d.tile_list[cid] : cid;
+        const uint32_t tile = d.order[blk];
         bool inside;
         int px, py;
         const TileGeom g = tile_geom(tile, tid, d.a, &inside, &px, &py);
-        const uint2 rg = d.ranges[cid];
+        const uint2 rg = d.ranges[tile];
         PixelState p{inside ? 1.f : 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         walk_range<false>(d.recs, d.vals, rg.x, rg.y, s_rec, s_list + (tid >> 6) * kListLen, g, d.a, p, wc);
         if (inside) write_pixel<kPatch>(p, px, py, d.a, d.rgb, d.dz, d.alpha, d.cls);
@@ -1896,76 +1943,7 @@ hipError_t launch_blend_batch(const BatchBlendDesc* descs, int n, uint32_t* scra
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_mask_to16(const uint8_t* __restrict__ tm, int T, int tw, int th, int tiles_x,
-                                                   int tiles_y, uint8_t* __restrict__ m16) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= tiles_x * tiles_y) return;
-    const int tx = t % tiles_x, ty = t / tiles_x;
-    uint8_t v = 0;
-    if (T == 32) {
-        v = tm[(ty >> 1) * tw + (tx >> 1)] != 0;
-    } else {  // T == 8: any of the (up to) four 8x8 tiles of this 16x16 tile
-        for (int dy = 0; dy < 2; ++dy)
-            for (int dx = 0; dx < 2; ++dx) {
-                const int qx = 2 * tx + dx, qy = 2 * ty + dy;
-                if (qx < tw && qy < th && tm[qy * tw + qx]) v = 1;
-            }
-    }
-    m16[t] = v;
-}
-
-hipError_t launch_mask_to16(const uint8_t* tmask, int T, int W, int H, uint8_t* mask16, hipStream_t s) {
-    if (T != 8 && T != 32) return hipErrorInvalidValue;
-    const int tiles_x = (W + kTile - 1) / kTile, tiles_y = (H + kTile - 1) / kTile;
-    const int tw = (W + T - 1) / T, th = (H + T - 1) / T;
-    hipLaunchKernelGGL(k_mask_to16, dim3((unsigned)((tiles_x * tiles_y + 255) / 256)), dim3(256), 0, s, tmask, T, tw,
-                       th, tiles_x, tiles_y, mask16);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_mask_copy(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst,
-                                                   int64_t n, uint32_t mask) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) dst[i] = src[i] & mask;
-}
-
-hipError_t launch_mask_copy(const uint32_t* src, uint32_t* dst, int64_t n, uint32_t mask, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mask_copy, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, src, dst, n, mask);
-    return hipGetLastError();
-}
-
-hipError_t launch_ranges(const uint32_t* tkeys, const uint32_t* n_dev, int64_t cap, uint2* ranges, int n_tiles,
-                         int key_shift, hipStream_t s) {
-    if (key_shift < 0 || key_shift > 31) return hipErrorInvalidValue;
-    if (n_tiles <= 0) return hipSuccess;
-    const int64_t blocks = std::min<int64_t>(4096, std::max<int64_t>(1, (cap + 1023) / 1024));
-    hipLaunchKernelGGL(k_ranges, dim3((unsigned)blocks), dim3(256), 0, s, tkeys, n_dev, ranges, (uint32_t)n_tiles,
-                       key_shift);
-    return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void k_fill_u2(uint2* p, int64_t n, uint2 v) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-hipError_t launch_clear_ranges(uint2* ranges, int n_tiles, hipStream_t s) {
-    if (n_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_u2, dim3((unsigned)((n_tiles + 255) / 256)), dim3(256), 0, s, ranges, (int64_t)n_tiles,
-                       make_uint2(0u, 0u));
-    return hipGetLastError();
-}
-
-hipError_t launch_tile_order(const uint2* ranges, const uint32_t* n_live, int n_tiles, uint32_t* order,
-                             hipStream_t s) {
-    if (n_tiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tile_order, dim3(1), dim3(1024), 0, s, ranges, n_live, (uint32_t)n_tiles, order);
-    return hipGetLastError();
-}
-
-hipError_t launch_blend(const SurfelRec* recs, const uint32_t* vals, const uint2* ranges, const uint32_t* tile_list,
-                        const uint32_t* order, const uint32_t* n_live, int n_blocks, const BlendArgs& a,
+hipError_t launch_blend(const SurfelRec* recs, const uint32_t* vals, const uint2* ranges, const uint32_t* order, const uint32_t* n_live, int n_blocks, const BlendArgs& a,
                         const ContArgs& ca, float* rgb, float* d_or_z, float* alpha, uint8_t* cls,
                         unsigned long long* pair_counts, long long* trace, hipStream_t s) {
     if (n_blocks <= 0) return hipSuccess;
@@ -1975,72 +1953,60 @@ hipError_t launch_blend(const SurfelRec* recs, const uint32_t* vals, const uint2
     if (a.patch && a.xrecs) return hipErrorInvalidValue;  // the transfer belongs to the dominant eye
     if (a.patch) {
         if (pair_counts) {
-            hipLaunchKernelGGL((k_blend<true, true>), g, b, 0, s, recs, vals, ranges, tile_list, order, n_live, a, ca,
+            hipLaunchKernelGGL((k_blend<true, true>), g, b, 0, s, recs, vals, ranges, order, n_live, a, ca,
                                rgb, d_or_z, alpha, cls, pair_counts, trace);
             if (cont) {
                 for (int round = 0; round < kRounds; ++round)
-                    hipLaunchKernelGGL((k_blend_seg<true>), gc, b, 0, s, recs, vals, tile_list, a, ca, round,
+                    hipLaunchKernelGGL((k_blend_seg<true>), gc, b, 0, s, recs, vals, a, ca, round,
                                        pair_counts);
-                hipLaunchKernelGGL((k_blend_chain<true>), gs, b, 0, s, tile_list, a, ca, rgb, d_or_z, alpha, cls);
-                hipLaunchKernelGGL((k_blend_fix<true, true>), gc, b, 0, s, recs, vals, tile_list, a, ca, rgb, d_or_z,
+                hipLaunchKernelGGL((k_blend_chain<true>), gs, b, 0, s, a, ca, rgb, d_or_z, alpha, cls);
+                hipLaunchKernelGGL((k_blend_fix<true, true>), gc, b, 0, s, recs, vals, a, ca, rgb, d_or_z,
                                    alpha, cls, pair_counts);
             }
         } else {
-            hipLaunchKernelGGL((k_blend<false, true>), g, b, 0, s, recs, vals, ranges, tile_list, order, n_live, a, ca,
+            hipLaunchKernelGGL((k_blend<false, true>), g, b, 0, s, recs, vals, ranges, order, n_live, a, ca,
                                rgb, d_or_z, alpha, cls, pair_counts, (long long*)nullptr);
             if (cont) {
                 for (int round = 0; round < kRounds; ++round)
-                    hipLaunchKernelGGL((k_blend_seg<false>), gc, b, 0, s, recs, vals, tile_list, a, ca, round,
+                    hipLaunchKernelGGL((k_blend_seg<false>), gc, b, 0, s, recs, vals, a, ca, round,
                                        pair_counts);
-                hipLaunchKernelGGL((k_blend_chain<true>), gs, b, 0, s, tile_list, a, ca, rgb, d_or_z, alpha, cls);
-                hipLaunchKernelGGL((k_blend_fix<false, true>), gc, b, 0, s, recs, vals, tile_list, a, ca, rgb, d_or_z,
+                hipLaunchKernelGGL((k_blend_chain<true>), gs, b, 0, s, a, ca, rgb, d_or_z, alpha, cls);
+                hipLaunchKernelGGL((k_blend_fix<false, true>), gc, b, 0, s, recs, vals, a, ca, rgb, d_or_z,
                                    alpha, cls, pair_counts);
             }
         }
     } else {
         if (pair_counts && a.xrecs) {
-            hipLaunchKernelGGL((k_blend<true, false, true>), g, b, 0, s, recs, vals, ranges, tile_list, order, n_live,
+            hipLaunchKernelGGL((k_blend<true, false, true>), g, b, 0, s, recs, vals, ranges, order, n_live,
                                a, ca, rgb, d_or_z, alpha, cls, pair_counts, trace);
         } else if (pair_counts) {
-            hipLaunchKernelGGL((k_blend<true, false>), g, b, 0, s, recs, vals, ranges, tile_list, order, n_live, a, ca,
+            hipLaunchKernelGGL((k_blend<true, false>), g, b, 0, s, recs, vals, ranges, order, n_live, a, ca,
                                rgb, d_or_z, alpha, cls, pair_counts, trace);
             if (cont) {
                 for (int round = 0; round < kRounds; ++round)
-                    hipLaunchKernelGGL((k_blend_seg<true>), gc, b, 0, s, recs, vals, tile_list, a, ca, round,
+                    hipLaunchKernelGGL((k_blend_seg<true>), gc, b, 0, s, recs, vals, a, ca, round,
                                        pair_counts);
-                hipLaunchKernelGGL((k_blend_chain<false>), gs, b, 0, s, tile_list, a, ca, rgb, d_or_z, alpha, cls);
-                hipLaunchKernelGGL((k_blend_fix<true, false>), gc, b, 0, s, recs, vals, tile_list, a, ca, rgb, d_or_z,
+                hipLaunchKernelGGL((k_blend_chain<false>), gs, b, 0, s, a, ca, rgb, d_or_z, alpha, cls);
+                hipLaunchKernelGGL((k_blend_fix<true, false>), gc, b, 0, s, recs, vals, a, ca, rgb, d_or_z,
                                    alpha, cls, pair_counts);
             }
         } else if (a.xrecs) {
             // View-colour transfer: never continued.
-            hipLaunchKernelGGL((k_blend<false, false, true>), g, b, 0, s, recs, vals, ranges, tile_list, order, n_live,
+            hipLaunchKernelGGL((k_blend<false, false, true>), g, b, 0, s, recs, vals, ranges, order, n_live,
                                a, ca, rgb, d_or_z, alpha, cls, pair_counts, (long long*)nullptr);
         } else {
-            hipLaunchKernelGGL((k_blend<false, false>), g, b, 0, s, recs, vals, ranges, tile_list, order, n_live, a,
+            hipLaunchKernelGGL((k_blend<false, false>), g, b, 0, s, recs, vals, ranges, order, n_live, a,
                                ca, rgb, d_or_z, alpha, cls, pair_counts, (long long*)nullptr);
             if (cont) {
                 for (int round = 0; round < kRounds; ++round)
-                    hipLaunchKernelGGL((k_blend_seg<false>), gc, b, 0, s, recs, vals, tile_list, a, ca, round,
+                    hipLaunchKernelGGL((k_blend_seg<false>), gc, b, 0, s, recs, vals, a, ca, round,
                                        pair_counts);
-                hipLaunchKernelGGL((k_blend_chain<false>), gs, b, 0, s, tile_list, a, ca, rgb, d_or_z, alpha, cls);
-                hipLaunchKernelGGL((k_blend_fix<false, false>), gc, b, 0, s, recs, vals, tile_list, a, ca, rgb,
+                hipLaunchKernelGGL((k_blend_chain<false>), gs, b, 0, s, a, ca, rgb, d_or_z, alpha, cls);
+                hipLaunchKernelGGL((k_blend_fix<false, false>), gc, b, 0, s, recs, vals, a, ca, rgb,
                                    d_or_z, alpha, cls, pair_counts);
             }
         }
     }
-    return hipGetLastError();
-}
-
-hipError_t launch_mask_tables(const uint8_t* tile_mask, int n_tiles, int tiles_x, uint32_t* prefix,
-                              uint32_t* tile_list, uint32_t* colcum, DevStatus* st, hipStream_t s) {
-    hipLaunchKernelGGL(k_mask_tables, dim3(1), dim3(1024), 0, s, tile_mask, n_tiles, tiles_x, prefix, tile_list,
-                       colcum, st);
-    return hipGetLastError();
-}
-
-hipError_t launch_status_keys(const uint32_t* offs, int n, DevStatus* st, uint32_t cap, int which, hipStream_t s) {
-    hipLaunchKernelGGL(k_status_keys, dim3(1), dim3(1), 0, s, offs, n, st, cap, which);
     return hipGetLastError();
 }
 
