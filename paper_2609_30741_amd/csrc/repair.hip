@@ -7,13 +7,13 @@
 // consecutive pixels of one image row, the reduction runs over (tap, input
 // channel).  The input-gradient pass is the same kernel
 // with the weights transposed and flipped.  The weight gradient is a GEMM
-// over pixels: each block accumulates a slab of rows into per-block
-// partials that a second kernel adds in a fixed order, so results are
+// over pixels: each block accumulates its pixels into a partial, and a
+// second kernel adds the partials in a fixed order, so results are
 // deterministic.  Activations and gradients between layers are stored as
 // bf16 [B][H][W][C], channels innermost; a layer may read or write a
-// channel slice of a larger tensor (the pixel stride exceeds the slice),
-// which is how the skip connections land in the decoder's concatenated
-// inputs without copies.  The images the network reads and writes are
+// channel slice of a larger tensor (the pixel stride exceeds the slice); a
+// decoder reads its upsampled channels from the coarser level and the others
+// from the skip connection, so no concatenation is stored.  The images the network reads and writes are
 // planar fp32.
 #include <hip/hip_runtime.h>
 
@@ -294,105 +294,208 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Weight and bias gradient: part[chunk][co][col] = sum over the chunk's
-// pixels of g[p, co] * in[p + tap offset, ci] for col = ci * 9 + tap < K,
-// and of g[p, co] (a column of ones) for col = K, the bias.  Block: 4
-// waves, one 16-column tile each; blockIdx.y: chunk of image rows.  The
-// reduction runs over 32 pixels of a row per v_mfma_f32_16x16x32_bf16.
+// Weight and bias gradients.  dW[co][ci][tap] = sum over pixels p of
+// g[p, co] * in[p + tap offset, ci]: per tap a GEMM over pixels with both
+// operands stored pixel by pixel, so both must be read transposed.  A block
+// stages kWgRows x kWgCols pixels of the gradient and the same with a
+// one-pixel border of 16 input channels in LDS as they lie in memory, and
+// ds_read_b64_tr_b16 turns 4 pixels x 16 channels into an MFMA operand: a
+// tap is another pixel address, and needs no realignment.  (Gathering the
+// operands' elements one by one from memory, 42 us a layer on eight 128x128
+// crops, was bound by its 2-byte loads.)  Three waves take a row of taps
+// each, for all output channels (MT tiles of 16), so a wave holds 3 MT
+// accumulator tiles and nothing is reduced across waves; wave 0 also takes
+// the bias, a product with ones.  A block sums kWgRows x kWgCols items of
+// its chunk and writes one partial; a second kernel adds the partials in a
+// fixed order, so results are deterministic.  The layers' blocks go in one
+// launch per MT after the whole backward pass, and all reductions in one:
+// on the small crops of training a launch costs as much as its work.
 // ---------------------------------------------------------------------------
-struct WgradArgs {
+constexpr int kWgRows = 4, kWgCols = 64, kWgPix = kWgRows * kWgCols;
+constexpr int kWgInPix = (kWgRows + 2) * (kWgCols + 2);
+constexpr int kWgThreads = 192;
+constexpr int kWgChunks = 256;  // partials per layer at most
+
+struct WgradJob {
     const uint16_t* g;  // layer output gradient, [B][H][W] pixels of g_ps elements
     int64_t g_bs;
-    int g_ps;
-    int cout;
-    const uint16_t* in;  // layer input, in_ps elements per pixel
+    int g_ps, cout;
+    const uint16_t* in;  // layer input from channel up_c on, in_ps elements per pixel
     int64_t in_bs;
-    int in_ps;
-    int cin;
+    int in_ps, cin;
+    const uint16_t* up;  // input channels [0, up_c), at half resolution (up_c a multiple of 16)
+    int64_t up_bs;
+    int up_ps, up_c;
     int B, H, W;
-    int rows;  // image rows (over the whole batch) per chunk
-    float* part;
+    int items_x, items_y;  // items per image row and column
+    int items, per;        // over the batch; per chunk
+    int chunks, nt;        // partials; 16-channel input tiles
+    int first;             // first block: block first + chunk * nt + tile
+    float* part;           // [chunk]: [tap][cout][16 nt], then [cout]
+};
+constexpr int kWgJobs = 4;
+struct WgradJobs {
+    WgradJob job[kWgJobs];
+    int n;
 };
 
-__global__ __launch_bounds__(256) void k_wgrad(WgradArgs a) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int K = a.cin * 9, KC = K + 1;
-    const int nt = blockIdx.x * 4 + wave;
-    if (nt * 16 >= KC) return;  // whole wave
-    const int n = lane & 15, kq = (lane >> 4) * 8;
-    const int col = nt * 16 + n;
-    const bool col_ok = col < K, is_bias = col == K;
-    const int ci = col_ok ? col / 9 : 0, t = col_ok ? col - ci * 9 : 4;
-    const int ky = t / 3, kx = t - ky * 3;
-    const int mt = (a.cout + 15) >> 4;
-    v4f acc[4];
+typedef short v4s __attribute__((ext_vector_type(4)));
+
+// Eight pixels' values of one channel for this lane (channel lane & 15,
+// pixels 8 (lane >> 4) on), from LDS pixels of 16 channels starting at p:
+// each group of 16 lanes reads four pixels as they lie and gets them
+// transposed.
+__device__ __forceinline__ v8bf tr_operand(const uint16_t* p, int lane) {
+    const uint16_t* q = p + (8 * (lane >> 4) + ((lane & 15) >> 2)) * 16 + (lane & 3) * 4;
+    typedef __attribute__((address_space(3))) v4s* lds_v4s;
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(q));
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(q + 4 * 16));
+    return __builtin_bit_cast(v8bf, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int MT>
+__global__ __launch_bounds__(kWgThreads) void k_wgrad(WgradJobs J) {
+    __shared__ __attribute__((aligned(16))) uint16_t s_in[kWgInPix * 16];
+    __shared__ __attribute__((aligned(16))) uint16_t s_g[MT * kWgPix * 16];
+    int jb = 0;
+    while (jb + 1 < J.n && (int)blockIdx.x >= J.job[jb + 1].first) ++jb;
+    const WgradJob& a = J.job[jb];
+    const int local = (int)blockIdx.x - a.first, chunk = local / a.nt, nt = local - chunk * a.nt;
+    const int ci0 = 16 * nt;
+    const int tid = threadIdx.x, lane = tid & 63, ky = tid >> 6;
+    const bool from_up = ci0 < a.up_c;
+    v4f acc[MT][3], accb[MT];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) acc[m] = v4f{0.f, 0.f, 0.f, 0.f};
-    const int r0 = blockIdx.y * a.rows, r1 = min(r0 + a.rows, a.B * a.H);
-    for (int r = r0; r < r1; ++r) {
-        const int b = r / a.H, y = r - b * a.H;
-        const uint16_t* gb = a.g + (int64_t)b * a.g_bs + (int64_t)y * a.W * a.g_ps;
-        const uint16_t* ib = a.in + (int64_t)b * a.in_bs + ci;
-        const int yy = y + ky - 1;
-        const bool row_ok = col_ok && yy >= 0 && yy < a.H;
-#pragma unroll 2
-        for (int xb = 0; xb < a.W; xb += 32) {
-            v8s bv;
+    for (int m = 0; m < MT; ++m) {
+        accb[m] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int xp = xb + kq + j, xx = xp + kx - 1;
-                const bool ok = row_ok && xp < a.W && xx >= 0 && xx < a.W;
-                bv[j] = (short)(ok ? ib[((int64_t)yy * a.W + xx) * a.in_ps]
-                                   : (is_bias && xp < a.W) ? (uint16_t)0x3F80u : (uint16_t)0);
-            }
+        for (int k = 0; k < 3; ++k) acc[m][k] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    const v8s one8 = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};
+    const v8bf ones = __builtin_bit_cast(v8bf, one8);
+    const int i1 = min(a.items, (chunk + 1) * a.per);
+    for (int item = chunk * a.per; item < i1; ++item) {
+        const int ix = item % a.items_x, r = item / a.items_x, iy = r % a.items_y, b = r / a.items_y;
+        const int x0 = ix * kWgCols, y0 = iy * kWgRows;
+        // All of a thread's loads, then the stores (16 bytes: eight channels
+        // of a pixel; zero outside the image and past the last channel).
+        constexpr int kInWords = 2 * kWgInPix, kGWords = 2 * MT * kWgPix;
+        constexpr int kInU = (kInWords + kWgThreads - 1) / kWgThreads, kGU = (kGWords + kWgThreads - 1) / kWgThreads;
+        uint4 vi[kInU], vg[kGU];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                if (m < mt) {
-                    const int co = m * 16 + n;
-                    v8s av;
+        for (int u = 0; u < kInU; ++u) {
+            const int w = tid + u * kWgThreads, c = ci0 + 8 * (w & 1), p = w >> 1;
+            const int y = y0 + p / (kWgCols + 2) - 1, x = x0 + p % (kWgCols + 2) - 1;
+            vi[u] = uint4{0u, 0u, 0u, 0u};
+            if (w < kInWords && y >= 0 && y < a.H && x >= 0 && x < a.W && c < a.cin)
+                vi[u] = *reinterpret_cast<const uint4*>(
+                    from_up ? a.up + (int64_t)b * a.up_bs + ((int64_t)(y >> 1) * (a.W >> 1) + (x >> 1)) * a.up_ps + c
+                            : a.in + (int64_t)b * a.in_bs + ((int64_t)y * a.W + x) * a.in_ps + (c - a.up_c));
+        }
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const int xp = xb + kq + j;
-                        av[j] = (short)((co < a.cout && xp < a.W) ? gb[(int64_t)xp * a.g_ps + co] : (uint16_t)0);
-                    }
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, av),
-                                                                    __builtin_bit_cast(v8bf, bv), acc[m], 0, 0, 0);
+        for (int u = 0; u < kGU; ++u) {
+            const int w = tid + u * kWgThreads, c = 8 * (w % (2 * MT)), p = w / (2 * MT);
+            const int y = y0 + p / kWgCols, x = x0 + p % kWgCols;
+            vg[u] = uint4{0u, 0u, 0u, 0u};
+            if (w < kGWords && y < a.H && x < a.W && c < a.cout)
+                vg[u] = *reinterpret_cast<const uint4*>(a.g + (int64_t)b * a.g_bs + ((int64_t)y * a.W + x) * a.g_ps + c);
+        }
+        __syncthreads();  // the previous item's operands have been read
+#pragma unroll
+        for (int u = 0; u < kInU; ++u) {
+            const int w = tid + u * kWgThreads;
+            if (w < kInWords) *reinterpret_cast<uint4*>(s_in + 8 * w) = vi[u];
+        }
+#pragma unroll
+        for (int u = 0; u < kGU; ++u) {
+            const int w = tid + u * kWgThreads, g8 = w % (2 * MT), p = w / (2 * MT);
+            if (w < kGWords) *reinterpret_cast<uint4*>(s_g + ((g8 >> 1) * kWgPix + p) * 16 + 8 * (g8 & 1)) = vg[u];
+        }
+        __syncthreads();
+        for (int row = 0; row < kWgRows; ++row) {
+            if (y0 + row >= a.H) break;
+#pragma unroll
+            for (int sx = 0; sx < kWgCols; sx += 32) {
+                if (x0 + sx >= a.W) break;
+                v8bf ga[MT];
+#pragma unroll
+                for (int m = 0; m < MT; ++m) ga[m] = tr_operand(s_g + (m * kWgPix + row * kWgCols + sx) * 16, lane);
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) {
+                    const v8bf ib = tr_operand(s_in + ((row + ky) * (kWgCols + 2) + sx + kx) * 16, lane);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+                        acc[m][kx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga[m], ib, acc[m][kx], 0, 0, 0);
+                }
+                if (ky == 0 && nt == 0) {
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+                        accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ga[m], ones, accb[m], 0, 0, 0);
                 }
             }
         }
     }
-    if (col >= KC) return;
-    float* pb = a.part + (size_t)blockIdx.y * a.cout * KC;
+    // Lane holds channels co .. co + 3 of input channel ci.
+    const int cinp = 16 * a.nt, n = lane & 15;
+    float* pb = a.part + (size_t)chunk * (9 * a.cout * cinp + a.cout);
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        if (m >= mt) continue;
+    for (int m = 0; m < MT; ++m) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int co = m * 16 + (lane >> 4) * 4 + j;
-            if (co < a.cout) pb[(size_t)co * KC + col] = acc[m][j];
+            const int co = 16 * m + 4 * (lane >> 4) + j;
+            if (co >= a.cout) continue;
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) pb[(size_t)((3 * ky + kx) * a.cout + co) * cinp + ci0 + n] = acc[m][kx][j];
+            if (ky == 0 && nt == 0 && n == 0) pb[(size_t)9 * a.cout * cinp + co] = accb[m][j];
         }
     }
 }
 
-// grad (the layer's W[cout][K] then b[cout]) from the partials in a fixed
-// order: block of 64 outputs; wave q adds the q-th quarter of the chunks in
-// chunk order, then ((q0 + q1) + (q2 + q3)).
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ part, int chunks, int cout, int K,
-                                                      float* __restrict__ grad) {
+// grad (each layer's W[cout][cin][9] then b[cout]) from the partials in a
+// fixed order: block of 64 outputs; wave q adds the q-th quarter of the
+// chunks in chunk order, then ((q0 + q1) + (q2 + q3)).
+struct WgradSum {
+    const float* part;
+    float* grad;
+    int chunks, cout, cin, cinp, first;  // first: the layer's first block
+};
+struct WgradSums {
+    WgradSum job[kLayers];
+    int n;
+};
+
+__global__ __launch_bounds__(256) void k_wgrad_reduce(WgradSums J) {
     __shared__ float s_q[4][64];
-    const int KC = K + 1;
+    int jb = 0;
+    while (jb + 1 < J.n && (int)blockIdx.x >= J.job[jb + 1].first) ++jb;
+    const WgradSum& a = J.job[jb];
+    const int W = 9 * a.cout * a.cinp, n = W + a.cout;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + lane;
-    const int per = (chunks + 3) / 4, c0 = q * per, c1 = min(chunks, c0 + per);
+    const int i = ((int)blockIdx.x - a.first) * 64 + lane;
+    const int per = (a.chunks + 3) / 4, c0 = q * per, c1 = min(a.chunks, c0 + per);
     float s = 0.f;
-    if (i < cout * KC)
-        for (int c = c0; c < c1; ++c) s += part[(size_t)c * cout * KC + i];
+    if (i < n) {
+        const float* p = a.part + i;
+        int c = c0;
+        for (; c + 8 <= c1; c += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = p[(size_t)(c + u) * n];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; c < c1; ++c) s += p[(size_t)c * n];
+    }
     s_q[q][lane] = s;
     __syncthreads();
-    if (q != 0 || i >= cout * KC) return;
+    if (q != 0 || i >= n) return;
     const float v = (s_q[0][lane] + s_q[1][lane]) + (s_q[2][lane] + s_q[3][lane]);
-    const int co = i / KC, col = i - co * KC;
-    grad[col < K ? co * K + col : cout * K + co] = v;
+    if (i >= W) {
+        a.grad[a.cout * a.cin * 9 + (i - W)] = v;
+        return;
+    }
+    const int t = i / (a.cout * a.cinp), rem = i - t * (a.cout * a.cinp), co = rem / a.cinp, ci = rem - co * a.cinp;
+    if (ci < a.cin) a.grad[(co * a.cin + ci) * 9 + t] = v;
 }
 
 __device__ __forceinline__ float block_sum(float v, float* red) {
@@ -479,18 +582,6 @@ __device__ __forceinline__ bool item(int64_t B, int64_t n, int C, int64_t& b, in
     b = bp / n;
     p = bp - b * n;
     return true;
-}
-
-// Nearest 2x upsample of [B][h][w][C] into the first C channel slots of a
-// larger tensor (out_bs, out_ps).
-__global__ __launch_bounds__(256) void k_up(const uint16_t* __restrict__ in, int B, int C, int h, int w,
-                                            uint16_t* __restrict__ out, int64_t out_bs, int out_ps) {
-    const int H = 2 * h, W = 2 * w;
-    int64_t b, p;
-    int c;
-    if (!item(B, (int64_t)H * W, C, b, p, c)) return;
-    const int y = (int)(p / W), x = (int)(p - (int64_t)y * W);
-    st8(out + b * out_bs + p * out_ps + c, ld8(in + (b * h * w + (int64_t)(y >> 1) * w + (x >> 1)) * C + c));
 }
 
 // Gradient of the upsample: sum of each 2x2 block of the first C channels
@@ -701,18 +792,34 @@ struct Layout {
 };
 
 struct Bufs {
-    uint16_t *x0, *e1a, *cat1, *p1, *e2a, *cat2, *p2, *e3a, *e3b, *d2, *d1;
+    uint16_t *x0, *e1a, *e1b, *p1, *e2a, *e2b, *p2, *e3a, *e3b, *d2, *d1;
     float* r;
     uint16_t* wf[kLayers];
     uint16_t* wb[kLayers];
     // training
     uint16_t *g_r, *g_d1, *g_cat1, *g_d2, *g_cat2, *g_e3b, *g_e3a, *g_p2, *g_e2b, *g_e2a, *g_p1, *g_e1b, *g_e1a;
-    float *part, *cnt_part, *loss_part, *n_hole;
-    int chunks1, chunks2, chunks3;
+    float *cnt_part, *loss_part, *n_hole;
+    float* part[kLayers];
     size_t bytes;
 };
 
-int chunk_rows(int rows) { return std::max(1, (rows + 127) / 128); }
+// Level (0: H x W, 1: halved, 2: quartered) of each layer's output.
+constexpr int kLevel[kLayers] = {0, 0, 1, 1, 2, 2, 1, 0, 0};
+
+// The weight gradient's items and chunks of layer l.
+void wgrad_split(int l, int B, int H, int W, WgradJob& a) {
+    a.B = B;
+    a.H = H >> kLevel[l];
+    a.W = W >> kLevel[l];
+    a.cin = kNet[l].cin;
+    a.cout = kNet[l].cout;
+    a.nt = pad16(a.cin) / 16;
+    a.items_x = (a.W + kWgCols - 1) / kWgCols;
+    a.items_y = (a.H + kWgRows - 1) / kWgRows;
+    a.items = B * a.items_y * a.items_x;  // at most 1000 * 2048 * 128
+    a.per = (a.items + kWgChunks - 1) / kWgChunks;
+    a.chunks = (a.items + a.per - 1) / a.per;
+}
 
 Bufs layout(int B, int H, int W, bool train, char* base) {
     Layout L;
@@ -722,10 +829,10 @@ Bufs layout(int B, int H, int W, bool train, char* base) {
     auto fl = [&](size_t elems) { return (float*)(base + L.take(elems * 4)); };
     f.x0 = bf(B * 8 * h1);
     f.e1a = bf(B * 16 * h1);
-    f.cat1 = bf(B * 48 * h1);
+    f.e1b = bf(B * 16 * h1);
     f.p1 = bf(B * 16 * h2);
     f.e2a = bf(B * 32 * h2);
-    f.cat2 = bf(B * 96 * h2);
+    f.e2b = bf(B * 32 * h2);
     f.p2 = bf(B * 32 * h3);
     f.e3a = bf(B * 64 * h3);
     f.e3b = bf(B * 64 * h3);
@@ -753,17 +860,11 @@ Bufs layout(int B, int H, int W, bool train, char* base) {
         f.g_p1 = bf(B * 16 * h2);
         f.g_e1b = bf(B * 16 * h1);
         f.g_e1a = bf(B * 16 * h1);
-        const int rows1 = B * H, rows2 = B * H / 2, rows3 = B * H / 4;
-        f.chunks1 = (rows1 + chunk_rows(rows1) - 1) / chunk_rows(rows1);
-        f.chunks2 = (rows2 + chunk_rows(rows2) - 1) / chunk_rows(rows2);
-        f.chunks3 = (rows3 + chunk_rows(rows3) - 1) / chunk_rows(rows3);
-        size_t mx = 0;
-        const int lvl[kLayers] = {1, 1, 2, 2, 3, 3, 2, 1, 1};
         for (int l = 0; l < kLayers; ++l) {
-            const int ch = lvl[l] == 1 ? f.chunks1 : lvl[l] == 2 ? f.chunks2 : f.chunks3;
-            mx = std::max(mx, (size_t)ch * kNet[l].cout * (kNet[l].cin * 9 + 1));
+            WgradJob a{};
+            wgrad_split(l, B, H, W, a);
+            f.part[l] = fl((size_t)a.chunks * (9 * a.cout * 16 * a.nt + a.cout));
         }
-        f.part = fl(mx);
     }
     f.bytes = L.off;
     return f;
@@ -898,49 +999,22 @@ void conv(hipStream_t s, int B, int H, int W, int l, bool transpose, const Bufs&
     }
 }
 
-void wgrad(hipStream_t s, int B, int H, int W, int l, const Bufs& f, View g, View in, int chunks, float* grad) {
-    WgradArgs a{};
-    a.g = g.p;
-    a.g_bs = g.bs;
-    a.g_ps = g.ps;
-    a.cout = kNet[l].cout;
-    a.in = in.p;
-    a.in_bs = in.bs;
-    a.in_ps = in.ps;
-    a.cin = kNet[l].cin;
-    a.B = B;
-    a.H = H;
-    a.W = W;
-    a.rows = chunk_rows(B * H);
-    a.part = f.part;
-    const int K = a.cin * 9;
-    const int nt = (K + 1 + 15) / 16;
-    hipLaunchKernelGGL(k_wgrad, dim3((nt + 3) / 4, chunks), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)(((int64_t)a.cout * (K + 1) + 63) / 64)), dim3(256), 0, s,
-                       (const float*)f.part, chunks, a.cout, K, grad + param_offset(l));
-}
-
 // The tensors of one pass, as views.
 struct Net {
-    View x0, e1a, cat1, e1b, p1, e2a, cat2, e2b, p2, e3a, e3b, d2, d1;
+    View x0, e1a, e1b, p1, e2a, e2b, p2, e3a, e3b, d2, d1;
     View g_r, g_d1, g_cat1, g_d2, g_cat2, g_e3b, g_e3a, g_p2, g_e2b, g_e2a, g_p1, g_e1b, g_e1a;
 };
 
-// Training keeps each decoder's concatenated input whole (the weight
-// gradient reads it), the skip connection in its last channels; inference
-// stores the skip tensors dense, in the same memory.
-Net views(const Bufs& f, int H, int W, bool train) {
+Net views(const Bufs& f, int H, int W) {
     const int64_t h1 = (int64_t)H * W, h2 = h1 / 4, h3 = h1 / 16;
     auto v = [](uint16_t* p, int c, int64_t hw) { return View{p, c * hw, c}; };
     Net n;
     n.x0 = v(f.x0, 8, h1);
     n.e1a = v(f.e1a, 16, h1);
-    n.cat1 = v(f.cat1, 48, h1);  // up(d2) in channels 0-31, e1b in 32-47
-    n.e1b = train ? n.cat1.at(32) : v(f.cat1, 16, h1);
+    n.e1b = v(f.e1b, 16, h1);
     n.p1 = v(f.p1, 16, h2);
     n.e2a = v(f.e2a, 32, h2);
-    n.cat2 = v(f.cat2, 96, h2);  // up(e3b) in channels 0-63, e2b in 64-95
-    n.e2b = train ? n.cat2.at(64) : v(f.cat2, 32, h2);
+    n.e2b = v(f.e2b, 32, h2);
     n.p2 = v(f.p2, 32, h3);
     n.e3a = v(f.e3a, 64, h3);
     n.e3b = v(f.e3b, 64, h3);
@@ -985,8 +1059,8 @@ void forward(hipStream_t s, int B, int H, int W, const float* params, const floa
             ++J.n;
         }
     hipLaunchKernelGGL(k_pack, dim3(blocks(J.start[J.n])), dim3(256), 0, s, J);
-    const Net n = views(f, H, W, train);
-    const int64_t h1 = (int64_t)H * W, h2 = h1 / 4;
+    const Net n = views(f, H, W);
+    const int64_t h1 = (int64_t)H * W;
     const int H2 = H / 2, W2 = W / 2, H3 = H / 4, W3 = W / 4;
     hipLaunchKernelGGL(k_input, dim3(blocks(B * h1)), dim3(256), 0, s, rgb, z, hole, B, (int)h1, f.x0);
     conv(s, B, H, W, E1A, false, f, n.x0, params, n.e1a, nullptr, kNone);
@@ -997,50 +1071,97 @@ void forward(hipStream_t s, int B, int H, int W, const float* params, const floa
     conv(s, B, H3, W3, E3A, false, f, n.p2, params, n.e3a, nullptr, kNone);
     conv(s, B, H3, W3, E3B, false, f, n.e3a, params, n.e3b, nullptr, kNone);
     // The decoders read their upsampled channels straight from the coarser
-    // level; training also stores the upsample, which the weight gradient
-    // reads.
-    if (train)
-        hipLaunchKernelGGL(k_up, dim3(chan_blocks(B, h2, 64)), dim3(256), 0, s, f.e3b, B, 64, H3, W3, n.cat2.p,
-                           n.cat2.bs, n.cat2.ps);
+    // level.
     conv(s, B, H2, W2, D2, false, f, n.e2b, params, n.d2, nullptr, kNone, n.e3b, 64);
-    if (train)
-        hipLaunchKernelGGL(k_up, dim3(chan_blocks(B, h1, 32)), dim3(256), 0, s, f.d2, B, 32, H2, W2, n.cat1.p,
-                           n.cat1.bs, n.cat1.ps);
     conv(s, B, H, W, D1, false, f, n.e1b, params, n.d1, nullptr, kNone, n.d2, 32);
     conv(s, B, H, W, OUT, false, f, n.d1, params, kNone, f.r, kNone);
 }
 
+// Input gradients layer by layer, then all weight gradients (every layer's
+// output gradient and input stay in the workspace).
 void backward(hipStream_t s, int B, int H, int W, const float* params, const Bufs& f, float* grad) {
-    const Net n = views(f, H, W, true);
+    const Net n = views(f, H, W);
     const int64_t h1 = (int64_t)H * W, h2 = h1 / 4;
     const int H2 = H / 2, W2 = W / 2, H3 = H / 4, W3 = W / 4;
-    wgrad(s, B, H, W, OUT, f, n.g_r, n.d1, f.chunks1, grad);
     conv(s, B, H, W, OUT, true, f, n.g_r, params, n.g_d1, nullptr, n.d1);
-    wgrad(s, B, H, W, D1, f, n.g_d1, n.cat1, f.chunks1, grad);
     conv(s, B, H, W, D1, true, f, n.g_d1, params, n.g_cat1, nullptr, kNone);
     hipLaunchKernelGGL(k_up_grad, dim3(chan_blocks(B, h2, 32)), dim3(256), 0, s, n.g_cat1.p, n.g_cat1.bs, n.g_cat1.ps,
                        B, 32, H, W, f.d2, f.g_d2);
-    wgrad(s, B, H2, W2, D2, f, n.g_d2, n.cat2, f.chunks2, grad);
     conv(s, B, H2, W2, D2, true, f, n.g_d2, params, n.g_cat2, nullptr, kNone);
     hipLaunchKernelGGL(k_up_grad, dim3(chan_blocks(B, h2 / 4, 64)), dim3(256), 0, s, n.g_cat2.p, n.g_cat2.bs,
                        n.g_cat2.ps, B, 64, H2, W2, f.e3b, f.g_e3b);
-    wgrad(s, B, H3, W3, E3B, f, n.g_e3b, n.e3a, f.chunks3, grad);
     conv(s, B, H3, W3, E3B, true, f, n.g_e3b, params, n.g_e3a, nullptr, n.e3a);
-    wgrad(s, B, H3, W3, E3A, f, n.g_e3a, n.p2, f.chunks3, grad);
     conv(s, B, H3, W3, E3A, true, f, n.g_e3a, params, n.g_p2, nullptr, kNone);
     const View sk2 = n.g_cat2.at(64), sk1 = n.g_cat1.at(32);
     hipLaunchKernelGGL(k_merge, dim3(chan_blocks(B, h2, 32)), dim3(256), 0, s, sk2.p, sk2.bs, sk2.ps, f.g_p2, n.e2b.p,
                        n.e2b.bs, n.e2b.ps, B, 32, H2, W2, f.g_e2b);
-    wgrad(s, B, H2, W2, E2B, f, n.g_e2b, n.e2a, f.chunks2, grad);
     conv(s, B, H2, W2, E2B, true, f, n.g_e2b, params, n.g_e2a, nullptr, n.e2a);
-    wgrad(s, B, H2, W2, E2A, f, n.g_e2a, n.p1, f.chunks2, grad);
     conv(s, B, H2, W2, E2A, true, f, n.g_e2a, params, n.g_p1, nullptr, kNone);
     hipLaunchKernelGGL(k_merge, dim3(chan_blocks(B, h1, 16)), dim3(256), 0, s, sk1.p, sk1.bs, sk1.ps, f.g_p1, n.e1b.p,
                        n.e1b.bs, n.e1b.ps, B, 16, H, W, f.g_e1b);
-    wgrad(s, B, H, W, E1B, f, n.g_e1b, n.e1a, f.chunks1, grad);
     conv(s, B, H, W, E1B, true, f, n.g_e1b, params, n.g_e1a, nullptr, n.e1a);
-    wgrad(s, B, H, W, E1A, f, n.g_e1a, n.x0, f.chunks1, grad);
+    // Per layer: output gradient, input (its own channels), and the
+    // upsampled source of the decoders' first channels.
+    struct Src {
+        View g, in, up;
+        int up_c;
+    };
+    const Src src[kLayers] = {{n.g_e1a, n.x0, kNone, 0}, {n.g_e1b, n.e1a, kNone, 0}, {n.g_e2a, n.p1, kNone, 0},
+                              {n.g_e2b, n.e2a, kNone, 0}, {n.g_e3a, n.p2, kNone, 0}, {n.g_e3b, n.e3a, kNone, 0},
+                              {n.g_d2, n.e2b, n.e3b, 64}, {n.g_d1, n.e1b, n.d2, 32}, {n.g_r, n.d1, kNone, 0}};
+    WgradSums S{};
+    int sum_blocks = 0;
+    for (int mt = 1; mt <= 4; mt *= 2) {
+        WgradJobs J{};
+        int nblk = 0;
+        for (int l = 0; l < kLayers; ++l) {
+            if (pad16(kNet[l].cout) != 16 * mt) continue;
+            WgradJob& a = J.job[J.n++];
+            wgrad_split(l, B, H, W, a);
+            a.g = src[l].g.p;
+            a.g_bs = src[l].g.bs;
+            a.g_ps = src[l].g.ps;
+            a.in = src[l].in.p;
+            a.in_bs = src[l].in.bs;
+            a.in_ps = src[l].in.ps;
+            a.up = src[l].up.p;
+            a.up_bs = src[l].up.bs;
+            a.up_ps = src[l].up.ps;
+            a.up_c = src[l].up_c;
+            a.part = f.part[l];
+            a.first = nblk;
+            nblk += a.chunks * a.nt;
+            WgradSum& q = S.job[S.n++];
+            q.part = f.part[l];
+            q.grad = grad + param_offset(l);
+            q.chunks = a.chunks;
+            q.cout = a.cout;
+            q.cin = a.cin;
+            q.cinp = 16 * a.nt;
+            q.first = sum_blocks;
+            sum_blocks += (9 * a.cout * q.cinp + a.cout + 63) / 64;
+        }
+        const dim3 g(nblk), b(kWgThreads);
+        if (mt == 1)
+            hipLaunchKernelGGL(k_wgrad<1>, g, b, 0, s, J);
+        else if (mt == 2)
+            hipLaunchKernelGGL(k_wgrad<2>, g, b, 0, s, J);
+        else
+            hipLaunchKernelGGL(k_wgrad<4>, g, b, 0, s, J);
+    }
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(sum_blocks), dim3(256), 0, s, S);
 }
+
+constexpr bool wgrad_jobs_ok() {
+    int n[5] = {};
+    for (int l = 0; l < kLayers; ++l) {
+        const int mt = pad16(kNet[l].cout) / 16;
+        if (mt != 1 && mt != 2 && mt != 4) return false;
+        if (++n[mt] > kWgJobs) return false;
+    }
+    return true;
+}
+static_assert(wgrad_jobs_ok(), "every layer has a weight gradient instance and a place in its launch");
 
 bool sizes_ok(int B, int H, int W) { return B >= 1 && B <= 1000 && H >= 4 && W >= 4 && H % 4 == 0 && W % 4 == 0 && H <= 8192 && W <= 8192; }
 
