@@ -431,6 +431,115 @@ __global__ __launch_bounds__(256, 2) void k_rs_scatter_cnt(const uint32_t* __res
     }
 }
 
+// ---------------------------------------------------------------------------
+// Sorts of up to kBlockSort keys: one workgroup of 1024 threads does every
+// pass in LDS, so a small frame's depth sort is one launch instead of
+// twelve (each of which costs its start-up, whatever it moves).  Thread t of
+// wave w holds the keys at w * 64 * kItems + it * 64 + lane; a pass ranks
+// them as k_rs_scatter does (match-any ballots, a count per wave and digit),
+// exchanges them through LDS and reads them back in order.  A digit that is
+// the same in every key is passed over: depths within a factor of four or
+// so share their upper bits.
+// ---------------------------------------------------------------------------
+constexpr int kBlockThreads = 1024, kBlockWaves = kBlockThreads / 64;
+constexpr int64_t kBlockSort = 16 * kBlockThreads;
+
+template <int kItems>
+__global__ __launch_bounds__(kBlockThreads) void k_rs_block(uint32_t* keys, const uint32_t* vin, uint32_t* vout,
+                                                            uint32_t n, int key_bits) {
+    constexpr int kSub = kBlockThreads * kItems;
+    __shared__ uint32_t s_keys[kSub], s_vals[kSub];
+    __shared__ uint16_t cnt[kBlockWaves][kRsBins];
+    __shared__ uint32_t wsum[4], wvary[kBlockWaves];
+    const uint32_t t = threadIdx.x, lane = lane_id(), wave = t >> 6;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    const uint32_t first = wave * (64 * kItems) + lane;
+    uint32_t k[kItems], v[kItems], r[kItems];
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+        const uint32_t i = first + it * 64;
+        k[it] = i < n ? keys[i] : 0u;
+        v[it] = i < n ? (vin ? vin[i] : i) : 0u;
+    }
+    // The bits in which any key differs from the first.
+    uint32_t vary = 0;
+    const uint32_t k0 = keys[0];
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) vary |= first + it * 64 < n ? k[it] ^ k0 : 0u;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) vary |= (uint32_t)__shfl_xor((int)vary, off, 64);
+    if (lane == 0) wvary[wave] = vary;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kBlockWaves; ++w) vary |= wvary[w];
+    for (int shift = 0; shift < key_bits; shift += kRsMaxBits) {
+        const int bits = min(kRsMaxBits, key_bits - shift);
+        const uint32_t mask = (1u << bits) - 1u;
+        if (((vary >> shift) & mask) == 0) continue;  // uniform over the block
+        for (uint32_t i = t; i < kBlockWaves * kRsBins / 2; i += kBlockThreads) reinterpret_cast<uint32_t*>(cnt)[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            const bool ok = first + it * 64 < n;
+            const uint32_t d = (k[it] >> shift) & mask;
+            const uint64_t peers = match_digit(d, __ballot(ok), bits);
+            const uint32_t c = ok ? cnt[wave][d] : 0u;
+            r[it] = c + (uint32_t)__popcll(peers & lt);
+            __builtin_amdgcn_wave_barrier();
+            if (ok && (peers & lt) == 0) cnt[wave][d] = (uint16_t)(c + (uint32_t)__popcll(peers));
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        // First place of every (digit, wave): thread d < 256 for digit d.
+        uint32_t c[kBlockWaves], tot = 0, inc = 0;
+        if (t < kRsBins) {
+#pragma unroll
+            for (int w = 0; w < kBlockWaves; ++w) {
+                c[w] = cnt[w][t];
+                tot += c[w];
+            }
+            inc = wave_incl_scan(tot);
+            if (lane == 63) wsum[wave] = inc;
+        }
+        __syncthreads();
+        if (t < kRsBins) {
+            uint32_t run = inc - tot;
+            for (uint32_t w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+            for (int w = 0; w < kBlockWaves; ++w) {
+                cnt[w][t] = (uint16_t)run;  // below n <= 16384
+                run += c[w];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            if (first + it * 64 < n) {
+                const uint32_t p = cnt[wave][(k[it] >> shift) & mask] + r[it];
+                s_keys[p] = k[it];
+                s_vals[p] = v[it];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            const uint32_t i = first + it * 64;
+            if (i < n) {
+                k[it] = s_keys[i];
+                v[it] = s_vals[i];
+            }
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+        const uint32_t i = first + it * 64;
+        if (i < n) {
+            keys[i] = k[it];
+            vout[i] = v[it];
+        }
+    }
+}
+
 uint32_t rs_grid(int64_t n_cap, int items) {
     const int64_t g = ceil_div(n_cap > 0 ? n_cap : 1, 256 * items);
     return (uint32_t)(g < kRsGrid ? g : kRsGrid);
@@ -448,6 +557,19 @@ hipError_t radix_sort(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, in
     *in_b = false;
     if (n <= 0 || key_bits <= 0) return hipSuccess;
     if (n > 0xFFFFFFFFll || key_bits > 32) return hipErrorInvalidValue;
+    if (n <= kBlockSort) {  // one launch, in place
+        const uint32_t* vin = iota ? nullptr : va;
+        const dim3 one(1), wg(kBlockThreads);
+        if (n <= 2 * kBlockThreads)
+            hipLaunchKernelGGL(k_rs_block<2>, one, wg, 0, s, ka, vin, va, (uint32_t)n, key_bits);
+        else if (n <= 6 * kBlockThreads)
+            hipLaunchKernelGGL(k_rs_block<6>, one, wg, 0, s, ka, vin, va, (uint32_t)n, key_bits);
+        else if (n <= 10 * kBlockThreads)
+            hipLaunchKernelGGL(k_rs_block<10>, one, wg, 0, s, ka, vin, va, (uint32_t)n, key_bits);
+        else
+            hipLaunchKernelGGL(k_rs_block<16>, one, wg, 0, s, ka, vin, va, (uint32_t)n, key_bits);
+        return hipGetLastError();
+    }
     // Small sorts (keys per block of the full grid below 1024): 1024-key
     // sub-chunks.
     const bool small = n <= (int64_t)kRsGrid * 256 * kRsItemsSmall;
