@@ -1276,6 +1276,34 @@ __device__ __forceinline__ void accumulate(float al, float dsel, const float4& r
     }
 }
 
+// Whether a record whose band meets the wave's 8x8 region (centre offset
+// dx, dy from the projected centre) still misses every pixel of it.  The
+// band bounds the footprint across its narrowest direction only; along the
+// others the region may lie past the footprint's end.  In plane coordinates
+// (u, v) = (nu, nv) / den the footprint is the disc u^2 + v^2 <= ln(o /
+// alpha_min); over the region |(nu, nv)| falls below its value at the centre
+// by at most the larger half diagonal of the region's image, and den rises
+// by at most 3.5 (|N1| + |N2|).  The low-pass disc must be missed too.
+// Every bound is widened far beyond the rounding of these sums and of
+// pair_alpha's, so a record dropped here would have got alpha < alpha_min at
+// every pixel and changed nothing.  (One lane tests one record, so this
+// costs each wave less than one of the evaluations it saves.)
+__device__ __forceinline__ bool region_misses(const float4& r0, const float4& r1, float op, float dx, float dy,
+                                              const BlendArgs& a) {
+    const float lr = __logf(op * __builtin_amdgcn_rcpf(a.alpha_min)) + 1e-3f;
+    const float cx = r0.z * dx, cy = r0.w * dy, ex = r1.x * dx, ey = r1.y * dy, nx = r1.z * dx, ny = r1.w * dy;
+    const float nu = cx + cy, nv = ex + ey;
+    const float dden = 3.5f * (fabsf(r1.z) + fabsf(r1.w)) + 1e-5f * (1.f + fabsf(nx) + fabsf(ny));
+    const float den = 1.f + nx + ny;
+    const float pu = r0.z + r0.w, pv = r1.x + r1.y, qu = r0.z - r0.w, qv = r1.x - r1.y;
+    const float reach = 3.5f * __builtin_amdgcn_sqrtf(fmaxf(fmaf(pu, pu, pv * pv), fmaf(qu, qu, qv * qv))) * 1.0001f +
+                        1e-5f * (fabsf(cx) + fabsf(cy) + fabsf(ex) + fabsf(ey));
+    const float rest = __builtin_amdgcn_sqrtf(fmaf(nu, nu, nv * nv)) * 0.9999f - reach, far = den + dden;
+    const bool plane = rest > 0.f && den > 2.f * dden && rest * rest * 0.9999f > lr * far * far;
+    const float lx = fmaxf(fabsf(dx) - 3.5f, 0.f), ly = fmaxf(fabsf(dy) - 3.5f, 0.f);
+    return plane && (!a.lowpass || fmaf(lx, lx, ly * ly) * 0.9999f > lr);
+}
+
 // Region test, compaction and compositing of one staged batch of nb records
 // by one wave (no block barriers).
 template <bool kCount, bool kXfer = false>
@@ -1294,7 +1322,8 @@ __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uin
             const float ny = snorm16_value((int)(int16_t)(nq >> 16));
             const float4 r0 = s_rec[4 * j];
             const float pr = fmaf(nx, g.scx - r0.x, ny * (g.scy - r0.y)) - half_value(bq);
-            h = fabsf(pr) <= half_value(bq >> 16) + 3.5f * (fabsf(nx) + fabsf(ny));
+            h = fabsf(pr) <= half_value(bq >> 16) + 3.5f * (fabsf(nx) + fabsf(ny)) &&
+                !region_misses(r0, s_rec[4 * j + 1], s_rec[4 * j + 2].z, g.scx - r0.x, g.scy - r0.y, a);
         }
         const uint64_t m = __ballot(h);
         if (h) {
