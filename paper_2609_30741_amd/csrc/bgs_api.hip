@@ -76,7 +76,7 @@ struct Layout {
     size_t zbuf, hole, hole2, bcount, rmask, bbox, pflag, pbox, wpart, gpart;
     size_t ranges, torder, cmask, ctot, cstart, cpre, ttot;
     size_t xrgb;  // view-colour transfer: the dominant pass's affiliated-view colours [3][H][W]
-    size_t recs, zkeys, rects, dkeys_b, dvals_a, dvals_b, matrix, kpart;
+    size_t recs, zkeys, rects, dkeys_b, dvals_a, dvals_b, band, mu, matrix, kpart;
     size_t recs2, zkeys2, rects2;  // the affiliated eye's surfels, from the dominant pass of a stereo frame
     size_t emask, eid, tcount, vals;
     size_t radix;
@@ -129,6 +129,8 @@ Layout make_layout(int64_t n, int64_t W, int64_t H, int64_t kc) {
     L.dkeys_b = take(4 * n);
     L.dvals_a = take(4 * n);
     L.dvals_b = take(4 * n);
+    L.band = take(16 * n);
+    L.mu = take(8 * n);
     // A smaller image has fewer cells and may take more chunks of the order:
     // the table is sized for the most that any image up to this size needs.
     L.matrix = take(4 * bin_table_words(n, nc));
@@ -416,6 +418,8 @@ int raster_pass(bgs_ctx* ctx, const Layout& L, void* ws, int64_t kc, const bgs_s
     bin_split(n, b.n_cells, &b.chunks, &b.fine, &b.per);
     b.cap = (uint32_t)kc;
     b.mask = mask;
+    b.band = at<uint4>(ws, L.band);
+    b.mu = at<float2>(ws, L.mu);
     b.matrix = at<uint32_t>(ws, L.matrix);
     b.kpart = at<uint2>(ws, L.kpart);
     b.ctot = at<uint32_t>(ws, L.ctot);

@@ -75,6 +75,8 @@ struct BinArgs {
     uint32_t n_cells;
     uint32_t cap;      // key capacity: list words, and at most as many entries
     CellMask mask;
+    uint4* band;       // per position of the order: rect, band direction and interval (empty rect: no entries)
+    float2* mu;        // and the projected centre
     uint32_t* matrix;  // [n_cells][chunks] entries, then their exclusive scan over the chunks
     uint2* kpart;      // per chunk: keys, entries
     uint32_t* ctot;    // per cell: entries

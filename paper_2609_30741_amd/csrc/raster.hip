@@ -182,14 +182,15 @@ struct BandRows {
     double k0, k16, r, inv;  // k(ty) = k0 + k16 ty; columns where |16 nx tx + k| <= r
     bool vertical;           // nx = 0 (or no direction): whole rows in or out
     __device__ BandRows() : k0(0.0), k16(0.0), r(-1.0), inv(0.0), vertical(true) {}  // no tile
-    __device__ explicit BandRows(const SurfelRec& rec) {
+    __device__ explicit BandRows(const SurfelRec& rec)
+        : BandRows(rec.a.x, rec.a.y, __float_as_uint(rec.c.w), __float_as_uint(rec.d.w)) {}
+    __device__ BandRows(float mux, float muy, uint32_t nq, uint32_t bq) {
 #pragma clang fp contract(off)
-        const uint32_t nq = __float_as_uint(rec.c.w), bq = __float_as_uint(rec.d.w);
         const double nx = (double)snorm16_value((int)(int16_t)(nq & 0xFFFFu));
         const double ny = (double)snorm16_value((int)(int16_t)(nq >> 16));
         const double c = (double)half_value(bq);
         r = (double)half_value(bq >> 16) + 7.5 * (fabs(nx) + fabs(ny)) + 0.5;
-        k0 = nx * (7.5 - (double)rec.a.x) + ny * (7.5 - (double)rec.a.y) - c;
+        k0 = nx * (7.5 - (double)mux) + ny * (7.5 - (double)muy) - c;
         k16 = 16.0 * ny;
         vertical = !(fabs(nx) > 1e-9);
         inv = vertical ? 0.0 : 1.0 / (16.0 * nx);
@@ -569,25 +570,41 @@ __device__ __forceinline__ void bin_chunk(const BinArgs& a, uint32_t c, int64_t*
 }
 
 // Stages surfels order[p0 .. p0 + m) and returns the number of items.  Has
-// block barriers; the stage may be read after it.
+// block barriers; the stage may be read after it.  kGather (the counting
+// kernel): rects and bands are gathered through the order, and kept in
+// compositing order for the emission, which reads them from there (two
+// gathers of a line each per surfel are a third of these kernels' time).
+template <bool kGather>
 __device__ __forceinline__ uint32_t bin_stage(const BinArgs& a, int64_t p0, int m, BinStage& s) {
     const int t = threadIdx.x;
     uint32_t rows = 0;
     if (t < m) {
         const uint32_t k = a.order[p0 + t];
-        const uint2 rc = a.rects[k];
-        if (!(rc.x > rc.y)) {
-            const int tx0 = rc.x & 0xFFFF, ty0 = rc.x >> 16, tx1 = rc.y & 0xFFFF, ty1 = rc.y >> 16;
-            if (!a.mask.cells || rect_masked(a.mask, tx0, ty0, tx1, ty1)) {
-                const BandRows br(a.recs[k]);
-                s.k0[t] = br.k0;
-                s.k16[t] = br.k16;
-                s.r[t] = br.r;
-                s.inv[t] = br.inv;
-                s.rect[t] = rc;
-                s.id[t] = k;
-                rows = (uint32_t)((ty1 >> 3) - (ty0 >> 3) + 1);
+        uint4 g = make_uint4(1u, 0u, 0u, 0u);  // rect, band direction and interval
+        float2 mu = make_float2(0.f, 0.f);
+        if (kGather) {
+            const uint2 rc = a.rects[k];
+            if (!(rc.x > rc.y) && (!a.mask.cells || rect_masked(a.mask, (int)(rc.x & 0xFFFFu), (int)(rc.x >> 16),
+                                                                (int)(rc.y & 0xFFFFu), (int)(rc.y >> 16)))) {
+                const SurfelRec& r = a.recs[k];
+                g = make_uint4(rc.x, rc.y, __float_as_uint(r.c.w), __float_as_uint(r.d.w));
+                mu = make_float2(r.a.x, r.a.y);
             }
+            a.band[p0 + t] = g;
+            a.mu[p0 + t] = mu;
+        } else {
+            g = a.band[p0 + t];
+            mu = a.mu[p0 + t];
+        }
+        if (!(g.x > g.y)) {
+            const BandRows br(mu.x, mu.y, g.z, g.w);
+            s.k0[t] = br.k0;
+            s.k16[t] = br.k16;
+            s.r[t] = br.r;
+            s.inv[t] = br.inv;
+            s.rect[t] = make_uint2(g.x, g.y);
+            s.id[t] = k;
+            rows = (g.y >> 19) - (g.x >> 19) + 1;  // cell rows: tile row / 8
         }
     }
     uint32_t total;
@@ -634,7 +651,7 @@ __global__ __launch_bounds__(256) void k_bin_count(BinArgs a) {
     uint32_t keys = 0;
     for (int64_t p = p0; p < p1; p += 256) {
         __syncthreads();
-        const uint32_t items = bin_stage(a, p, (int)min((int64_t)256, p1 - p), s);
+        const uint32_t items = bin_stage<true>(a, p, (int)min((int64_t)256, p1 - p), s);
         for (uint32_t it = t; it < items; it += 256)
             bin_item(a, s, it, [&](int, uint32_t cell, uint64_t m) {
                 atomicAdd(&s_cnt[cell], 1u);
@@ -786,7 +803,7 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
     bin_chunk(a, blockIdx.x, &p0, &p1);
     for (int64_t p = p0; p < p1; p += 256) {
         __syncthreads();
-        const uint32_t items = bin_stage(a, p, (int)min((int64_t)256, p1 - p), s);
+        const uint32_t items = bin_stage<false>(a, p, (int)min((int64_t)256, p1 - p), s);
         if (items == 0) continue;  // uniform
         for (uint32_t w0 = 0; w0 < a.n_cells; w0 += kBinWin) {
             const uint32_t nw = min((uint32_t)kBinWin, a.n_cells - w0);
