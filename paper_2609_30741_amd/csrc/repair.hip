@@ -21,6 +21,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "bgs_repair.h"
 
@@ -115,6 +116,24 @@ constexpr size_t conv_lds_bytes(int cpad, int rows) {
     return (size_t)(rows + 2) * kConvCols * (cpad + conv_pad(cpad)) * sizeof(uint16_t);
 }
 
+// Two floats to bf16, round to nearest even, the first in the low half.
+__device__ __forceinline__ uint32_t pack_bf(float a, float b) {
+    typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    const v2bf v = {(__bf16)a, (__bf16)b};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// Items of the fill that a thread has in flight: all of its share where
+// that leaves registers, else half.
+constexpr int conv_fill(int items) {
+    const int u = (items + 255) / 256;
+    return u <= 14 ? u : (u + 1) / 2;
+}
+
+// Input widths of the decoders, whose first channels come from the coarser
+// level.
+constexpr bool conv_has_up(int cpad) { return cpad == 48 || cpad == 96; }
+
 template <int CPAD, int MT, int R>
 __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
     constexpr int PS = CPAD + conv_pad(CPAD);  // staged bf16 per pixel
@@ -126,9 +145,6 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
     const int groups = (a.cout + 16 * MT - 1) / (16 * MT);
     const int y0 = blockIdx.y * R, b = blockIdx.z / groups, m0 = (blockIdx.z - b * groups) * MT;
     const int xb = blockIdx.x * 64;
-    const int W2 = a.W >> 1;
-    const uint16_t* inb = a.in + (int64_t)b * a.in_bs;
-    const uint16_t* upb = a.up ? a.up + (int64_t)b * a.up_bs : nullptr;
     const int n = lane & 15, kg = lane >> 4;
     const int mt = min(MT, ((a.cout + 15) >> 4) - m0);
     // Wave w computes output tile m = w % MT (of the group) for CT = 4 / CW
@@ -147,48 +163,87 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
 #pragma unroll
     for (int s = 0; s < P; ++s) wq[s] = *reinterpret_cast<const uint4*>(wl + 32 * s);
     // Fill: item = (row, column, channel group), group fastest, so a wave's
-    // loads walk consecutive 16-byte words of consecutive pixels.  Up to 12
-    // items' loads per thread are in flight before their stores (one round
-    // trip for all but the widest input).  Channels at or past
-    // cin read as zero (a group past cin is not loaded: it may lie beyond
-    // the tensor's pixel stride).
-    constexpr int items = (R + 2) * kConvCols * G;
-    constexpr int U = (items + 255) / 256 < 12 ? (items + 255) / 256 : 12;
-    for (int i0 = threadIdx.x; i0 < items; i0 += 256 * U) {
-        uint4 v[U];
+    // loads walk consecutive 16-byte words of consecutive pixels.  A thread
+    // takes every 256th item and steps its (row, column, group) along, with
+    // 32-bit offsets from the block's corner; blocks inside the image skip
+    // the bounds.  (These layers are as much bound by such arithmetic as by
+    // their products: deriving every item from its number, the 48-channel
+    // layer filled 57% of its issue slots with vector instructions.)  Up to
+    // 14 items' loads per thread are in flight before their stores.
+    // Channels at or past cin read as zero (a group past cin is not loaded:
+    // it may lie beyond the tensor's pixel stride); only 16-channel inputs
+    // have any.
+    constexpr int items = (R + 2) * kConvCols * G, U = conv_fill(items);
+    constexpr bool kUp = conv_has_up(CPAD), kPartial = CPAD == 16;
+    const char* in0 = reinterpret_cast<const char*>(
+        a.in + (int64_t)b * a.in_bs + ((int64_t)(y0 - 1) * a.W + (xb - 1)) * a.in_ps - a.up_c);
+    // y0 and xb are even, so the corner lies in the odd half of its 2x2 block.
+    const char* up0 = kUp ? reinterpret_cast<const char*>(a.up + (int64_t)b * a.up_bs +
+                                                          ((int64_t)(y0 / 2 - 1) * (a.W >> 1) + xb / 2 - 1) * a.up_ps)
+                          : nullptr;
+    const uint32_t in_row = 2u * a.W * a.in_ps, in_px = 2u * a.in_ps, up_row = (uint32_t)(a.W >> 1) * 2u * a.up_ps,
+                   up_px = 2u * a.up_ps;
+    const auto fill = [&](auto inside) {
+        int g = (int)threadIdx.x % G, rc = (int)threadIdx.x / G;
+        int c = rc % kConvCols, r = rc / kConvCols;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int it = i0 + 256 * u;
-            const int g = it % G, rc = it / G;
-            const int c = rc % kConvCols, r = rc / kConvCols;
-            const int yy = y0 + r - 1, xx = xb + c - 1, ci = 8 * g;
-            const bool ok = it < items && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W && ci < a.cin;
-            v[u] = uint4{0u, 0u, 0u, 0u};
-            if (ok) {
-                const uint16_t* src = ci < a.up_c
-                                          ? upb + ((int64_t)(yy >> 1) * W2 + (xx >> 1)) * a.up_ps + ci
-                                          : inb + ((int64_t)yy * a.W + xx) * a.in_ps + (ci - a.up_c);
-                v[u] = *reinterpret_cast<const uint4*>(src);
-                const int left = a.cin - ci;  // channels of this group that exist
-                if (left < 8) {
-                    uint32_t* q = reinterpret_cast<uint32_t*>(&v[u]);
+        for (int i0 = 0; i0 < items; i0 += 256 * U) {
+            uint4 v[U];
+            int at[U];
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const uint32_t keep = (2 * k + 1 < left ? 0xFFFF0000u : 0u) | (2 * k < left ? 0xFFFFu : 0u);
-                        q[k] &= keep;
-                    }
+            for (int u = 0; u < U; ++u) {
+                const int ci = 8 * g;
+                at[u] = rc * PS + ci;
+                bool ok = i0 + 256 * u + 256 <= items || i0 + 256 * u + (int)threadIdx.x < items;
+                if (!inside.value)
+                    ok = ok && (unsigned)(y0 - 1 + r) < (unsigned)a.H && (unsigned)(xb - 1 + c) < (unsigned)a.W;
+                if (kPartial) ok = ok && ci < a.cin;
+                v[u] = uint4{0u, 0u, 0u, 0u};
+                if (ok) {
+                    const bool up = kUp && ci < a.up_c;
+                    const char* src = up ? up0 : in0;
+                    const uint32_t rr = up ? (uint32_t)(r + 1) >> 1 : (uint32_t)r, cc = up ? (uint32_t)(c + 1) >> 1 : (uint32_t)c;
+                    v[u] = *reinterpret_cast<const uint4*>(
+                        src + (uint32_t)(rr * (up ? up_row : in_row) + cc * (up ? up_px : in_px) + 2u * ci));
+                }
+                // The thread's next item, 256 on.
+                constexpr int dg = 256 % G, dc = 256 / G;
+                rc += dc;
+                c += dc;
+                if (dg) {
+                    g += dg;
+                    const bool carry = g >= G;
+                    g -= carry ? G : 0;
+                    rc += carry ? 1 : 0;
+                    c += carry ? 1 : 0;
+                }
+#pragma unroll
+                for (int k = 0; k < (dc + kConvCols) / kConvCols; ++k) {
+                    const bool wrap = c >= kConvCols;
+                    c -= wrap ? kConvCols : 0;
+                    r += wrap ? 1 : 0;
                 }
             }
-        }
+            if (kPartial && a.cin < 16) {  // uniform: groups that straddle cin
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int it = i0 + 256 * u;
-            if (it < items) {
-                const int g = it % G, rc = it / G;
-                *reinterpret_cast<uint4*>(s_in + rc * PS + 8 * g) = v[u];
+                for (int u = 0; u < U; ++u) {
+                    const int left = a.cin - 8 * g;  // 256 % G is 0: one group per thread
+                    uint32_t* q = reinterpret_cast<uint32_t*>(&v[u]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        q[k] &= (2 * k + 1 < left ? 0xFFFF0000u : 0u) | (2 * k < left ? 0xFFFFu : 0u);
+                }
             }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + 256 * u + 256 <= items || i0 + 256 * u + (int)threadIdx.x < items)
+                    *reinterpret_cast<uint4*>(s_in + at[u]) = v[u];
         }
-    }
+    };
+    if (y0 > 0 && y0 + R < a.H && xb > 0 && xb + 64 < a.W)
+        fill(std::true_type{});
+    else
+        fill(std::false_type{});
     __syncthreads();
     if (!busy || wm >= mt || xb + 16 * wc >= a.W) return;  // whole wave, after the block's only barrier
     v4f acc[CT][R];
@@ -196,24 +251,31 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
     for (int c = 0; c < CT; ++c)
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[c][r] = v4f{0.f, 0.f, 0.f, 0.f};
+    // A lane's operands of slice s: k = 32 s + 8 kg .. + 7, one tap and eight
+    // channels.  A slice that crosses into the next tap does so at its middle
+    // (CPAD is 16 or a multiple of 16 that 32-slices meet there), and the
+    // next tap is one column on, or a row on and two columns back: three
+    // lane bases serve every slice with constant offsets.
+    static_assert(CPAD % 32 == 0 || CPAD % 32 == 16, "slices cross taps at their middle only");
+    const int hi = kg >= 2 ? 1 : 0;
+    const uint16_t* base0 = s_in + (16 * wc + n) * PS + 8 * kg;
+    const uint16_t* base1 = base0 + hi * (PS - CPAD);
+    const uint16_t* base2 = base0 + hi * ((kConvCols - 2) * PS - CPAD);
 #pragma unroll
     for (int s = 0; s < SL; ++s) {
-        // This lane's operands: k = 32 s + 8 kg .. + 7, one tap t and eight
-        // channels from ci.  Past the last tap (the zero padding of the
-        // reduction) the operands are zero.
-        const int k = 32 * s + 8 * kg;
-        const int t = k / CPAD, ci = k - t * CPAD;
-        const int ty = t / 3, tx = t - 3 * ty;
+        const int t0 = 32 * s / CPAD, t1 = (32 * s + 16) / CPAD;  // taps of the slice's halves
+        const int off = ((t0 / 3) * kConvCols + t0 % 3) * PS + 32 * s - t0 * CPAD;
+        const uint16_t* base = t1 == t0 || t1 >= 9 ? base0 : t1 % 3 ? base1 : base2;
         const v8bf av = __builtin_bit_cast(v8bf, wq[s % P]);
         if (s + P < SL) wq[s % P] = *reinterpret_cast<const uint4*>(wl + 32 * (s + P));
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            const int col = 16 * (wc + c) + n;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
+                // Past the last tap (the zero padding of the reduction) the
+                // operands are zero.
                 uint4 q = uint4{0u, 0u, 0u, 0u};
-                if (32 * s + 32 <= 9 * CPAD || t < 9)
-                    q = *reinterpret_cast<const uint4*>(s_in + ((r + ty) * kConvCols + col + tx) * PS + ci);
+                if (t1 < 9 || !hi) q = *reinterpret_cast<const uint4*>(base + off + (r * kConvCols + 16 * c) * PS);
                 acc[c][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(v8bf, q), acc[c][r], 0, 0, 0);
             }
         }
@@ -225,43 +287,38 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
     float bias[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) bias[j] = a.bias ? a.bias[co + j] : 0.f;
-    float st[CT][R][4];  // the stored values, for the pool
+    const int64_t corner = (int64_t)y0 * a.W + xb;  // offsets from here fit 32 bits
+    char* ob = a.out ? reinterpret_cast<char*>(a.out + (int64_t)b * a.out_bs + corner * a.out_ps) : nullptr;
+    const char* mb = a.mask ? reinterpret_cast<const char*>(a.mask + (int64_t)b * a.mask_bs + corner * a.mask_ps) : nullptr;
+    uint2 h[CT][R];  // the stored values
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-        const int x = xb + 16 * (wc + c) + n;
+        const int px = 16 * (wc + c) + n;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int y = y0 + r;
-            const bool in = x < a.W && y < a.H;
-            const int64_t pix = (int64_t)y * a.W + x;
+            const bool in = xb + px < a.W && y0 + r < a.H;
+            const uint32_t pix = (uint32_t)(r * a.W + px);
             float v[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 v[j] = acc[c][r][j] + bias[j];
                 if (a.relu) v[j] = fmaxf(v[j], 0.f);
             }
-            if (in && a.mask) {
-                const uint2 mk =
-                    *reinterpret_cast<const uint2*>(a.mask + (int64_t)b * a.mask_bs + pix * a.mask_ps + co);
-                if (!(bf2f((uint16_t)(mk.x & 0xFFFFu)) > 0.f)) v[0] = 0.f;
-                if (!(bf2f((uint16_t)(mk.x >> 16)) > 0.f)) v[1] = 0.f;
-                if (!(bf2f((uint16_t)(mk.y & 0xFFFFu)) > 0.f)) v[2] = 0.f;
-                if (!(bf2f((uint16_t)(mk.y >> 16)) > 0.f)) v[3] = 0.f;
+            if (in && mb) {
+                const uint2 mk = *reinterpret_cast<const uint2*>(mb + 2u * (pix * a.mask_ps + co));
+                if (!(__uint_as_float(mk.x << 16) > 0.f)) v[0] = 0.f;
+                if (!(__uint_as_float(mk.x & 0xFFFF0000u) > 0.f)) v[1] = 0.f;
+                if (!(__uint_as_float(mk.y << 16) > 0.f)) v[2] = 0.f;
+                if (!(__uint_as_float(mk.y & 0xFFFF0000u) > 0.f)) v[3] = 0.f;
             }
-            uint16_t h[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                h[j] = f2bf(v[j]);
-                st[c][r][j] = bf2f(h[j]);
-            }
+            h[c][r] = uint2{pack_bf(v[0], v[1]), pack_bf(v[2], v[3])};
             if (!in) continue;
             if (a.out_f) {
+                float* of = a.out_f + (int64_t)b * a.out_bs + (int64_t)co * a.H * a.W + corner;
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    a.out_f[(int64_t)b * a.out_bs + (int64_t)(co + j) * a.H * a.W + pix] = v[j];
+                for (int j = 0; j < 4; ++j) (of + (int64_t)j * a.H * a.W)[pix] = v[j];
             } else {
-                *reinterpret_cast<uint2*>(a.out + (int64_t)b * a.out_bs + pix * a.out_ps + co) =
-                    uint2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
+                *reinterpret_cast<uint2*>(ob + 2u * (pix * a.out_ps + co)) = h[c][r];
             }
         }
     }
@@ -271,24 +328,25 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
     // summed in the order (x, y), (x + 1, y), (x, y + 1), (x + 1, y + 1).
     // With W and H even a pair of columns or rows is inside the image or
     // outside together.
+    char* pb = reinterpret_cast<char*>(a.pool + (int64_t)b * a.pool_bs +
+                                       ((int64_t)(y0 >> 1) * (a.W >> 1) + (xb >> 1)) * a.pool_ps);
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-        const int x = xb + 16 * (wc + c) + n;
+        const int px = 16 * (wc + c) + n;
 #pragma unroll
         for (int r = 0; r < R; r += 2) {
-            const int y = y0 + r;
             float q[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float s0 = st[c][r][j], s2 = st[c][r + 1][j];
+                const uint32_t u0 = j < 2 ? h[c][r].x : h[c][r].y, u2 = j < 2 ? h[c][r + 1].x : h[c][r + 1].y;
+                const float s0 = __uint_as_float(j & 1 ? u0 & 0xFFFF0000u : u0 << 16);
+                const float s2 = __uint_as_float(j & 1 ? u2 & 0xFFFF0000u : u2 << 16);
                 const float s1 = __shfl_xor(s0, 1, 64), s3 = __shfl_xor(s2, 1, 64);
                 q[j] = 0.25f * (((s0 + s1) + s2) + s3);
             }
-            if ((n & 1) || x >= a.W || y >= a.H) continue;
-            const int64_t pp = (int64_t)(y >> 1) * (a.W >> 1) + (x >> 1);
-            *reinterpret_cast<uint2*>(a.pool + (int64_t)b * a.pool_bs + pp * a.pool_ps + co) =
-                uint2{(uint32_t)f2bf(q[0]) | ((uint32_t)f2bf(q[1]) << 16),
-                      (uint32_t)f2bf(q[2]) | ((uint32_t)f2bf(q[3]) << 16)};
+            if ((n & 1) || xb + px >= a.W || y0 + r >= a.H) continue;
+            const uint32_t pp = (uint32_t)((r >> 1) * (a.W >> 1) + (px >> 1));
+            *reinterpret_cast<uint2*>(pb + 2u * (pp * a.pool_ps + co)) = uint2{pack_bf(q[0], q[1]), pack_bf(q[2], q[3])};
         }
     }
 }
@@ -876,7 +934,10 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256); }
 constexpr bool conv_cpad_ok(int cpad) { return cpad == 16 || cpad == 32 || cpad == 48 || cpad == 64 || cpad == 96; }
 constexpr bool net_cpads_ok() {
     for (int l = 0; l < kLayers; ++l)
-        if (!conv_cpad_ok(pad16(kNet[l].cin)) || !conv_cpad_ok(pad16(kNet[l].cout))) return false;
+        if (!conv_cpad_ok(pad16(kNet[l].cin)) || !conv_cpad_ok(pad16(kNet[l].cout)) ||
+            conv_has_up(pad16(kNet[l].cin)) != (l == D2 || l == D1) || conv_has_up(pad16(kNet[l].cout)) ||
+            (kNet[l].cin > 16 && kNet[l].cin % 16) || (kNet[l].cout > 16 && kNet[l].cout % 16))
+            return false;
     return true;
 }
 static_assert(net_cpads_ok(), "every layer's input and output width needs a convolution instance");
