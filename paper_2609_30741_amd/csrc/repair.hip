@@ -88,7 +88,15 @@ struct ConvArgs {
     int pool_ps;
     int relu;
     int H, W;
+    // Inference: the first layer forms its input from the images
+    // (kConvInput), the last one writes the repaired image (kConvOutput).
+    const float* rgb;     // [B][3][H][W]
+    const float* z;       // [B][H][W]
+    const uint8_t* hole;  // [B][H][W]
+    float* rgb_out;       // [B][3][H][W]
+    float* err_out;       // [B][H][W], may be null
 };
+enum { kConvPlain, kConvInput, kConvOutput };
 
 // Block: 4 waves over 64 pixels (x from blockIdx.x * 64) of R consecutive
 // rows from R blockIdx.y; blockIdx.z = image * groups + group, a group
@@ -134,7 +142,17 @@ constexpr int conv_fill(int items) {
 // level.
 constexpr bool conv_has_up(int cpad) { return cpad == 48 || cpad == 96; }
 
-template <int CPAD, int MT, int R>
+// Network input of one pixel, eight channels: warped rgb (zero at holes),
+// hole flag, 1/z (zero at holes and background), three zero slots.
+__device__ __forceinline__ uint4 input_pixel(float r, float g, float b, float z, bool hole) {
+    const float inv = (hole || !(z < INFINITY)) ? 0.f : 1.f / z;
+    return uint4{pack_bf(hole ? 0.f : r, hole ? 0.f : g), pack_bf(hole ? 0.f : b, hole ? 1.f : 0.f), pack_bf(inv, 0.f), 0u};
+}
+
+// kMode: kConvInput and kConvOutput are the first and last layer of an
+// inference pass, without the tensors (16 bytes a pixel written and read
+// again, each) and the launches between them and the images.
+template <int CPAD, int MT, int R, int kMode = kConvPlain>
 __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
     constexpr int PS = CPAD + conv_pad(CPAD);  // staged bf16 per pixel
     constexpr int G = CPAD / 8;               // 16-byte channel groups per pixel
@@ -162,6 +180,22 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
     uint4 wq[P];
 #pragma unroll
     for (int s = 0; s < P; ++s) wq[s] = *reinterpret_cast<const uint4*>(wl + 32 * s);
+    // kConvOutput: the images' values, in flight during the fill.  Lane kg
+    // holds output channel kg of its pixels (spread weight rows): a colour
+    // plane, or the predicted error.
+    float oq[kMode == kConvOutput ? R : 1];
+    uint8_t oh[kMode == kConvOutput ? R : 1];
+    if constexpr (kMode == kConvOutput) {
+        static_assert(CT == 1, "the output layer has one column tile a wave");
+        const int64_t hw = (int64_t)a.H * a.W;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int x = min(xb + 16 * wc + n, a.W - 1), y = min(y0 + r, a.H - 1);
+            const int64_t p = (int64_t)y * a.W + x;
+            oh[r] = a.hole[b * hw + p];
+            oq[r] = a.rgb[(3 * b + min(kg, 2)) * hw + p];
+        }
+    }
     // Fill: item = (row, column, channel group), group fastest, so a wave's
     // loads walk consecutive 16-byte words of consecutive pixels.  A thread
     // takes every 256th item and steps its (row, column, group) along, with
@@ -240,10 +274,41 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
                     *reinterpret_cast<uint4*>(s_in + at[u]) = v[u];
         }
     };
-    if (y0 > 0 && y0 + R < a.H && xb > 0 && xb + 64 < a.W)
+    if constexpr (kMode == kConvInput) {
+        static_assert(CPAD == 16 && PS == 24, "the network input has eight of 16 channels");
+        constexpr int pixels = (R + 2) * kConvCols, V = (pixels + 255) / 256;
+        const int64_t hw = (int64_t)a.H * a.W;
+        const float *ib = a.rgb + 3 * b * hw, *zb = a.z + b * hw;
+        const uint8_t* hb = a.hole + b * hw;
+        float cr[V], cg[V], cb[V], cz[V];
+        uint8_t ch[V];
+        bool in[V];
+#pragma unroll
+        for (int u = 0; u < V; ++u) {  // all loads first
+            const int i = (int)threadIdx.x + 256 * u, r = i / kConvCols, c = i - r * kConvCols;
+            const int y = y0 - 1 + r, x = xb - 1 + c;
+            in[u] = i < pixels && y >= 0 && y < a.H && x >= 0 && x < a.W;
+            const int64_t p = in[u] ? (int64_t)y * a.W + x : 0;
+            cr[u] = ib[p];
+            cg[u] = ib[hw + p];
+            cb[u] = ib[2 * hw + p];
+            cz[u] = zb[p];
+            ch[u] = hb[p];
+        }
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            const int i = (int)threadIdx.x + 256 * u;
+            if (i >= pixels) continue;
+            uint4 v = input_pixel(cr[u], cg[u], cb[u], cz[u], ch[u] != 0);
+            if (!in[u]) v = uint4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<uint4*>(s_in + i * PS) = v;
+            *reinterpret_cast<uint4*>(s_in + i * PS + 8) = uint4{0u, 0u, 0u, 0u};
+        }
+    } else if (y0 > 0 && y0 + R < a.H && xb > 0 && xb + 64 < a.W) {
         fill(std::true_type{});
-    else
+    } else {
         fill(std::false_type{});
+    }
     __syncthreads();
     if (!busy || wm >= mt || xb + 16 * wc >= a.W) return;  // whole wave, after the block's only barrier
     v4f acc[CT][R];
@@ -282,6 +347,21 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
     }
     // Lane holds output channels co .. co + 3 of pixel column n of each
     // column tile: one 8-byte store per row and tile (cout is a multiple of 4).
+    if constexpr (kMode == kConvOutput) {
+        // Channels 0-2 the residual, 3 the predicted squared error.
+        const int64_t hw = (int64_t)a.H * a.W;
+        const float ob = a.bias[kg];
+        float* op = kg < 3 ? a.rgb_out + (3 * b + kg) * hw : a.err_out ? a.err_out + b * hw : nullptr;
+        if (!op) return;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int x = xb + 16 * wc + n, y = y0 + r;
+            if (x >= a.W || y >= a.H) continue;
+            const float res = acc[0][r][0] + ob;
+            op[(int64_t)y * a.W + x] = kg < 3 ? (oh[r] ? oq[r] + res : oq[r]) : (oh[r] ? res : 0.f);
+        }
+        return;
+    }
     const int co = (m0 + wm) * 16 + 4 * kg;
     if (co >= a.cout) return;
     float bias[4];
@@ -580,6 +660,7 @@ struct PackJob {
     const float* w;
     uint16_t* out;
     int cin, cout, transpose, cpad, kpad;
+    int spread;  // output channel c in row 4 c (kConvOutput), the other rows zero
 };
 struct PackJobs {
     PackJob job[2 * kLayers];
@@ -596,7 +677,9 @@ __global__ __launch_bounds__(256) void k_pack(PackJobs J) {
     const float* __restrict__ w = P.w;
     const int cin = P.cin, cout = P.cout, transpose = P.transpose, cpad = P.cpad, kpad = P.kpad;
     const int i = g - J.start[jb];
-    const int m = i / kpad, k = i - m * kpad;
+    int m = i / kpad;
+    const int k = i - m * kpad;
+    if (P.spread) m = m % 4 ? cout : m / 4;
     const int t = k / cpad, c = k - t * cpad;
     float v = 0.f;
     if (t < 9) {
@@ -687,40 +770,15 @@ __global__ __launch_bounds__(256) void k_merge(const uint16_t* __restrict__ skip
     st8(out + (b * H * W + p) * C + c, pack8(o));
 }
 
-// Network input x0 [B][H][W][8]: warped rgb (zero at holes), hole flag,
-// 1/z (zero at holes and background), three zero slots.
+// Network input x0 [B][H][W][8] (training: the weight gradient reads it).
 __global__ __launch_bounds__(256) void k_input(const float* __restrict__ rgb, const float* __restrict__ z,
                                                const uint8_t* __restrict__ hole, int B, int HW,
                                                uint16_t* __restrict__ x0) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= (int64_t)B * HW) return;
     const int64_t b = i / HW, p = i - b * HW;
-    const bool h = hole[i] != 0;
-    const float zz = z[i];
-    float f[8];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) f[c] = h ? 0.f : rgb[(b * 3 + c) * HW + p];
-    f[3] = h ? 1.f : 0.f;
-    f[4] = (h || !(zz < INFINITY)) ? 0.f : 1.f / zz;
-    f[5] = f[6] = f[7] = 0.f;
-    st8(x0 + i * 8, pack8(f));
-}
-
-// r: [B][4][HW], channels 0-2 the residual, 3 the predicted squared error.
-__global__ __launch_bounds__(256) void k_output(const float* __restrict__ rgb, const uint8_t* __restrict__ hole,
-                                                const float* __restrict__ r, int B, int HW,
-                                                float* __restrict__ out, float* __restrict__ err) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (int64_t)B * HW) return;
-    const int64_t b = i / HW, p = i - b * HW;
-    const bool h = hole[i] != 0;
-    const float* rb = r + b * 4 * HW + p;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const int64_t q = (b * 3 + c) * HW + p;
-        out[q] = h ? rgb[q] + rb[(int64_t)c * HW] : rgb[q];
-    }
-    if (err) err[i] = h ? rb[3 * (int64_t)HW] : 0.f;
+    const float* q = rgb + b * 3 * HW + p;
+    st8(x0 + i * 8, input_pixel(q[0], q[HW], q[2 * (int64_t)HW], z[i], hole[i] != 0));
 }
 
 // Per-block hole counts.
@@ -885,7 +943,7 @@ Bufs layout(int B, int H, int W, bool train, char* base) {
     const size_t h1 = (size_t)H * W, h2 = h1 / 4, h3 = h1 / 16;
     auto bf = [&](size_t elems) { return (uint16_t*)(base + L.take(elems * 2)); };
     auto fl = [&](size_t elems) { return (float*)(base + L.take(elems * 4)); };
-    f.x0 = bf(B * 8 * h1);
+    if (train) f.x0 = bf(B * 8 * h1);
     f.e1a = bf(B * 16 * h1);
     f.e1b = bf(B * 16 * h1);
     f.p1 = bf(B * 16 * h2);
@@ -896,7 +954,7 @@ Bufs layout(int B, int H, int W, bool train, char* base) {
     f.e3b = bf(B * 64 * h3);
     f.d2 = bf(B * 32 * h2);
     f.d1 = bf(B * 16 * h1);
-    f.r = fl(B * 4 * h1);
+    if (train) f.r = fl(B * 4 * h1);
     for (int l = 0; l < kLayers; ++l) {
         f.wf[l] = bf((size_t)pad16(kNet[l].cout) * pad32(9 * pad16(kNet[l].cin)));
         f.wb[l] = bf((size_t)pad16(kNet[l].cin) * pad32(9 * pad16(kNet[l].cout)));
@@ -945,8 +1003,18 @@ static_assert(net_cpads_ok(), "every layer's input and output width needs a conv
 template <int CPAD, int MT, int R>
 void launch_conv(hipStream_t s, int B, const ConvArgs& a) {
     const int groups = (a.cout + 16 * MT - 1) / (16 * MT);
-    hipLaunchKernelGGL((k_conv3x3<CPAD, MT, R>), dim3((a.W + 63) / 64, (a.H + R - 1) / R, B * groups), dim3(256),
-                       conv_lds_bytes(CPAD, R), s, a);
+    const dim3 g((a.W + 63) / 64, (a.H + R - 1) / R, B * groups), wg(256);
+    if constexpr (CPAD == 16 && MT == 1) {  // the network's first and last layer
+        if (a.rgb_out) {
+            hipLaunchKernelGGL((k_conv3x3<CPAD, MT, R, kConvOutput>), g, wg, conv_lds_bytes(CPAD, R), s, a);
+            return;
+        }
+        if (a.rgb) {
+            hipLaunchKernelGGL((k_conv3x3<CPAD, MT, R, kConvInput>), g, wg, conv_lds_bytes(CPAD, R), s, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_conv3x3<CPAD, MT, R>), g, wg, conv_lds_bytes(CPAD, R), s, a);
 }
 
 // mt <= 2 for the tall shapes (more tiles would not fit in registers).
@@ -1022,9 +1090,20 @@ const View kNone{nullptr, 0, 0};
 // up (optional, with up_c): the half-resolution source of the first up_c
 // input channels, read through the nearest 2x upsample.  out_f (fp32
 // planes) replaces out when set.
+// images (first and last layer of an inference pass): see ConvArgs.
+struct Images {
+    const float *rgb, *z;
+    const uint8_t* hole;
+    float *rgb_out, *err_out;
+};
 void conv(hipStream_t s, int B, int H, int W, int l, bool transpose, const Bufs& f, View in, const float* params,
-          View out, float* out_f, View mask, View up = kNone, int up_c = 0, View pool = kNone) {
+          View out, float* out_f, View mask, View up = kNone, int up_c = 0, View pool = kNone, Images im = Images{}) {
     ConvArgs a{};
+    a.rgb = im.rgb;
+    a.z = im.z;
+    a.hole = im.hole;
+    a.rgb_out = im.rgb_out;
+    a.err_out = im.err_out;
     a.in = in.p;
     a.in_bs = in.bs;
     a.in_ps = in.ps;
@@ -1099,8 +1178,10 @@ Net views(const Bufs& f, int H, int W) {
 
 inline unsigned chan_blocks(int B, int64_t pixels, int C) { return blocks((int64_t)B * pixels * (C / 8)); }
 
+// Training keeps the network's input and residual; inference (rgb_out set)
+// takes the images straight into the first layer and out of the last.
 void forward(hipStream_t s, int B, int H, int W, const float* params, const float* rgb, const float* z,
-             const uint8_t* hole, const Bufs& f, bool train) {
+             const uint8_t* hole, const Bufs& f, bool train, float* rgb_out = nullptr, float* err_out = nullptr) {
     // Forward weights always; the transposed ones only for the input
     // gradient of training.
     PackJobs J{};
@@ -1116,6 +1197,7 @@ void forward(hipStream_t s, int B, int H, int W, const float* params, const floa
             P.transpose = t;
             P.cpad = pad16(t ? co : ci);
             P.kpad = pad32(9 * P.cpad);
+            P.spread = !train && l == OUT;
             J.start[J.n + 1] = J.start[J.n] + pad16(t ? ci : co) * P.kpad;
             ++J.n;
         }
@@ -1123,8 +1205,10 @@ void forward(hipStream_t s, int B, int H, int W, const float* params, const floa
     const Net n = views(f, H, W);
     const int64_t h1 = (int64_t)H * W;
     const int H2 = H / 2, W2 = W / 2, H3 = H / 4, W3 = W / 4;
-    hipLaunchKernelGGL(k_input, dim3(blocks(B * h1)), dim3(256), 0, s, rgb, z, hole, B, (int)h1, f.x0);
-    conv(s, B, H, W, E1A, false, f, n.x0, params, n.e1a, nullptr, kNone);
+    if (train)
+        hipLaunchKernelGGL(k_input, dim3(blocks(B * h1)), dim3(256), 0, s, rgb, z, hole, B, (int)h1, f.x0);
+    const Images none{}, first{rgb, z, hole, nullptr, nullptr}, last{rgb, nullptr, hole, rgb_out, err_out};
+    conv(s, B, H, W, E1A, false, f, n.x0, params, n.e1a, nullptr, kNone, kNone, 0, kNone, train ? none : first);
     // The encoders' second convolutions also store the pooled output.
     conv(s, B, H, W, E1B, false, f, n.e1a, params, n.e1b, nullptr, kNone, kNone, 0, n.p1);
     conv(s, B, H2, W2, E2A, false, f, n.p1, params, n.e2a, nullptr, kNone);
@@ -1135,7 +1219,7 @@ void forward(hipStream_t s, int B, int H, int W, const float* params, const floa
     // level.
     conv(s, B, H2, W2, D2, false, f, n.e2b, params, n.d2, nullptr, kNone, n.e3b, 64);
     conv(s, B, H, W, D1, false, f, n.e1b, params, n.d1, nullptr, kNone, n.d2, 32);
-    conv(s, B, H, W, OUT, false, f, n.d1, params, kNone, f.r, kNone);
+    conv(s, B, H, W, OUT, false, f, n.d1, params, kNone, train ? f.r : nullptr, kNone, kNone, 0, kNone, train ? none : last);
 }
 
 // Input gradients layer by layer, then all weight gradients (every layer's
@@ -1253,10 +1337,7 @@ BGS_API int32_t bgs_repair_forward(const float* params, int32_t batch, int32_t h
     if (ws_bytes < f.bytes) return BGS_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
     (void)hipGetLastError();
-    forward(s, batch, height, width, params, rgb, z, hole, f, false);
-    const int64_t np = (int64_t)batch * height * width;
-    hipLaunchKernelGGL(k_output, dim3(blocks(np)), dim3(256), 0, s, rgb, hole, (const float*)f.r, batch,
-                       height * width, rgb_out, err_out);
+    forward(s, batch, height, width, params, rgb, z, hole, f, false, rgb_out, err_out);
     return launched();
 }
 
