@@ -614,6 +614,27 @@ __device__ __forceinline__ uint32_t bin_stage(const BinArgs& a, int64_t p0, int 
     return total;
 }
 
+// The band of surfel j of the stage.
+__device__ __forceinline__ BandRows stage_band(const BinStage& s, int j) {
+    BandRows br;
+    br.k0 = s.k0[j];
+    br.k16 = s.k16[j];
+    br.r = s.r[j];
+    br.inv = s.inv[j];
+    br.vertical = br.inv == 0.0;
+    return br;
+}
+
+// f(cell column, mask) for every entry of surfel j in cell row cr.
+template <typename F>
+__device__ __forceinline__ void surfel_cells(const BinArgs& a, const BinStage& s, int j, int cr, F&& f) {
+    const uint2 rc = s.rect[j];
+    cell_masks(stage_band(s, j), rc.x & 0xFFFF, rc.x >> 16, rc.y & 0xFFFF, rc.y >> 16, cr, [&](int cx, uint64_t m) {
+        if (a.mask.cells) m &= a.mask.cells[(uint32_t)(cr * a.cells_x + cx)];
+        if (m) f(cx, m);
+    });
+}
+
 // f(surfel of the stage, cell, mask) for every entry of item `it`.
 template <typename F>
 __device__ __forceinline__ void bin_item(const BinArgs& a, const BinStage& s, uint32_t it, F&& f) {
@@ -623,24 +644,12 @@ __device__ __forceinline__ void bin_item(const BinArgs& a, const BinStage& s, ui
         if (s.item[mid] <= it) lo = mid;
         else hi = mid - 1;
     }
-    BandRows br;
-    br.k0 = s.k0[lo];
-    br.k16 = s.k16[lo];
-    br.r = s.r[lo];
-    br.inv = s.inv[lo];
-    br.vertical = br.inv == 0.0;
-    const uint2 rc = s.rect[lo];
-    const int tx0 = rc.x & 0xFFFF, ty0 = rc.x >> 16, tx1 = rc.y & 0xFFFF, ty1 = rc.y >> 16;
-    const int cr = (ty0 >> 3) + (int)(it - s.item[lo]);
-    cell_masks(br, tx0, ty0, tx1, ty1, cr, [&](int cx, uint64_t m) {
-        const uint32_t cell = (uint32_t)(cr * a.cells_x + cx);
-        if (a.mask.cells) m &= a.mask.cells[cell];
-        if (m) f(lo, cell, m);
-    });
+    const int cr = (int)(s.rect[lo].x >> 19) + (int)(it - s.item[lo]);
+    surfel_cells(a, s, lo, cr, [&](int cx, uint64_t m) { f(lo, (uint32_t)(cr * a.cells_x + cx), m); });
 }
 
 // Entries per (cell, chunk of the order), and the keys and entries of each
-// chunk.  One workgroup per chunk.
+// chunk (k_bin_scan makes the keys a running sum).  One workgroup per chunk.
 __global__ __launch_bounds__(256) void k_bin_count(BinArgs a) {
     extern __shared__ uint32_t s_cnt[];  // a.n_cells words
     __shared__ BinStage s;
@@ -685,23 +694,32 @@ __device__ __forceinline__ void bin_status(const BinArgs& a, DevStatus* st, int 
 }
 
 // Block c < n_cells: exclusive scan of the cell's row of the matrix over the
-// chunks, in place, and the cell's total.  The last block: the key count of
-// the pass into the status block.
+// chunks, in place, and the cell's total.  The last block: the chunks' keys
+// as an inclusive running sum, and the pass's key count into the status
+// block.
 __global__ __launch_bounds__(256) void k_bin_scan(BinArgs a, DevStatus* st, int which) {
     __shared__ uint32_t w4[4];
     const int t = threadIdx.x;
     constexpr int kPer = kBinMaxChunks / 256;
     uint32_t total;
+    const uint32_t per = (a.chunks + 255) / 256, c0 = t * per;
+    uint32_t v[kPer], sum = 0;
     if (blockIdx.x == a.n_cells) {
-        uint32_t k = 0;
-        for (uint32_t c = t; c < a.chunks; c += 256) k += a.kpart[c].x;
-        (void)block_scan_256(k, w4, &total);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            v[j] = ((uint32_t)j < per && c0 + j < a.chunks) ? a.kpart[c0 + j].x : 0u;
+            sum += v[j];
+        }
+        uint32_t run = block_scan_256(sum, w4, &total);
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            run += v[j];
+            if ((uint32_t)j < per && c0 + j < a.chunks) a.kpart[c0 + j].x = run;
+        }
         if (t == 0) bin_status(a, st, which, total);
         return;
     }
     uint32_t* row = a.matrix + (size_t)blockIdx.x * a.chunks;
-    const uint32_t per = (a.chunks + 255) / 256, c0 = t * per;
-    uint32_t v[kPer], sum = 0;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         v[j] = ((uint32_t)j < per && c0 + j < a.chunks) ? row[c0 + j] : 0u;
@@ -720,9 +738,11 @@ __global__ __launch_bounds__(256) void k_bin_scan(BinArgs a, DevStatus* st, int 
 // time, a bitmap per cell of the surfels that have an entry there, from
 // which an entry's rank follows, so that a cell's entries keep the
 // compositing order without a sort.  The first workgroup also writes the
-// cells' first entries and first expansion chunks.  Entries past the
-// capacity are dropped (the key count then exceeds it too, and the pass
-// reports the overflow).  kScan: a small count table is read whole by every
+// cells' first entries and first expansion chunks.  A pass with more keys
+// than the capacity reports the overflow and keeps the first of them, in
+// compositing order and within a surfel in row order of its tiles: the
+// masks of the entries past it lose their bits.  (Entries past the capacity
+// are dropped.)  kScan: a small count table is read whole by every
 // workgroup, which takes what it needs of k_bin_scan's sums itself, so that
 // small frames save that launch.
 template <bool kScan>
@@ -732,25 +752,21 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
     __shared__ uint64_t s_mask[kBinKeep];
     __shared__ uint32_t s_at[kBinKeep];  // cell << 8 | surfel of the stage
     __shared__ uint32_t s_n;
+    __shared__ uint32_t s_kpos[257];  // past the capacity: the surfels' first keys
     uint32_t* s_base = s_dyn;              // n_cells
     uint32_t* s_bits = s_dyn + a.n_cells;  // min(n_cells, kBinWin) x 8 words
     const int t = threadIdx.x;
     if (blockIdx.x != 0 && a.kpart[blockIdx.x].y == 0) return;
     // ctot[c]: the entries of cell c; pre(c): those of earlier chunks.
     const uint32_t* ctot = a.ctot;
+    uint32_t key0 = 0, key1;  // the chunk's keys, counted through the order
     if (kScan) {
-        if (blockIdx.x == 0) {
-            uint32_t k = 0, total;
-            for (uint32_t c = t; c < a.chunks; c += 256) k += a.kpart[c].x;
-            (void)block_scan_256(k, s.wsum, &total);
-            if (t == 0) bin_status(a, st, which, total);
-        }
         uint32_t* s_tot = s_dyn + a.n_cells;  // the bitmap's words, not in use yet
-        for (uint32_t c = t >> 6; c < a.n_cells; c += 4) {
+        for (uint32_t c = t >> 6; c <= a.n_cells; c += 4) {  // the last: the chunks' keys
             const uint32_t* row = a.matrix + (size_t)c * a.chunks;
             uint32_t pre = 0, tot = 0;
             for (uint32_t q = t & 63; q < a.chunks; q += 64) {
-                const uint32_t v = row[q];
+                const uint32_t v = c < a.n_cells ? row[q] : a.kpart[q].x;
                 pre += q < blockIdx.x ? v : 0u;
                 tot += v;
             }
@@ -759,14 +775,24 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
                 pre += (uint32_t)__shfl_xor((int)pre, off, 64);
                 tot += (uint32_t)__shfl_xor((int)tot, off, 64);
             }
-            if ((t & 63) == 0) {
+            if ((t & 63) == 0 && c < a.n_cells) {
                 s_base[c] = pre;
                 s_tot[c] = tot;
+            } else if ((t & 63) == 0) {
+                s_kpos[0] = pre;
+                s_kpos[1] = tot;
             }
         }
         __syncthreads();
         ctot = s_tot;
+        key0 = s_kpos[0];
+        key1 = key0 + a.kpart[blockIdx.x].x;
+        if (blockIdx.x == 0 && t == 0) bin_status(a, st, which, s_kpos[1]);
+    } else {
+        if (blockIdx.x != 0) key0 = a.kpart[blockIdx.x - 1].x;
+        key1 = a.kpart[blockIdx.x].x;
     }
+    const bool over = key1 > a.cap;  // uniform; so is key0
     {
         const uint32_t per = (a.n_cells + 255) / 256, c0 = min(a.n_cells, t * per), c1 = min(a.n_cells, c0 + per);
         uint32_t sum = 0, total;
@@ -805,6 +831,18 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
         __syncthreads();
         const uint32_t items = bin_stage<false>(a, p, (int)min((int64_t)256, p1 - p), s);
         if (items == 0) continue;  // uniform
+        if (over) {
+            s_kpos[t] = 0u;
+            __syncthreads();
+            for (uint32_t it = t; it < items; it += 256)
+                bin_item(a, s, it, [&](int j, uint32_t, uint64_t m) { atomicAdd(&s_kpos[j], (uint32_t)__popcll(m)); });
+            __syncthreads();
+            uint32_t total;
+            const uint32_t first = key0 + block_scan_256(s_kpos[t], s.wsum, &total);
+            s_kpos[t] = first;
+            key0 += total;
+            if (t == 0) s_kpos[256] = key0;
+        }
         for (uint32_t w0 = 0; w0 < a.n_cells; w0 += kBinWin) {
             const uint32_t nw = min((uint32_t)kBinWin, a.n_cells - w0);
             for (uint32_t i = t; i < 8 * nw; i += 256) s_bits[i] = 0u;
@@ -825,6 +863,7 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
                 const uint32_t* b = s_bits + 8 * (cell - w0);
                 uint32_t pos = s_base[cell] + (uint32_t)__popc(b[j >> 5] & ((1u << (j & 31)) - 1u));
                 for (int q = 0; q < (j >> 5); ++q) pos += (uint32_t)__popc(b[q]);
+                if (over && s_kpos[j] >= a.cap) m = 0ull;
                 if (pos < a.cap) {
                     a.emask[pos] = m;
                     a.eid[pos] = s.id[j];
@@ -840,6 +879,39 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
                     });
             }
             __syncthreads();
+            if (over) {  // the surfel that the capacity cuts, if it is staged
+                if (t == 0) s_n = 256u;
+                __syncthreads();
+                if (s_kpos[t] < a.cap && s_kpos[t + 1] > a.cap) s_n = (uint32_t)t;
+                __syncthreads();
+                const int j = (int)s_n;
+                uint32_t room = j < 256 ? a.cap - s_kpos[j] : 0u;
+                for (int cr = (int)(s.rect[j & 255].x >> 19); j < 256 && cr <= (int)(s.rect[j].y >> 19); ++cr) {
+                    // A row of its cells (at most 128: sides <= 16384 px), a thread each.
+                    __syncthreads();
+                    if (t < a.cells_x) s_mask[t] = 0ull;
+                    __syncthreads();
+                    if (t == 0) surfel_cells(a, s, j, cr, [&](int cx, uint64_t m) { s_mask[cx] = m; });
+                    __syncthreads();
+                    const uint64_t m = t < a.cells_x ? s_mask[t] : 0ull;
+                    uint64_t kept = 0;
+                    for (int y = 0; y < 8; ++y) {
+                        uint32_t left = 0, row = 0;  // keys of this tile row: in the cells before, and all
+                        for (int c = 0; c < a.cells_x; ++c) {
+                            const uint32_t k = (uint32_t)__popc((uint32_t)(s_mask[c] >> (8 * y)) & 255u);
+                            row += k;
+                            left += c < t ? k : 0u;
+                        }
+                        uint32_t bits = (uint32_t)(m >> (8 * y)) & 255u;
+                        for (; bits && left < room; bits &= bits - 1u, ++left)
+                            kept |= (uint64_t)(bits & (0u - bits)) << (8 * y);
+                        room -= min(room, row);
+                    }
+                    const uint32_t cell = (uint32_t)(cr * a.cells_x + t);
+                    if (m && cell - w0 < nw) place(j, cell, kept);
+                }
+                __syncthreads();
+            }
             if (p + 256 < p1)
                 for (uint32_t c = t; c < nw; c += 256) {
                     uint32_t k = 0;
