@@ -73,7 +73,7 @@ inline size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // is whatever the remaining bytes hold.
 struct Layout {
     size_t status;
-    size_t zbuf, hole, hole2, bcount, rmask, bbox, pflag, pbox, wpart, gpart;
+    size_t zbuf, hole, hole2, bcount, rmask, pflag, pbox, wpart, gpart;
     size_t ranges, torder, cmask, ctot, cstart, cpre, ttot;
     size_t xrgb;  // view-colour transfer: the dominant pass's affiliated-view colours [3][H][W]
     size_t recs, zkeys, rects, dkeys_b, dvals_a, dvals_b, band, mu, matrix, kpart;
@@ -106,10 +106,8 @@ Layout make_layout(int64_t n, int64_t W, int64_t H, int64_t kc) {
     L.zbuf = take(8 * np);
     L.hole = take(np);
     L.hole2 = take(np);
-    const int64_t nb = (np + 255) / 256;  // 256-pixel blocks of the component labelling
-    L.bcount = take(4 * (nb + 1));
-    L.rmask = take(32 * nb);
-    L.bbox = take(16 * np);  // 8 words per component; at most np / 2 components
+    L.bcount = take(4 * ((np + 1023) / 1024 + 1));  // component roots per 1024 pixels, and their number
+    L.rmask = take(8 * ((np + 63) / 64));
     L.pflag = take(np);
     L.pbox = take(16 * np);
     L.wpart = take(16 * H);                                   // one per row
@@ -759,7 +757,7 @@ int32_t bgs_classify_holes(bgs_ctx* ctx, const bgs_camera* src, const bgs_camera
     const Layout L = make_layout(0, dst->width, dst->height, 0);
     if (L.total > ws_bytes) return fail(ctx, BGS_ERR_WORKSPACE, "workspace of %zu bytes is too small", ws_bytes);
     ClassifyBufs b{at<uint8_t>(ws, L.hole), at<uint8_t>(ws, L.hole2), at<uint32_t>(ws, L.bcount),
-                   at<uint32_t>(ws, L.rmask), at<int32_t>(ws, L.bbox), at<uint8_t>(ws, L.pflag),
+                   at<unsigned long long>(ws, L.rmask), at<uint8_t>(ws, L.pflag),
                    at<int4>(ws, L.pbox), at<uint4>(ws, L.wpart), at<uint2>(ws, L.gpart)};
     HIP_CHECK(launch_classify(make_warpcam(*src), make_warpcam(*dst), rel_pose(*src, *dst), *roi, raster->bg,
                               depth_range, rgb_dst, z_dst, alpha_dst, cls, labels, boxes, box_capacity, n_boxes,
@@ -847,7 +845,7 @@ int32_t bgs_render_stereo(bgs_ctx* ctx, const bgs_scene* scene, const bgs_camera
     mark(ctx, BGS_STAGE_REPROJECT, 1);
     // Stage 3: hole classification and interpolation.
     ClassifyBufs b{at<uint8_t>(ws, L.hole), at<uint8_t>(ws, L.hole2), at<uint32_t>(ws, L.bcount),
-                   at<uint32_t>(ws, L.rmask), at<int32_t>(ws, L.bbox), at<uint8_t>(ws, L.pflag),
+                   at<unsigned long long>(ws, L.rmask), at<uint8_t>(ws, L.pflag),
                    at<int4>(ws, L.pbox), at<uint4>(ws, L.wpart), at<uint2>(ws, L.gpart)};
     mark(ctx, BGS_STAGE_CLASSIFY, 0);
     HIP_CHECK(launch_classify(wd, wa, P, *roi, raster->bg, nullptr, rgb_aff, z_aff, alpha_aff, cls_aff, labels, boxes,
@@ -956,7 +954,7 @@ int batch_issue(bgs_ctx* ctx, int32_t n, const bgs_batch_pair* pairs, const bgs_
                                    false, at<uint4>(ws, L.wpart), st, s),
                   "reproject");
         ClassifyBufs b{at<uint8_t>(ws, L.hole), at<uint8_t>(ws, L.hole2), at<uint32_t>(ws, L.bcount),
-                       at<uint32_t>(ws, L.rmask), at<int32_t>(ws, L.bbox), at<uint8_t>(ws, L.pflag),
+                       at<unsigned long long>(ws, L.rmask), at<uint8_t>(ws, L.pflag),
                        at<int4>(ws, L.pbox), at<uint4>(ws, L.wpart), at<uint2>(ws, L.gpart)};
         HIP_CHECK(launch_classify(wd, wa, P, q.roi, raster->bg, nullptr, q.rgb_aff, q.z_aff, q.alpha_aff, q.cls_aff,
                                   q.labels, q.boxes, q.box_capacity, q.n_boxes, q.tile_mask, b, st, s),

@@ -78,7 +78,7 @@ struct BinArgs {
     uint4* band;       // per position of the order: rect, band direction and interval (empty rect: no entries)
     float2* mu;        // and the projected centre
     uint32_t* matrix;  // [n_cells][chunks] entries, then their exclusive scan over the chunks
-    uint2* kpart;      // per chunk: keys, entries
+    uint2* kpart;      // per chunk: keys (then their running sum), entries
     uint32_t* ctot;    // per cell: entries
     uint32_t* cstart;  // n_cells + 1: first entry
     uint32_t* cpre;    // n_cells + 1: first expansion chunk (kBinChunk entries each)
@@ -281,11 +281,10 @@ hipError_t launch_reproject(const WarpCam& src, const WarpCam& dst, const RelPos
 struct ClassifyBufs {
     uint8_t* hole;     // interpolation tags
     uint8_t* hole2;    // center-hole mask
-    uint32_t* bcount;  // component roots per 256-pixel block, then their exclusive scan
-    uint32_t* rmask;   // per 256-pixel block: bit mask of its component roots (8 words)
-    int32_t* bbox;     // per component: box (4) and root pixel (1), 8 words
-    uint8_t* pflag;    // block-local piece roots
-    int4* pbox;        // piece boxes, indexed by root pixel
+    uint32_t* bcount;  // component roots per 1024-pixel block, then their exclusive scan
+    unsigned long long* rmask;  // per 64 pixels: bit mask of the component roots
+    uint8_t* pflag;    // tile-local piece roots
+    int4* pbox;        // piece boxes, indexed by root pixel; then the component's at its root
     uint4* wpart;      // reprojection partials (warp_parts entries)
     uint2* gpart;      // gap-fill partials, one per gap-fill block
 };

@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void k_fill_u64(unsigned long long* p, int64_t
 // fixed-order fp64 recipe of Eq. 4-5.  Returns false when it lands nowhere;
 // *df gets the fp32 depth proxy of a covered source pixel (else stays
 // untouched).
-__device__ inline bool splat_target_v(const WarpCam& src, const WarpCam& dst, const RelPose& P, float a_min, float A,
+__device__ inline bool splat_target(const WarpCam& src, const WarpCam& dst, const RelPose& P, float a_min, float A,
                                       float Dr, int i, int j, int64_t* fu_out, int64_t* fv_out,
                                       unsigned long long* key, float* df_out) {
     const int64_t s = (int64_t)j * src.W + i;
@@ -157,12 +157,6 @@ __device__ inline bool splat_target_v(const WarpCam& src, const WarpCam& dst, co
     *key = ((unsigned long long)__float_as_uint(zf) << 32) | (unsigned long long)(uint32_t)s;
     return true;
 }
-__device__ inline bool splat_target(const WarpCam& src, const WarpCam& dst, const RelPose& P, float a_min,
-                                    const float* __restrict__ draw, const float* __restrict__ alpha, int i, int j,
-                                    int64_t* fu_out, int64_t* fv_out, unsigned long long* key, float* df_out) {
-    const int64_t s = (int64_t)j * src.W + i;
-    return splat_target_v(src, dst, P, a_min, alpha[s], draw[s], i, j, fu_out, fv_out, key, df_out);
-}
 
 // Forward splat of every source pixel into the destination z-buffer.
 __global__ __launch_bounds__(256) void k_reproject_scatter(WarpCam src, WarpCam dst, RelPose P, float a_min,
@@ -172,13 +166,24 @@ __global__ __launch_bounds__(256) void k_reproject_scatter(WarpCam src, WarpCam 
     __shared__ uint32_t s4[4];
     const int i = blockIdx.x * 64 + (threadIdx.x & 63);
     uint32_t dmin = 0xFFFFFFFFu, dmax = 0u;
-    for (int r = threadIdx.x >> 6; r < kBandRows; r += 4) {
-        const int j = blockIdx.y * kBandRows + r;
+    // All of the thread's pixels are loaded first, so none waits on another.
+    constexpr int kP = kBandRows / 4;
+    float Av[kP], Dv[kP];
+#pragma unroll
+    for (int q = 0; q < kP; ++q) {
+        const int j = blockIdx.y * kBandRows + (threadIdx.x >> 6) + 4 * q;
+        const bool in = i < src.W && j < src.H;
+        Av[q] = in ? alpha[(int64_t)j * src.W + i] : 0.f;
+        Dv[q] = in ? draw[(int64_t)j * src.W + i] : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < kP; ++q) {
+        const int j = blockIdx.y * kBandRows + (threadIdx.x >> 6) + 4 * q;
         if (i >= src.W || j >= src.H) continue;
         int64_t fu, fv;
         unsigned long long key;
         float df = -1.f;
-        const bool hit = splat_target(src, dst, P, a_min, draw, alpha, i, j, &fu, &fv, &key, &df);
+        const bool hit = splat_target(src, dst, P, a_min, Av[q], Dv[q], i, j, &fu, &fv, &key, &df);
         if (df >= 0.f) {
             dmin = min(dmin, __float_as_uint(df));
             dmax = max(dmax, __float_as_uint(df));
@@ -191,30 +196,6 @@ __global__ __launch_bounds__(256) void k_reproject_scatter(WarpCam src, WarpCam 
         if (dmin != 0xFFFFFFFFu) atomicMax(&st->dmin_inv, ~dmin);
         if (dmax != 0u) atomicMax(&st->dmax_bits, dmax);
     }
-}
-
-// Resolve one destination pixel t from its z-buffer key.
-__device__ inline uint32_t resolve_pixel(unsigned long long key, int64_t t, int64_t nd, int64_t ns,
-                                         const float* __restrict__ rgb, const float* __restrict__ alpha,
-                                         float* __restrict__ rgb_dst, float* __restrict__ z_dst,
-                                         float* __restrict__ a_dst, uint8_t* __restrict__ hole) {
-    if (key == ~0ull) {
-        rgb_dst[t] = 0.f;
-        rgb_dst[nd + t] = 0.f;
-        rgb_dst[2 * nd + t] = 0.f;
-        z_dst[t] = INFINITY;
-        a_dst[t] = 0.f;
-        hole[t] = 1;
-        return 1;
-    }
-    const uint32_t s = (uint32_t)(key & 0xFFFFFFFFull);
-    rgb_dst[t] = rgb[s];
-    rgb_dst[nd + t] = rgb[ns + s];
-    rgb_dst[2 * nd + t] = rgb[2 * ns + s];
-    z_dst[t] = __uint_as_float((uint32_t)(key >> 32));
-    a_dst[t] = alpha[s];
-    hole[t] = 0;
-    return 0;
 }
 
 // Row-preserving form (the host has proven that every splat stays on its
@@ -274,7 +255,7 @@ __global__ __launch_bounds__(NT) void k_reproject_rows(WarpCam src, WarpCam dst,
             int64_t fu, fv;
             unsigned long long key;
             float df = -1.f;
-            const bool hit = splat_target_v(src, dst, P, a_min, Av[k], Dv[k], i, j, &fu, &fv, &key, &df);
+            const bool hit = splat_target(src, dst, P, a_min, Av[k], Dv[k], i, j, &fu, &fv, &key, &df);
             if (df >= 0.f) {
                 dmin = min(dmin, __float_as_uint(df));
                 dmax = max(dmax, __float_as_uint(df));
@@ -411,10 +392,36 @@ __global__ __launch_bounds__(256) void k_reproject_resolve(int64_t nd, int64_t n
                                                            float* __restrict__ a_dst, uint8_t* __restrict__ hole,
                                                            DevStatus* st) {
     __shared__ uint32_t s4[4];
+    // Four pixels per thread, the keys loaded together and then the source
+    // pixels they name: two memory latencies per block, not two per pixel.
+    const int64_t t0 = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+    unsigned long long key[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) key[q] = t0 + 256 * q < nd ? zbuf[t0 + 256 * q] : ~0ull;
+    float c0[4], c1[4], c2[4], a[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bool have = key[q] != ~0ull;
+        const uint32_t s = (uint32_t)(key[q] & 0xFFFFFFFFull);
+        c0[q] = have ? rgb[s] : 0.f;
+        c1[q] = have ? rgb[ns + s] : 0.f;
+        c2[q] = have ? rgb[2 * ns + s] : 0.f;
+        a[q] = have ? alpha[s] : 0.f;
+    }
     uint32_t h = 0;
-    for (int64_t t = (int64_t)blockIdx.x * 1024 + threadIdx.x, e = min(nd, (int64_t)blockIdx.x * 1024 + 1024); t < e;
-         t += 256)
-        h += resolve_pixel(zbuf[t], t, nd, ns, rgb, alpha, rgb_dst, z_dst, a_dst, hole);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int64_t t = t0 + 256 * q;
+        if (t >= nd) continue;
+        const bool have = key[q] != ~0ull;
+        rgb_dst[t] = c0[q];
+        rgb_dst[nd + t] = c1[q];
+        rgb_dst[2 * nd + t] = c2[q];
+        z_dst[t] = have ? __uint_as_float((uint32_t)(key[q] >> 32)) : INFINITY;
+        a_dst[t] = a[q];
+        hole[t] = have ? 0 : 1;
+        h += have ? 0u : 1u;
+    }
     h = block_sum_u32(h, s4);
     if (threadIdx.x == 0 && h) atomicAdd(&st->n_holes, h);
 }
@@ -793,44 +800,56 @@ __global__ __launch_bounds__(256) void k_gap_fill(int W, int H, int passes, floa
             tm[(int64_t)ty * tiles_x + tx] = eb.overlaps(tx * T, ty * T, T) ? 1 : 0;
         }
     }
-    {
-        // Holes are sparse: a tile without one has nothing to fill and no
-        // center pixel, and needs none of its neighbours' values.  (The
-        // loads are issued together: unrolled, none waits on another.)
-        const int cx = bx * 64 + (threadIdx.x & 63);
-        uint8_t hv[kBandRows / 4];
-#pragma unroll
-        for (int q = 0; q < kBandRows / 4; ++q) {
-            const int cy = by * kBandRows + (threadIdx.x >> 6) + 4 * q;
-            hv[q] = (cx < W && cy < H) ? cls[(int64_t)cy * W + cx] : 0;
-        }
-        bool any = false;
-#pragma unroll
-        for (int q = 0; q < kBandRows / 4; ++q) any = any || hv[q] != 0;
-        if (!__syncthreads_or(any)) {
-            for (int r = threadIdx.x >> 6; r < kBandRows; r += 4) {
-                const int cy = by * kBandRows + r;
-                if (cx < W && cy < H) {
-                    tag_out[(int64_t)cy * W + cx] = 0;
-                    center[(int64_t)cy * W + cx] = 0;
-                }
-            }
-            if (threadIdx.x == 0) gpart[gb] = make_uint2(0u, 0u);
-            return;
-        }
-    }
-    // The tile and its halo: all loads first (unrolled, so none waits on
-    // another), then the LDS stores.
+    // The classes of the tile and its halo first.  Holes are sparse: without
+    // an open one in the tile (a hole outside the edge ROIs), or without any
+    // filled pixel around them, no pass changes the tile and the images are
+    // not read (2064x2208: 60 -> 55 us).
     constexpr int kLoads = (RW * RH + 255) / 256;
-    float lc0[kLoads], lc1[kLoads], lc2[kLoads], la[kLoads], lz[kLoads];
     uint8_t lh[kLoads];
 #pragma unroll
     for (int q = 0; q < kLoads; ++q) {
         const int i = threadIdx.x + 256 * q;
         const int lx = i % RW, ly = i / RW, x = x0 + lx, y = y0 + ly;
         const bool ok = i < RW * RH && x >= 0 && y >= 0 && x < W && y < H;
+        lh[q] = !ok ? kTagOut : cls[(int64_t)y * W + x] ? 255 : 0;
+    }
+    bool open = false, full = false;
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+        const int i = threadIdx.x + 256 * q;
+        if (i >= RW * RH) continue;
+        const int lx = i % RW, ly = i / RW, x = x0 + lx, y = y0 + ly;
+        const uint8_t t = lh[q] == 255 && eb.contains(x, y) ? kTagEdge : lh[q];
+        s_tag[i] = t;
+        full = full || t == 0;
+        open = open || (t == 255 && lx >= kH && lx < kH + 64 && ly >= kH && ly < kH + kBandRows);
+    }
+    const bool any_open = __syncthreads_or(open), any_full = __syncthreads_or(full);
+    if (!any_open || !any_full) {
+        uint32_t centers = 0;
+        for (int i = threadIdx.x; i < 64 * kBandRows; i += 256) {
+            const int lx = kH + (i & 63), ly = kH + (i >> 6), x = x0 + lx, y = y0 + ly;
+            if (x >= W || y >= H) continue;
+            const int64_t p = (int64_t)y * W + x;
+            const uint8_t t = s_tag[ly * RW + lx];
+            tag_out[p] = t >= kTagEdge ? 255 : t;
+            const uint32_t c = t == 255 ? 1u : 0u;
+            center[p] = (uint8_t)c;
+            centers += c;
+        }
+        if (any_open) centers = block_sum_u32(centers, s4);
+        if (threadIdx.x == 0) gpart[gb] = make_uint2(0u, centers);
+        return;
+    }
+    // The images' values there: all loads first (unrolled, so none waits on
+    // another), then the LDS stores.
+    float lc0[kLoads], lc1[kLoads], lc2[kLoads], la[kLoads], lz[kLoads];
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+        const int i = threadIdx.x + 256 * q;
+        const int lx = i % RW, ly = i / RW, x = x0 + lx, y = y0 + ly;
+        const bool ok = lh[q] == 0;
         const int64_t p = ok ? (int64_t)y * W + x : 0;
-        lh[q] = ok ? cls[p] : 0;
         lc0[q] = ok ? rgb[p] : 0.f;
         lc1[q] = ok ? rgb[n + p] : 0.f;
         lc2[q] = ok ? rgb[2 * n + p] : 0.f;
@@ -841,12 +860,6 @@ __global__ __launch_bounds__(256) void k_gap_fill(int W, int H, int passes, floa
     for (int q = 0; q < kLoads; ++q) {
         const int i = threadIdx.x + 256 * q;
         if (i >= RW * RH) continue;
-        const int lx = i % RW, ly = i / RW, x = x0 + lx, y = y0 + ly;
-        if (x < 0 || y < 0 || x >= W || y >= H) {
-            s_tag[i] = kTagOut;
-            continue;
-        }
-        s_tag[i] = lh[q] == 0 ? 0 : eb.contains(x, y) ? kTagEdge : 255;
         s_c[0][i] = lc0[q];
         s_c[1][i] = lc1[q];
         s_c[2][i] = lc2[q];
@@ -1036,29 +1049,66 @@ __global__ __launch_bounds__(256) void k_row_fill(int W, int H, const uint8_t* _
 }
 
 // ---------------------------------------------------------------------------
-// Connected components: block-local union-find in LDS over 16x16 pixel
-// blocks, then unions across block borders with global atomicMin, then
-// flattening.  Links always go from the larger to the smaller index, so the
-// root of every component is its smallest linear index.
+// Connected components: union-find in LDS over tiles of 64x16 pixels, then
+// unions across tile borders with global atomicMin, then flattening.  Links
+// always go from the larger to the smaller index, so the root of every
+// component is its smallest linear index.
+//
+// The unions, each a chain of dependent reads and an atomic, are what these
+// kernels wait for, so they are few: a wave holds a row's 64 pixels as the
+// bits of one word, the nodes of a tile are its rows' runs of set pixels,
+// and the words say where two adjacent runs first touch.  (A union per
+// pixel and neighbour, over 16x16 tiles: 2064x2208 with 16 components, tiles
+// 26 -> 16 us, borders 126 -> 15; 1603x1061, 20 -> 9 and 21 -> 8.)
 // ---------------------------------------------------------------------------
+constexpr int kCclRows = 16;  // rows per tile (64 columns)
+
+// First bit of the run of set bits that holds bit x of w.
+__device__ inline int run_start(unsigned long long w, int x) {
+    const unsigned long long zeros = ~w & ((1ull << x) - 1ull);
+    return zeros ? 64 - __clzll((long long)zeros) : 0;
+}
+
+// Where pixels of a row are joined to the row above, one pair of touching
+// runs at a time: vertically where the overlap of two runs begins, and, with
+// 8 neighbours, diagonally where two runs touch at a corner only (were the
+// pixel above or the pixel beside set as well, the runs overlap there).
+// The neighbours left and right of the word come in with cl, cr, ul, ur.
+struct RowLinks {
+    unsigned long long vert, left, right;  // to the pixel above; above left; above right
+    __device__ RowLinks(unsigned long long cur, unsigned long long up, int conn, unsigned long long cl = 0,
+                        unsigned long long cr = 0, unsigned long long ul = 0, unsigned long long ur = 0) {
+        const unsigned long long o = cur & up;
+        vert = o & ~(o << 1);
+        left = conn == 8 ? cur & ((up << 1) | ul) & ~up & ~((cur << 1) | cl) : 0ull;
+        right = conn == 8 ? cur & ((up >> 1) | (ur << 63)) & ~up & ~((cur >> 1) | (cr << 63)) : 0ull;
+    }
+};
+
 __device__ inline int find_root_lds(int* L, int x) {
-    int p = __atomic_load_n(&L[x], __ATOMIC_RELAXED);
+    int p = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     while (p != x) {
         x = p;
-        p = __atomic_load_n(&L[x], __ATOMIC_RELAXED);
+        p = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     return x;
 }
 
-__device__ inline int find_root_g(int* L, int x) {
-    int p = __atomic_load_n(&L[x], __ATOMIC_RELAXED);
+// In global memory.  Parents only ever get smaller and every value a node
+// has had is an ancestor of it, so a read that another XCD's unions have
+// overtaken still leads towards the root: it may come out of this XCD's
+// cache.
+__device__ inline int find_root_g(const int* L, int x) {
+    int p = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     while (p != x) {
         x = p;
-        p = __atomic_load_n(&L[x], __ATOMIC_RELAXED);
+        p = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     return x;
 }
 
+// Ends whatever the finds read: the atomic returns the current parent, and
+// the larger index strictly falls from round to round.
 __device__ inline void unite_g(int* L, int a, int b) {
     while (true) {
         a = find_root_g(L, a);
@@ -1091,91 +1141,130 @@ __device__ inline void unite_lds(int* L, int a, int b) {
     }
 }
 
-// Block-local labelling of a 16x16 pixel block.  With pflag/pbox given, it
-// also records every block-local piece (its root pixel gets pflag = 1 and
-// the piece's half-open bounding box in pbox), so that component boxes can
-// be formed from pieces instead of pixels.
+// Tile-local labelling.  With pflag/pbox given, it also records every
+// tile-local piece (its root pixel gets pflag = 1 and the piece's half-open
+// bounding box in pbox), so that component boxes can be formed from pieces
+// instead of pixels.
 __global__ __launch_bounds__(256) void k_ccl_local(int W, int H, int conn, const uint8_t* __restrict__ mask,
                                                    int* __restrict__ labels, uint8_t* __restrict__ pflag,
                                                    int4* __restrict__ pbox) {
-    __shared__ int L[256];
-    __shared__ uint8_t m[256];
-    __shared__ int bx0[256], by0[256], bx1[256], by1[256];
-    const int lx = threadIdx.x & 15, ly = threadIdx.x >> 4;
-    const int x = blockIdx.x * 16 + lx, y = blockIdx.y * 16 + ly;
-    const bool in = x < W && y < H;
-    const int li = threadIdx.x;
-    const bool set = in && mask[(int64_t)y * W + x];
-    if (!__syncthreads_or(set)) {  // an empty block (the usual case for a sparse mask)
-        if (in) {
-            labels[(int64_t)y * W + x] = -1;
-            if (pflag) pflag[(int64_t)y * W + x] = 0;
-        }
+    constexpr int kR = kCclRows / 4;  // rows per wave
+    __shared__ unsigned long long s_row[kCclRows];
+    __shared__ int L[64 * kCclRows];  // parents of run starts
+    __shared__ int bx0[64 * kCclRows], bx1[64 * kCclRows], by1[64 * kCclRows];
+    const int lane = threadIdx.x & 63, row0 = (threadIdx.x >> 6) * kR;
+    const int x = blockIdx.x * 64 + lane, y = blockIdx.y * kCclRows + row0;
+    const int64_t g0 = (int64_t)y * W + x;
+    bool set[kR];
+#pragma unroll
+    for (int q = 0; q < kR; ++q) set[q] = x < W && y + q < H && mask[g0 + (int64_t)q * W];
+    unsigned long long w[kR], any = 0;
+#pragma unroll
+    for (int q = 0; q < kR; ++q) {
+        w[q] = __ballot(set[q]);
+        any |= w[q];
+        if (lane == 0) s_row[row0 + q] = w[q];
+    }
+    if (!__syncthreads_or(any != 0)) {  // an empty tile (the usual case for a sparse mask)
+#pragma unroll
+        for (int q = 0; q < kR; ++q)
+            if (x < W && y + q < H) {
+                labels[g0 + (int64_t)q * W] = -1;
+                if (pflag) pflag[g0 + (int64_t)q * W] = 0;
+            }
         return;
     }
-    m[li] = set ? 1 : 0;
-    L[li] = li;
-    bx0[li] = INT_MAX;
-    by0[li] = INT_MAX;
-    bx1[li] = -1;
-    by1[li] = -1;
+#pragma unroll
+    for (int q = 0; q < kR; ++q) {
+        const int li = (row0 + q) * 64 + lane;
+        if (((w[q] & ~(w[q] << 1)) >> lane) & 1) {
+            L[li] = li;
+            bx0[li] = INT_MAX;
+            bx1[li] = -1;
+            by1[li] = -1;
+        }
+    }
     __syncthreads();
-    if (set) {
-        // Backward neighbours inside the block: left, up-left, up, up-right.
-        if (lx > 0 && m[li - 1]) unite_lds(L, li, li - 1);
-        if (ly > 0) {
-            if (m[li - 16]) unite_lds(L, li, li - 16);
-            if (conn == 8) {
-                if (lx > 0 && m[li - 17]) unite_lds(L, li, li - 17);
-                if (lx < 15 && m[li - 15]) unite_lds(L, li, li - 15);
+#pragma unroll
+    for (int q = 0; q < kR; ++q) {
+        const int ly = row0 + q;
+        if (ly == 0) continue;
+        const unsigned long long up = q > 0 ? w[q > 0 ? q - 1 : 0] : s_row[ly - 1];
+        const RowLinks k(w[q], up, conn);
+        if (((k.vert | k.left | k.right) >> lane) & 1) {
+            const int me = ly * 64 + run_start(w[q], lane), above = (ly - 1) * 64;
+            if ((k.vert >> lane) & 1) unite_lds(L, me, above + run_start(up, lane));
+            if ((k.left >> lane) & 1) unite_lds(L, me, above + run_start(up, lane - 1));
+            if ((k.right >> lane) & 1) unite_lds(L, me, above + run_start(up, lane + 1));
+        }
+    }
+    __syncthreads();
+    int root[kR];  // of the run that starts at this lane, then of this lane's run
+#pragma unroll
+    for (int q = 0; q < kR; ++q) {
+        root[q] = -1;
+        if (((w[q] & ~(w[q] << 1)) >> lane) & 1) {
+            root[q] = find_root_lds(L, (row0 + q) * 64 + lane);
+            if (pbox) {
+                const unsigned long long after = ~(w[q] >> lane);
+                const int len = after ? __ffsll((long long)after) - 1 : 64;
+                atomicMin(&bx0[root[q]], lane);
+                atomicMax(&bx1[root[q]], lane + len);
+                atomicMax(&by1[root[q]], row0 + q + 1);
             }
         }
+        root[q] = __shfl(root[q], run_start(w[q], lane), 64);
     }
     __syncthreads();
-    int r = -1;
-    if (set) {
-        r = find_root_lds(L, li);
-        if (pbox) {
-            atomicMin(&bx0[r], x);
-            atomicMin(&by0[r], y);
-            atomicMax(&bx1[r], x + 1);
-            atomicMax(&by1[r], y + 1);
+    const int X = blockIdx.x * 64, Y = blockIdx.y * kCclRows;
+#pragma unroll
+    for (int q = 0; q < kR; ++q) {
+        if (x >= W || y + q >= H) continue;
+        const int64_t g = g0 + (int64_t)q * W;
+        const int li = (row0 + q) * 64 + lane, r = root[q];
+        labels[g] = set[q] ? (Y + (r >> 6)) * W + X + (r & 63) : -1;
+        if (pflag) {
+            const bool is_root = set[q] && r == li;
+            pflag[g] = is_root ? 1 : 0;
+            // The root is the piece's first pixel: its row is the box's first.
+            if (is_root) pbox[g] = make_int4(X + bx0[li], y + q, X + bx1[li], Y + by1[li]);
         }
-    }
-    __syncthreads();
-    if (!in) return;
-    const int64_t g = (int64_t)y * W + x;
-    if (set) {
-        const int rx = blockIdx.x * 16 + (r & 15), ry = blockIdx.y * 16 + (r >> 4);
-        labels[g] = ry * W + rx;
-    } else {
-        labels[g] = -1;
-    }
-    if (pflag) {
-        const bool root = set && r == li;
-        pflag[g] = root ? 1 : 0;
-        if (root) pbox[g] = make_int4(bx0[li], by0[li], bx1[li], by1[li]);
     }
 }
 
-__global__ __launch_bounds__(256) void k_ccl_border(int W, int H, int conn, const uint8_t* __restrict__ mask,
-                                                    int* labels) {
-    const int lx = threadIdx.x & 15, ly = threadIdx.x >> 4;
-    const int x = blockIdx.x * 16 + lx, y = blockIdx.y * 16 + ly;
-    if (x >= W || y >= H) return;
-    if (!(lx == 0 || ly == 0 || lx == 15)) return;
-    const int64_t p = (int64_t)y * W + x;
-    if (!mask[p]) return;
-    const int me = (int)p;
-    // Neighbours in another block (the rest were joined in LDS).
-    if (lx == 0 && x > 0 && mask[p - 1]) unite_g(labels, me, me - 1);
-    if (y > 0) {
-        if (ly == 0 && mask[p - W]) unite_g(labels, me, me - W);
-        if (conn == 8) {
-            if (x > 0 && (lx == 0 || ly == 0) && mask[p - W - 1]) unite_g(labels, me, me - W - 1);
-            if (x + 1 < W && (lx == 15 || ly == 0) && mask[p - W + 1]) unite_g(labels, me, me - W + 1);
-        }
-    }
+// Unions across tile borders: a wave per tile, for the tile's first row
+// against the row above and its first column against the column before,
+// and the corners that its last column shares with the column after.
+// What lies inside one tile is joined already, and each tile leaves to its
+// neighbours what lies between those.
+__global__ __launch_bounds__(256) void k_ccl_border(int W, int H, int conn, int tiles_x, int n_tiles,
+                                                    const uint8_t* __restrict__ mask, int* labels) {
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (t >= n_tiles) return;
+    const int ty = t / tiles_x, X = (t - ty * tiles_x) * 64, Y = ty * kCclRows;
+    // The two rows; and, in lanes k and 32 + k for k <= kCclRows, row
+    // Y - 1 + k of the two columns at the left and at the right border.
+    const int x = X + lane, k = lane & 31, yk = Y - 1 + k, xk = lane < 32 ? X - 1 : X + 63;
+    const int64_t p = (int64_t)Y * W + x, pk = (int64_t)yk * W + xk;
+    const bool on = k <= kCclRows && yk >= 0 && yk < H;
+    const uint8_t vc = x < W ? mask[p] : 0, vu = x < W && Y > 0 ? mask[p - W] : 0;
+    const uint8_t va = on && xk >= 0 && xk < W ? mask[pk] : 0, vb = on && xk + 1 < W ? mask[pk + 1] : 0;
+    const unsigned long long cur = __ballot(vc != 0), up = __ballot(vu != 0);
+    const unsigned long long ca = __ballot(va != 0), cb = __ballot(vb != 0);  // bit k: row Y - 1 + k
+    const RowLinks r(cur, up, conn, (ca >> 1) & 1, (cb >> 33) & 1, ca & 1, (cb >> 32) & 1);
+    if ((r.vert >> lane) & 1) unite_g(labels, (int)p, (int)p - W);
+    if ((r.left >> lane) & 1) unite_g(labels, (int)p, (int)p - W - 1);
+    if ((r.right >> lane) & 1) unite_g(labels, (int)p, (int)p - W + 1);
+    // Columns a | b side by side: joined where both are set, unless both
+    // are set in the tile's row above too; corners where only those touch.
+    const unsigned long long low = (1ull << kCclRows) - 1ull, rows = low << 1, in = low << 2 & rows;
+    const unsigned long long both = ca & cb;
+    const unsigned long long side = both & rows & ~((both << 1) & in);
+    const unsigned long long dl = conn == 8 ? cb & (ca << 1) & ~(cb << 1) & ~ca & in : 0ull;
+    const unsigned long long dr = conn == 8 ? ca & (cb << 1) & ~(ca << 1) & ~cb & (in << 32) : 0ull;
+    if ((side >> lane) & 1) unite_g(labels, (int)pk + 1, (int)pk);
+    if ((dl >> lane) & 1) unite_g(labels, (int)pk + 1, (int)pk - W);
+    if ((dr >> lane) & 1) unite_g(labels, (int)pk, (int)pk - W + 1);
 }
 
 __global__ __launch_bounds__(256) void k_ccl_flatten(int64_t n, int* labels) {
@@ -1189,41 +1278,67 @@ __global__ __launch_bounds__(256) void k_ccl_flatten(int64_t n, int* labels) {
 // ---------------------------------------------------------------------------
 // Center boxes.  Component c (in order of root pixel) gets box slot
 // n_edge + c.  A component's root is its smallest pixel index, so the
-// component roots are the pixels with labels[p] == p; slot_of() ranks a
-// root among them from per-block root counts (scanned) and per-block root
-// masks, so no per-pixel slot map is needed.
+// component roots are the pixels with labels[p] == p; per-block root counts
+// (scanned) and root masks give each its slot, so no per-pixel slot map is
+// needed.  The box of a component is formed where the box of the piece with
+// its root is.
 // ---------------------------------------------------------------------------
-constexpr int kBoxWords = 8;  // per component: x0, y0, x1, y1, root pixel, pad
+// One workgroup scans the counts, so they are few: 1024 pixels each.
+constexpr int kRootBlock = 1024;
 
-// Flatten every label to its root (as k_ccl_flatten) and record, per
-// 256-pixel block of the flatten grid, the mask of component roots and its
-// population.
-__global__ __launch_bounds__(256) void k_ccl_flatten_roots(int64_t n, int* labels, uint32_t* __restrict__ bcount,
-                                                           uint32_t* __restrict__ rmask) {
+// Widen the box at e by b.  A bound that a read already shows to hold is
+// left alone (bounds only ever widen, so one read late holds too): the
+// pieces of a large component otherwise wait for each other at its four
+// words.
+__device__ inline void widen_box(int32_t* e, int4 b) {
+    int32_t now[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) now[q] = __hip_atomic_load(&e[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (b.x < now[0]) atomicMin(&e[0], b.x);
+    if (b.y < now[1]) atomicMin(&e[1], b.y);
+    if (b.z > now[2]) atomicMax(&e[2], b.z);
+    if (b.w > now[3]) atomicMax(&e[3], b.w);
+}
+
+// Flatten every label to its root (as k_ccl_flatten), widen the box at the
+// component's root pixel by those of its other pieces, and record, per block
+// of kRootBlock pixels, the mask of component roots and its population.
+// (2064x2208: 25 us, and 7 for the boxes' records and tiles; flattening and
+// boxes took 10 + 62 + 9 with a kernel of their own for the pieces and every
+// piece's four atomics sent.)
+__global__ __launch_bounds__(256) void k_ccl_flatten_roots(int64_t n, int* labels, const uint8_t* __restrict__ pflag,
+                                                           int4* pbox, uint32_t* __restrict__ bcount,
+                                                           unsigned long long* __restrict__ rmask) {
+    constexpr int kP = kRootBlock / 256;
     __shared__ uint32_t cnt[4];
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    bool root = false;
-    if (p < n) {
-        const int l = labels[p];
-        if (l >= 0) {
-            root = l == (int)p;
-            if (!root) labels[p] = find_root_g(labels, l);
+    const int64_t p0 = (int64_t)blockIdx.x * kRootBlock + threadIdx.x;
+    int l[kP];
+#pragma unroll
+    for (int q = 0; q < kP; ++q) l[q] = p0 + 256 * q < n ? labels[p0 + 256 * q] : -1;
+    uint32_t c = 0;
+#pragma unroll
+    for (int q = 0; q < kP; ++q) {
+        const int64_t p = p0 + 256 * q;
+        const bool root = l[q] >= 0 && l[q] == (int)p;
+        if (l[q] >= 0 && !root) {
+            const int r = find_root_g(labels, l[q]);
+            labels[p] = r;
+            if (pflag[p]) widen_box(reinterpret_cast<int32_t*>(pbox + r), pbox[p]);
         }
+        const unsigned long long m = __ballot(root);
+        // A word per 64 pixels; those past the image have none.
+        if ((threadIdx.x & 63) == 0 && p < n) rmask[p >> 6] = m;
+        c += (uint32_t)__popcll(m);
     }
-    const unsigned long long m = __ballot(root);
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        rmask[(size_t)blockIdx.x * 8 + 2 * w] = (uint32_t)m;
-        rmask[(size_t)blockIdx.x * 8 + 2 * w + 1] = (uint32_t)(m >> 32);
-        cnt[w] = (uint32_t)__popcll(m);
-    }
+    if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = c;
     __syncthreads();
     if (threadIdx.x == 0) bcount[blockIdx.x] = cnt[0] + cnt[1] + cnt[2] + cnt[3];
 }
 
 // One workgroup: the gap-fill counts, an exclusive scan of the nb block
 // counts in place (bcount[nb] gets the component count), the box count and
-// capacity flag, and the initial (empty) box of every component.
+// the capacity flag.
+//
 // Adds the gap-fill block counts (n_gpart entries) to the status block.  The
 // status words are read first and up to four partials per thread are
 // loaded together: this runs on one workgroup, where load latency is most
@@ -1266,9 +1381,9 @@ __device__ inline void fold_gap_parts(const uint2* __restrict__ gpart, int n_gpa
 // images walk per-thread chunks in global memory.
 constexpr int kRootLds = 16384;
 
-__global__ __launch_bounds__(1024) void k_root_scan(int64_t nb, uint32_t* bcount, int32_t* __restrict__ bbox,
-                                                    int box_cap, int32_t* __restrict__ n_boxes,
-                                                    const uint2* __restrict__ gpart, int n_gpart, DevStatus* st) {
+__global__ __launch_bounds__(1024) void k_root_scan(int64_t nb, uint32_t* bcount, int box_cap,
+                                                    int32_t* __restrict__ n_boxes, const uint2* __restrict__ gpart,
+                                                    int n_gpart, DevStatus* st) {
     __shared__ uint32_t s_cnt[kRootLds];
     __shared__ uint32_t wsum[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1329,56 +1444,30 @@ __global__ __launch_bounds__(1024) void k_root_scan(int64_t nb, uint32_t* bcount
         if ((int64_t)tot > box_cap) atomicOr(&st->overflow, 2u);
         *n_boxes = (int32_t)tot;
     }
-    for (uint32_t c = tid; c < total; c += 1024) {
-        int32_t* e = bbox + (size_t)c * kBoxWords;
-        e[0] = INT_MAX;
-        e[1] = INT_MAX;
-        e[2] = -1;
-        e[3] = -1;
-        e[4] = -1;
-    }
 }
 
-// Rank of component root r among all roots, in pixel order.
-__device__ inline uint32_t slot_of(int r, const uint32_t* __restrict__ boff, const uint32_t* __restrict__ rmask) {
-    const uint32_t blk = (uint32_t)r >> 8, bit = (uint32_t)r & 255u;
-    const uint32_t* m = rmask + (size_t)blk * 8;
-    uint32_t rank = boff[blk];
-    for (uint32_t q = 0; q < (bit >> 5); ++q) rank += __popc(m[q]);
-    const uint32_t low = bit & 31u;
-    if (low) rank += __popc(m[bit >> 5] & ((1u << low) - 1u));
-    return rank;
-}
-
-// Component boxes from the block-local pieces: 4 atomics per piece; the
-// piece that holds the component root records it.
-__global__ __launch_bounds__(256) void k_bbox_acc(int64_t n, const int* __restrict__ labels,
-                                                  const uint8_t* __restrict__ pflag, const int4* __restrict__ pbox,
-                                                  const uint32_t* __restrict__ boff, const uint32_t* __restrict__ rmask,
-                                                  int32_t* bbox) {
-    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (p >= n || !pflag[p]) return;
-    const int r = labels[p];
-    int32_t* e = bbox + (size_t)slot_of(r, boff, rmask) * kBoxWords;
-    const int4 b = pbox[p];
-    atomicMin(&e[0], b.x);
-    atomicMin(&e[1], b.y);
-    atomicMax(&e[2], b.z);
-    atomicMax(&e[3], b.w);
-    if (r == (int)p) e[4] = r;
-}
-
-// One workgroup per component (grid-stride over the component count):
-// margin, clip, tile alignment, the box record, and its tiles in the mask.
+// The components whose roots lie in this block's kRootBlock pixels, a wave per
+// component in turn (large boxes: all four): margin, clip, tile alignment, the box record, and its tiles in
+// the mask.
 __global__ __launch_bounds__(256) void k_center_boxes(int W, int H, int margin, int T, int tiles_x,
-                                                      const uint32_t* __restrict__ ncomp,
-                                                      const int32_t* __restrict__ bbox, bgs_box* __restrict__ boxes,
+                                                      const uint32_t* __restrict__ boff,
+                                                      const unsigned long long* __restrict__ rmask,
+                                                      const int4* __restrict__ pbox, bgs_box* __restrict__ boxes,
                                                       int box_cap, uint8_t* tm, const DevStatus* st) {
-    const uint32_t total = *ncomp;
-    for (uint32_t c = blockIdx.x; c < total; c += gridDim.x) {
-        const int32_t* e = bbox + (size_t)c * kBoxWords;
-        int64_t x0 = e[0] - margin, y0 = e[1] - margin;
-        int64_t x1 = e[2] + margin, y1 = e[3] + margin;
+    constexpr int kWords = kRootBlock / 64;
+    const uint32_t c0 = boff[blockIdx.x], c1 = boff[blockIdx.x + 1];
+    if (c0 == c1) return;
+    int word = blockIdx.x * kWords;
+    unsigned long long left = rmask[word];
+    for (uint32_t c = c0; c < c1; ++c) {
+        while (left == 0) left = rmask[++word];  // the block's masks hold c1 - c0 roots
+        const int root = 64 * word + __ffsll((long long)left) - 1;
+        left &= left - 1;
+        const bool mine = ((c - c0) & 3u) == threadIdx.x >> 6;
+        const int lane = threadIdx.x & 63;
+        const int4 e = pbox[root];
+        int64_t x0 = e.x - margin, y0 = e.y - margin;
+        int64_t x1 = (int64_t)e.z + margin, y1 = (int64_t)e.w + margin;
         if (x0 < 0) x0 = 0;
         if (y0 < 0) y0 = 0;
         if (x1 > W) x1 = W;
@@ -1389,7 +1478,7 @@ __global__ __launch_bounds__(256) void k_center_boxes(int W, int H, int margin, 
         y1 = align_up(y1, T);
         if (x1 > W) x1 = W;
         if (y1 > H) y1 = H;
-        if (threadIdx.x == 0) {
+        if (mine && lane == 0) {
             const int64_t slot = (int64_t)st->n_edge + c;
             if (slot < box_cap) {
                 boxes[slot].x0 = (int32_t)x0;
@@ -1397,12 +1486,17 @@ __global__ __launch_bounds__(256) void k_center_boxes(int W, int H, int margin, 
                 boxes[slot].x1 = (int32_t)x1;
                 boxes[slot].y1 = (int32_t)y1;
                 boxes[slot].kind = BGS_BOX_CENTER;
-                boxes[slot].label = e[4];
+                boxes[slot].label = root;
             }
         }
-        const int64_t tx0 = x0 / T, ty0 = y0 / T;
-        const int64_t bw = (x1 + T - 1) / T - tx0, bh = (y1 + T - 1) / T - ty0;
-        for (int64_t q = threadIdx.x; q < bw * bh; q += 256) tm[(ty0 + q / bw) * tiles_x + tx0 + q % bw] = 1;
+        const int tx0 = (int)(x0 / T), ty0 = (int)(y0 / T);
+        const int bw = (int)((x1 + T - 1) / T) - tx0, bh = (int)((y1 + T - 1) / T) - ty0;
+        const bool large = bw * bh > 1024;
+        if (!mine && !large) continue;
+        for (int q = large ? (int)threadIdx.x : lane; q < bw * bh; q += large ? 256 : 64) {
+            const int r = q / bw;
+            tm[(int64_t)(ty0 + r) * tiles_x + tx0 + q - r * bw] = 1;
+        }
     }
 }
 
@@ -1483,19 +1577,20 @@ hipError_t launch_reproject(const WarpCam& src, const WarpCam& dst, const RelPos
     return hipGetLastError();
 }
 
-static hipError_t label_components(const uint8_t* mask, int W, int H, int conn, int32_t* labels, uint8_t* pflag,
-                                   int4* pbox, hipStream_t s) {
-    const int64_t n = (int64_t)W * H;
-    if (n == 0) return hipSuccess;
-    dim3 g((W + 15) / 16, (H + 15) / 16);
-    hipLaunchKernelGGL(k_ccl_local, g, dim3(256), 0, s, W, H, conn, mask, labels, pflag, pbox);
-    hipLaunchKernelGGL(k_ccl_border, g, dim3(256), 0, s, W, H, conn, mask, labels);
-    hipLaunchKernelGGL(k_ccl_flatten, dim3(grid(n)), dim3(256), 0, s, n, labels);
-    return hipGetLastError();
+// Tile-local labels and the unions across tile borders, unflattened.
+static void launch_ccl_tiles(const uint8_t* mask, int W, int H, int conn, int32_t* labels, uint8_t* pflag, int4* pbox,
+                             hipStream_t s) {
+    const int tx = (W + 63) / 64, ty = (H + kCclRows - 1) / kCclRows;
+    hipLaunchKernelGGL(k_ccl_local, dim3(tx, ty), dim3(256), 0, s, W, H, conn, mask, labels, pflag, pbox);
+    hipLaunchKernelGGL(k_ccl_border, dim3((tx * ty + 3) / 4), dim3(256), 0, s, W, H, conn, tx, tx * ty, mask, labels);
 }
 
 hipError_t launch_label_components(const uint8_t* mask, int W, int H, int conn, int32_t* labels, hipStream_t s) {
-    return label_components(mask, W, H, conn, labels, nullptr, nullptr, s);
+    const int64_t n = (int64_t)W * H;
+    if (n == 0) return hipSuccess;
+    launch_ccl_tiles(mask, W, H, conn, labels, nullptr, nullptr, s);
+    hipLaunchKernelGGL(k_ccl_flatten, dim3(grid(n)), dim3(256), 0, s, n, labels);
+    return hipGetLastError();
 }
 
 hipError_t launch_classify(const WarpCam& src, const WarpCam& dst, const RelPose& P, const bgs_roi_params& roi,
@@ -1529,18 +1624,14 @@ hipError_t launch_classify(const WarpCam& src, const WarpCam& dst, const RelPose
         hipLaunchKernelGGL(k_center_mask, band_grid(W, H), dim3(256), 0, s, W, H, tag, center, st);
     }
     if (roi.center_roi) {
-        const int64_t nb = (n + 255) / 256;
-        dim3 g((W + 15) / 16, (H + 15) / 16);
-        hipLaunchKernelGGL(k_ccl_local, g, dim3(256), 0, s, W, H, 8, center, labels, b.pflag, b.pbox);
-        hipLaunchKernelGGL(k_ccl_border, g, dim3(256), 0, s, W, H, 8, center, labels);
-        hipLaunchKernelGGL(k_ccl_flatten_roots, dim3((unsigned)nb), dim3(256), 0, s, n, labels, b.bcount, b.rmask);
-        hipLaunchKernelGGL(k_root_scan, dim3(1), dim3(1024), 0, s, nb, b.bcount, b.bbox, box_cap, n_boxes, b.gpart,
-                           n_gpart, st);
-        hipLaunchKernelGGL(k_bbox_acc, dim3((unsigned)nb), dim3(256), 0, s, n, labels, b.pflag, b.pbox, b.bcount,
-                           b.rmask, b.bbox);
-        const unsigned gcb = (unsigned)std::min<int64_t>(256, nb);
-        hipLaunchKernelGGL(k_center_boxes, dim3(gcb), dim3(256), 0, s, W, H, roi.margin, T, tiles_x, b.bcount + nb,
-                           b.bbox, boxes, box_cap, tile_mask, st);
+        const int64_t nb = (n + kRootBlock - 1) / kRootBlock;
+        launch_ccl_tiles(center, W, H, 8, labels, b.pflag, b.pbox, s);
+        hipLaunchKernelGGL(k_ccl_flatten_roots, dim3((unsigned)nb), dim3(256), 0, s, n, labels, b.pflag, b.pbox, b.bcount,
+                           b.rmask);
+        hipLaunchKernelGGL(k_root_scan, dim3(1), dim3(1024), 0, s, nb, b.bcount, box_cap, n_boxes, b.gpart, n_gpart,
+                           st);
+        hipLaunchKernelGGL(k_center_boxes, dim3((unsigned)nb), dim3(256), 0, s, W, H, roi.margin, T, tiles_x, b.bcount,
+                           b.rmask, b.pbox, boxes, box_cap, tile_mask, st);
     } else {
         hipLaunchKernelGGL(k_fill_i32, dim3(grid(n)), dim3(256), 0, s, n, labels, -1);
         hipLaunchKernelGGL(k_row_fill, dim3(H), dim3(256), 0, s, W, H, tag, center, bg[0], bg[1], bg[2], rgb, z, alpha,
