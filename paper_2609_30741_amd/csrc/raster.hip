@@ -179,9 +179,12 @@ __device__ uint2 strip_band(bool bounded, double c00, double c01, double c02, do
 // this one function on the same values, so counts and keys agree exactly.
 // ---------------------------------------------------------------------------
 struct BandRows {
-    double k0, k16, r, inv;  // k(ty) = k0 + k16 ty; columns where |16 nx tx + k| <= r
-    bool vertical;           // nx = 0 (or no direction): whole rows in or out
-    __device__ BandRows() : k0(0.0), k16(0.0), r(-1.0), inv(0.0), vertical(true) {}  // no tile
+    // k(ty) = k0 + k16 ty; columns where |16 nx tx + k| <= r.  r has the sign
+    // of nx, so that the interval's ends come out in order; inv = 1 / (16 nx),
+    // or 0 where nx = 0 (or no direction): whole rows in or out.
+    double k0, k16, r, inv;
+    __device__ BandRows() : k0(0.0), k16(0.0), r(-1.0), inv(0.0) {}  // no tile
+    __device__ BandRows(double k0, double k16, double r, double inv) : k0(k0), k16(k16), r(r), inv(inv) {}
     __device__ explicit BandRows(const SurfelRec& rec)
         : BandRows(rec.a.x, rec.a.y, __float_as_uint(rec.c.w), __float_as_uint(rec.d.w)) {}
     __device__ BandRows(float mux, float muy, uint32_t nq, uint32_t bq) {
@@ -192,38 +195,45 @@ struct BandRows {
         r = (double)half_value(bq >> 16) + 7.5 * (fabs(nx) + fabs(ny)) + 0.5;
         k0 = nx * (7.5 - (double)mux) + ny * (7.5 - (double)muy) - c;
         k16 = 16.0 * ny;
-        vertical = !(fabs(nx) > 1e-9);
-        inv = vertical ? 0.0 : 1.0 / (16.0 * nx);
+        inv = !(fabs(nx) > 1e-9) ? 0.0 : 1.0 / (16.0 * nx);
+        if (inv < 0.0) r = -r;
     }
-    __device__ void row(int ty, int tx0, int tx1, int* a, int* b) const {
+};
+
+// The same, prepared for the rows of one surfel's rect.  Rows are where the
+// counting and the emission spend their time (vector instructions, in fp64),
+// so there is one path for both kinds of bands, without branches: a whole
+// row's interval is [0, kFar], or a row out of the band (|k| > rv).  (1.2M
+// surfels at 1920x1080: counting 78 -> 68 us, emission 90 -> 77.)
+struct BandRect {
+    static constexpr double kFar = 1e9;
+    double k0, k16, r, inv, rv, far, x0, x1;
+    __device__ BandRect(const BandRows& b, int tx0, int tx1) : k0(b.k0), k16(b.k16), r(b.r), inv(b.inv) {
+        const bool whole = inv == 0.0;  // also an infinite band (r = inf): every column
+        rv = whole ? r : INFINITY;
+        far = whole ? kFar : 0.0;
+        x0 = (double)tx0;
+        x1 = (double)tx1;
+    }
+    // Columns [*a, *b] of row ty; empty when *b < *a, or when false.
+    __device__ bool row(int ty, int* a, int* b) const {
 #pragma clang fp contract(off)
         const double k = fma(k16, (double)ty, k0);
-        if (vertical) {  // also an infinite band (r = inf): every column
-            const bool in = !(fabs(k) > r);
-            *a = in ? tx0 : 1;
-            *b = in ? tx1 : 0;
-            return;
-        }
-        double lo = (-r - k) * inv, hi = (r - k) * inv;
-        if (lo > hi) {
-            const double t = lo;
-            lo = hi;
-            hi = t;
-        }
-        lo = ceil(lo);
-        hi = floor(hi);
-        *a = lo > (double)tx0 ? (lo > (double)tx1 ? tx1 + 1 : (int)lo) : tx0;
-        *b = hi < (double)tx1 ? (hi < (double)tx0 ? tx0 - 1 : (int)hi) : tx1;
+        const double lo = (-r - k) * inv, hi = (r - k) * inv + far;
+        // (An infinite whole row's ends are NaN, which fmax and fmin pass over.)
+        *a = (int)fmin(fmax(ceil(lo), x0), x1 + 1.0);
+        *b = (int)fmax(fmin(floor(hi), x1), x0 - 1.0);
+        return !(fabs(k) > rv);
     }
 };
 
 // Tiles of a surfel's rect that its band meets.
 __device__ inline uint32_t band_count(const BandRows& br, int tx0, int ty0, int tx1, int ty1) {
     uint32_t cnt = 0;
+    const BandRect rect(br, tx0, tx1);
     for (int y = ty0; y <= ty1; ++y) {
         int a, b;
-        br.row(y, tx0, tx1, &a, &b);
-        if (b >= a) cnt += (uint32_t)(b - a + 1);
+        if (rect.row(y, &a, &b) && b >= a) cnt += (uint32_t)(b - a + 1);
     }
     return cnt;
 }
@@ -234,25 +244,26 @@ __device__ inline uint32_t band_count(const BandRows& br, int tx0, int ty0, int 
 // may be empty.
 template <typename F>
 __device__ inline void cell_masks(const BandRows& br, int tx0, int ty0, int tx1, int ty1, int cr, F&& f) {
-    int a[8], b[8], lo = INT_MAX, hi = -1;
+    constexpr int kNone = 1 << 14;  // an empty row: [kNone, kNone), past every column
+    const BandRect rect(br, tx0, tx1);
+    int a[8], e[8], lo = kNone, hi = -1;  // columns [a, e)
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
         const int y = 8 * cr + u;
-        a[u] = 1;
-        b[u] = 0;
-        if (y >= ty0 && y <= ty1) br.row(y, tx0, tx1, &a[u], &b[u]);
-        if (b[u] >= a[u]) {
-            lo = min(lo, a[u]);
-            hi = max(hi, b[u]);
-        }
+        int b;
+        const bool ok = rect.row(y, &a[u], &b) && y >= ty0 && y <= ty1 && b >= a[u];
+        a[u] = ok ? a[u] : kNone;
+        e[u] = ok ? b + 1 : kNone;
+        lo = min(lo, a[u]);
+        hi = max(hi, ok ? b : -1);
     }
     if (hi < 0) return;
     for (int cx = lo >> 3; cx <= hi >> 3; ++cx) {
         uint32_t w[2] = {0u, 0u};
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int s = max(a[u] - 8 * cx, 0), e = min(b[u] - 8 * cx, 7);  // e < s for an empty row
-            w[u >> 2] |= ((1u << max(e + 1 - s, 0)) - 1u) << ((min(s, 8) + 8 * u) & 31);
+            const int s = min(max(a[u] - 8 * cx, 0), 8), t = min(max(e[u] - 8 * cx, 0), 8);  // s <= t
+            w[u >> 2] |= ((1u << t) - (1u << s)) << (8 * (u & 3));
         }
         f(cx, (uint64_t)w[0] | ((uint64_t)w[1] << 32));
     }
@@ -616,13 +627,7 @@ __device__ __forceinline__ uint32_t bin_stage(const BinArgs& a, int64_t p0, int 
 
 // The band of surfel j of the stage.
 __device__ __forceinline__ BandRows stage_band(const BinStage& s, int j) {
-    BandRows br;
-    br.k0 = s.k0[j];
-    br.k16 = s.k16[j];
-    br.r = s.r[j];
-    br.inv = s.inv[j];
-    br.vertical = br.inv == 0.0;
-    return br;
+    return BandRows(s.k0[j], s.k16[j], s.r[j], s.inv[j]);
 }
 
 // f(cell column, mask) for every entry of surfel j in cell row cr.
