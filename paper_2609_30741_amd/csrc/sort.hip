@@ -69,39 +69,41 @@ hipError_t launch_fill_u32(uint32_t* dst, int64_t n, uint32_t value, hipStream_t
 
 // ---------------------------------------------------------------------------
 // Radix sort.  Stable LSD with digits of up to 8 bits (a 32-bit key takes four
-// passes, a 13-bit one two of 7 and 6 bits).  The grid is fixed by the
-// capacity (at most kRsGrid blocks; always kRsSmallGrid for small sorts,
-// which use 1024-key sub-chunks instead of 6144); block b owns the contiguous
-// chunk [b C, b C + C) of the n keys, C = n / grid rounded up to 256.
-// A pass is three launches:
+// passes, a 13-bit one two of 7 and 6 bits).  The grid is kRsGrid blocks;
+// block b owns the contiguous chunk [b C, b C + C) of the n keys, C = n /
+// kRsGrid rounded up to 256.  A pass is three launches:
 //   1. k_rs_hist: per-block digit counts (LDS atomics), stored
 //      digit-major: counts[d * grid + b].
 //   2. k_rs_scan: one block per digit scans its row over the blocks and
 //      writes the digit total.
 //   3. k_rs_scatter: every block scans the digit totals, then walks its chunk
-//      in sub-chunks of 6144 keys: each wave ranks its 1536 keys in 24 steps
-//      of 64 (1024-key sub-chunks, 4 steps, for small sorts) with match-any
-//      ballots and a per-wave LDS count per digit, the sub-chunk is
-//      reordered by digit in LDS, and each digit's run (24 keys on average
-//      at 8 bits) is written out contiguously.  Large sorts rank digits of
-//      at most 7 bits with per-thread counters instead (k_rs_scatter_cnt).
+//      in sub-chunks of kThreads * kItems keys: each wave ranks its keys in
+//      kItems steps of 64 with match-any ballots and a per-wave LDS count per
+//      digit, the sub-chunk is reordered by digit in LDS, and each digit's
+//      run is written out contiguously while the next sub-chunk's keys are
+//      on their way.
 // Blocks never wait on each other.
+//
+// Bound by memory on large sorts, by the latency of the launches and of a
+// block's steps on small ones.  Two blocks a CU, all resident: every digit of
+// every block has a line of keys and one of values open in its XCD's L2 (4
+// MiB at 8 bits and 512 blocks), and more blocks only add to these.  What
+// hides the steps' latency is waves: 512 threads with 8 keys each (16 waves
+// a CU) took 19.6M 13-bit pairs from 288 to 214 us and 4M 32-bit pairs from
+// 267 to 150, against 256 threads with 24 keys (8 waves); 12 or 16 keys a
+// thread, whose registers halve the waves, took 305 and 281, and 768 or 1024
+// blocks 255 and 223.
 // ---------------------------------------------------------------------------
 namespace {
 
 constexpr int kRsMaxBits = 8;
 constexpr int kRsBins = 1 << kRsMaxBits;
-constexpr int kRsGrid = 1024;
-// Small sorts use half the grid: a 300k-key depth sort then gives each
-// block about 600 keys, and its count table and per-digit scans shrink by
-// half (61.8 against 69.2 us).
-constexpr int kRsSmallGrid = 512;
-// Keys per thread per sub-chunk: 24 (6144-key sub-chunks, long digit runs;
-// a 6M-key tile sort then gives each block one sub-chunk, not a full and a
-// partial one in turn) for large sorts; 4 (1024-key sub-chunks) for small
-// ones, where a block holds only a few hundred keys and its latency is the
-// sort's.
-constexpr int kRsItemsBig = 24, kRsItemsSmall = 4;
+constexpr int kRsGrid = 512;
+// Threads and keys per thread of a block, by the keys of its chunk: one
+// sub-chunk where it can be, as small as it can be.  (300k pairs of 32 bits:
+// 74 us with 256 threads of 4, 80 of 8, 85 with 512 of 8; 1M: 98, 92, 95;
+// 1.2M: 110, 110, 99; it was 123.)
+constexpr int64_t kRsSmall = kRsGrid * 256 * 4, kRsMedium = kRsGrid * 256 * 8;
 __device__ inline uint64_t match_digit(uint32_t d, uint64_t valid, int bits) {
     uint64_t peers = valid;
 #pragma unroll
@@ -123,29 +125,28 @@ __device__ inline void chunk_of(uint32_t n, uint32_t grid, uint32_t b, uint32_t*
     *hi = (uint32_t)min<uint64_t>(l + c, n);
 }
 
-template <int kRsItems>
-__global__ __launch_bounds__(256) void k_rs_hist(const uint32_t* __restrict__ keys, uint32_t n, int shift, int bits,
-                                                 uint32_t* __restrict__ counts) {
-    constexpr int kRsSub = 256 * kRsItems;
+template <int kThreads, int kItems>
+__global__ __launch_bounds__(kThreads) void k_rs_hist(const uint32_t* __restrict__ keys, uint32_t n, int shift, int bits,
+                                                      uint32_t* __restrict__ counts) {
     __shared__ uint32_t h[kRsBins];
     const uint32_t bins = 1u << bits, mask = bins - 1u;
-    h[threadIdx.x] = 0;
+    if (threadIdx.x < kRsBins) h[threadIdx.x] = 0u;
     __syncthreads();
     uint32_t lo, hi;
     chunk_of(n, gridDim.x, blockIdx.x, &lo, &hi);
-    for (uint64_t sub = lo; sub < hi; sub += kRsSub) {
-        uint32_t k[kRsItems];
+    for (uint64_t sub = lo; sub < hi; sub += kThreads * kItems) {
+        uint32_t k[kItems];
 #pragma unroll
-        for (int it = 0; it < kRsItems; ++it) {
-            const uint64_t i = sub + it * 256 + threadIdx.x;
+        for (int it = 0; it < kItems; ++it) {
+            const uint64_t i = sub + it * kThreads + threadIdx.x;
             k[it] = i < hi ? keys[i] : 0u;
         }
         // Counts only (no ranks): one LDS add per key; lanes of a wave on
         // one digit are serialised by the LDS, which costs less than
         // matching the digits with ballots.
 #pragma unroll
-        for (int it = 0; it < kRsItems; ++it) {
-            if (sub + it * 256 + threadIdx.x < hi) atomicAdd(&h[(k[it] >> shift) & mask], 1u);
+        for (int it = 0; it < kItems; ++it) {
+            if (sub + it * kThreads + threadIdx.x < hi) atomicAdd(&h[(k[it] >> shift) & mask], 1u);
         }
     }
     __syncthreads();
@@ -176,258 +177,116 @@ __global__ __launch_bounds__(256) void k_rs_scan(uint32_t* __restrict__ counts, 
     if (threadIdx.x == 0) totals[blockIdx.x] = tot;
 }
 
-template <int kRsItems>
-__global__ __launch_bounds__(256) void k_rs_scatter(const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                    uint32_t n, int shift, int bits,
-                                                    const uint32_t* __restrict__ counts,
-                                                    const uint32_t* __restrict__ totals) {
-    constexpr int kRsSub = 256 * kRsItems;
-    __shared__ uint32_t s_keys[kRsSub], s_vals[kRsSub];
-    __shared__ uint32_t cnt0[4 * kRsBins], dstart[kRsBins], gbase[kRsBins], run[kRsBins], lds[4];
-    const uint32_t G = gridDim.x;
-    const auto cnt = [&](uint32_t w) { return cnt0 + w * kRsBins; };
-    const uint32_t bins = 1u << bits, mask = bins - 1u;
+template <int kThreads, int kItems>
+__global__ __launch_bounds__(kThreads) void k_rs_scatter(const uint32_t* __restrict__ kin,
+                                                         const uint32_t* __restrict__ vin, uint32_t* __restrict__ kout,
+                                                         uint32_t* __restrict__ vout, uint32_t n, int shift, int bits,
+                                                         const uint32_t* __restrict__ counts,
+                                                         const uint32_t* __restrict__ totals) {
+    constexpr int kWaves = kThreads / 64;
+    constexpr uint32_t kSub = kThreads * kItems;
+    __shared__ uint32_t s_keys[kSub], s_vals[kSub];
+    __shared__ uint32_t cnt[kWaves][kRsBins], to[kRsBins], lds[4];
+    const uint32_t G = gridDim.x, bins = 1u << bits, mask = bins - 1u;
     uint32_t lo, hi;
     chunk_of(n, G, blockIdx.x, &lo, &hi);
     if (lo >= hi) return;
-    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t t = threadIdx.x, lane = lane_id(), wave = t >> 6;
     const uint64_t lt = (1ull << lane) - 1ull;
-    const uint32_t dt = threadIdx.x;  // the digit this thread looks after
-    {
-        // run[d] = (keys of smaller digits) + (keys of digit d in earlier blocks).
-        const uint32_t t = dt < bins ? totals[dt] : 0u;
-        const uint32_t acc = block_excl_scan(t, lds, nullptr);
-        if (dt < bins) run[dt] = acc + counts[(uint64_t)dt * G + blockIdx.x];
+    const uint32_t first = wave * (64 * kItems) + lane;  // the thread's first key of a sub-chunk
+    uint32_t k[kItems], v[kItems];
+    const auto load = [&](uint64_t sub) {
 #pragma unroll
-        for (int w = 0; w < 4; ++w) cnt(w)[dt] = 0;
-    }
-    __syncthreads();
-    for (uint64_t sub = lo; sub < hi; sub += kRsSub) {
-        uint32_t k[kRsItems], v[kRsItems], r[kRsItems];
-#pragma unroll
-        for (int it = 0; it < kRsItems; ++it) {
-            const uint64_t i = sub + wave * (64 * kRsItems) + it * 64 + lane;
+        for (int it = 0; it < kItems; ++it) {
+            const uint64_t i = sub + first + it * 64;
             const bool ok = i < hi;
             k[it] = ok ? kin[i] : 0u;
             v[it] = ok ? (vin ? vin[i] : (uint32_t)i) : 0u;
         }
-#pragma unroll
-        for (int it = 0; it < kRsItems; ++it) {
-            const uint64_t i = sub + wave * (64 * kRsItems) + it * 64 + lane;
-            const bool ok = i < hi;
-            const uint32_t d = (k[it] >> shift) & mask;
-            const uint64_t peers = match_digit(d, __ballot(ok), bits);
-            const uint32_t c = ok ? cnt(wave)[d] : 0u;
-            r[it] = ok ? c + (uint32_t)__popcll(peers & lt) : 0xFFFFFFFFu;
-            __builtin_amdgcn_wave_barrier();
-            if (ok && (peers & lt) == 0) cnt(wave)[d] = c + (uint32_t)__popcll(peers);
-            __builtin_amdgcn_wave_barrier();
-        }
-        __syncthreads();
-        {
-            const uint32_t c0 = cnt(0)[dt], c1 = cnt(1)[dt], c2 = cnt(2)[dt], c3 = cnt(3)[dt];
-            const uint32_t tot = c0 + c1 + c2 + c3;
-            const uint32_t st = block_excl_scan(tot, lds, nullptr);
-            cnt(0)[dt] = st;
-            cnt(1)[dt] = st + c0;
-            cnt(2)[dt] = st + c0 + c1;
-            cnt(3)[dt] = st + c0 + c1 + c2;
-            dstart[dt] = st;
-            if (dt < bins) {
-                gbase[dt] = run[dt];
-                run[dt] += tot;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < kRsItems; ++it) {
-            if (r[it] != 0xFFFFFFFFu) {
-                const uint32_t lp = cnt(wave)[(k[it] >> shift) & mask] + r[it];
-                s_keys[lp] = k[it];
-                s_vals[lp] = v[it];
-            }
-        }
-        __syncthreads();
-        const uint32_t m = (uint32_t)min<uint64_t>((uint64_t)kRsSub, hi - sub);
-        for (uint32_t p = threadIdx.x; p < m; p += 256) {
-            const uint32_t kk = s_keys[p];
-            const uint32_t d = (kk >> shift) & mask;
-            const uint32_t o = gbase[d] + (p - dstart[d]);
-            if (o < n) {  // always true for consistent counts; keeps every write in bounds
-                kout[o] = kk;
-                vout[o] = s_vals[p];
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < 4; ++w) cnt(w)[dt] = 0;
-        __syncthreads();
-    }
-}
-
-// k_rs_scatter for digits of at most 7 bits and 6144-key sub-chunks, with
-// the ranks taken from per-thread digit counters instead of ballots: thread
-// t holds the sub-chunk's keys [24 t, 24 t + 24) (blocked, so input order is
-// (thread, item) order), counts its digits in a 16-bit LDS counter per
-// (digit, thread), a raking scan of the counters in (digit, thread) order
-// gives every (digit, thread) its first rank, and the thread's own count
-// before each key adds the rest.  Stable, like the ballot ranking, at a
-// fraction of its vector work.  The counter words are padded by one word in
-// 32 so the raking threads hit distinct banks; the same LDS holds the
-// reordered keys and values once the ranks are known.  (At 24 keys per
-// thread a counter reaches 24 and a rank 6143: 16 bits hold both.)
-// Digits of 7 bits need 64 KiB of counters, which gfx950's 160 KiB of LDS
-// per workgroup holds for two workgroups per CU: a 13-bit tile id then
-// takes two counter-ranked passes (7 + 6 bits) instead of a ballot-ranked
-// 7-bit pass and a counter-ranked one.  Digits of at most 6 bits keep the
-// 32 KiB form.
-constexpr int kRsCntMaxBits = 7;
-__host__ __device__ constexpr int rs_cnt_words(int bits) { return (1 << bits) * 256 / 2; }  // two 16-bit counters a word
-__host__ __device__ constexpr int rs_cnt_lds(int bits) { return rs_cnt_words(bits) + rs_cnt_words(bits) / 32; }  // padded
-static_assert(kRsItemsBig % 4 == 0, "a thread's keys are loaded as 16-byte vectors");
-
-__device__ __forceinline__ uint32_t cnt_slot(uint32_t w) { return w + (w >> 5); }
-
-// The counters, then the sub-chunk's keys and values.
-template <int kBits>
-__host__ __device__ constexpr int rs_cnt_buf() {
-    return rs_cnt_lds(kBits) > 2 * 256 * kRsItemsBig ? rs_cnt_lds(kBits) : 2 * 256 * kRsItemsBig;
-}
-
-template <int kBits>
-__global__ __launch_bounds__(256, 2) void k_rs_scatter_cnt(const uint32_t* __restrict__ kin,
-                                                           const uint32_t* __restrict__ vin,
-                                                           uint32_t* __restrict__ kout, uint32_t* __restrict__ vout,
-                                                           uint32_t n, int shift, int bits,
-                                                           const uint32_t* __restrict__ counts,
-                                                           const uint32_t* __restrict__ totals) {
-    constexpr int kItems = kRsItemsBig;
-    constexpr int kSub = 256 * kItems;
-    constexpr int kBins = 1 << kBits;
-    __shared__ uint32_t s_buf[rs_cnt_buf<kBits>()];
-    __shared__ uint32_t dstart[kBins + 1], gbase[kBins], run[kBins], lds[4];
-    uint32_t* s_keys = s_buf;
-    uint32_t* s_vals = s_buf + kSub;
-    const uint32_t G = gridDim.x;
-    const uint32_t bins = 1u << bits, mask = bins - 1u;
-    uint32_t lo, hi;
-    chunk_of(n, G, blockIdx.x, &lo, &hi);
-    if (lo >= hi) return;
-    const uint32_t t = threadIdx.x;
+    };
+    load(lo);
+    // Of the digit that this thread looks after: where its next key goes,
+    // i.e. (keys of smaller digits) + (keys of the digit in earlier blocks).
+    uint32_t run = 0;
+    const bool mine = t < bins;
+    if (mine) run = counts[(uint64_t)t * G + blockIdx.x];
     {
-        // run[d] = (keys of smaller digits) + (keys of digit d in earlier blocks).
-        const uint32_t tv = t < bins ? totals[t] : 0u;
-        const uint32_t acc = block_excl_scan(tv, lds, nullptr);
-        if (t < bins) run[t] = acc + counts[(uint64_t)t * G + blockIdx.x];
+        uint32_t x = 0;
+        if (t < kRsBins) {
+            x = wave_incl_scan(mine ? totals[t] : 0u);
+            if (lane == 63) lds[wave] = x;
+        }
+        __syncthreads();
+        if (mine) {
+            run += x - totals[t];
+            for (uint32_t w = 0; w < wave; ++w) run += lds[w];
+        }
     }
-    const uint32_t rake = bins / 2;         // counter words per thread (bins * 256 / 2 words over 256 threads)
-    const uint32_t nclear = cnt_slot(bins * 128u);
     for (uint64_t sub = lo; sub < hi; sub += kSub) {
         const uint32_t m = (uint32_t)min<uint64_t>((uint64_t)kSub, hi - sub);
-        const uint32_t i0 = t * kItems;
-        uint32_t k[kItems], v[kItems];
-        if (i0 + kItems <= m) {
-            const uint4* kp = reinterpret_cast<const uint4*>(kin + sub + i0);
+        for (uint32_t i = t; i < kWaves * kRsBins; i += kThreads) (&cnt[0][0])[i] = 0u;
+        __syncthreads();
+        uint32_t r[kItems];
 #pragma unroll
-            for (int q = 0; q < kItems / 4; ++q) {
-                const uint4 x = kp[q];
-                k[4 * q] = x.x; k[4 * q + 1] = x.y; k[4 * q + 2] = x.z; k[4 * q + 3] = x.w;
+        for (int it = 0; it < kItems; ++it) {
+            const bool ok = first + it * 64 < m;
+            const uint32_t d = (k[it] >> shift) & mask;
+            const uint64_t peers = match_digit(d, __ballot(ok), bits);
+            const uint32_t c = ok ? cnt[wave][d] : 0u;
+            r[it] = c + (uint32_t)__popcll(peers & lt);
+            __builtin_amdgcn_wave_barrier();
+            if (ok && (peers & lt) == 0) cnt[wave][d] = c + (uint32_t)__popcll(peers);
+            __builtin_amdgcn_wave_barrier();
+        }
+        __syncthreads();
+        // First place of every (digit, wave) in the sub-chunk.
+        uint32_t tot = 0, x = 0;
+        if (mine) {
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t c = cnt[w][t];
+                cnt[w][t] = tot;
+                tot += c;
             }
-            if (vin) {
-                const uint4* vp = reinterpret_cast<const uint4*>(vin + sub + i0);
+        }
+        if (t < kRsBins) {
+            x = wave_incl_scan(tot);
+            if (lane == 63) lds[wave] = x;
+        }
+        __syncthreads();
+        if (mine) {
+            uint32_t at = x - tot;
+            for (uint32_t w = 0; w < wave; ++w) at += lds[w];
 #pragma unroll
-                for (int q = 0; q < kItems / 4; ++q) {
-                    const uint4 x = vp[q];
-                    v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
+            for (int w = 0; w < kWaves; ++w) cnt[w][t] += at;
+            to[t] = run - at;  // where the sub-chunk's places of this digit go
+            run += tot;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            if (first + it * 64 < m) {
+                const uint32_t p = cnt[wave][(k[it] >> shift) & mask] + r[it];
+                s_keys[p] = k[it];
+                s_vals[p] = v[it];
+            }
+        }
+        __syncthreads();
+        if (sub + kSub < hi) load(sub + kSub);  // in flight while this one is written
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            const uint32_t p = t + it * kThreads;
+            if (p < m) {
+                const uint32_t kk = s_keys[p];
+                const uint32_t o = to[(kk >> shift) & mask] + p;
+                if (o < n) {  // always true for consistent counts; keeps every write in bounds
+                    kout[o] = kk;
+                    vout[o] = s_vals[p];
                 }
-            } else {
-#pragma unroll
-                for (int it = 0; it < kItems; ++it) v[it] = (uint32_t)(sub + i0 + it);
-            }
-        } else {
-#pragma unroll
-            for (int it = 0; it < kItems; ++it) {
-                const bool ok = i0 + it < m;
-                k[it] = ok ? kin[sub + i0 + it] : 0u;
-                v[it] = ok ? (vin ? vin[sub + i0 + it] : (uint32_t)(sub + i0 + it)) : 0u;
             }
         }
-        for (uint32_t w = t; w < nclear; w += 256) s_buf[w] = 0u;
-        __syncthreads();
-        // This thread's count of each digit before each of its keys.  Ranks
-        // stay below 2^16 (a sub-chunk holds 6144 keys), so two share a
-        // register: fewer live registers, more waves per SIMD.
-        uint32_t r2[kItems / 2];
-#pragma unroll
-        for (int q = 0; q < kItems / 2; ++q) r2[q] = 0u;
-#pragma unroll
-        for (int it = 0; it < kItems; ++it) {
-            if (i0 + it < m) {
-                const uint32_t d = (k[it] >> shift) & mask;
-                const uint32_t e = d * 256u + t;
-                const uint32_t h = 16u * (e & 1u);
-                const uint32_t old = atomicAdd(&s_buf[cnt_slot(e >> 1)], 1u << h);
-                r2[it >> 1] |= ((old >> h) & 0xFFFFu) << (16 * (it & 1));
-            }
-        }
-        __syncthreads();
-        // Raking exclusive scan of the counters in (digit, thread) order; the
-        // words are read again for the second sweep rather than held.
-        uint32_t sum = 0;
-#pragma unroll
-        for (int j = 0; j < kBins / 2; ++j) {
-            if ((uint32_t)j < rake) {
-                const uint32_t w = s_buf[cnt_slot(t * rake + j)];
-                sum += (w & 0xFFFFu) + (w >> 16);
-            }
-        }
-        uint32_t acc = block_excl_scan(sum, lds, nullptr);
-#pragma unroll
-        for (int j = 0; j < kBins / 2; ++j) {
-            if ((uint32_t)j < rake) {
-                const uint32_t w = s_buf[cnt_slot(t * rake + j)];
-                const uint32_t e0 = acc;
-                acc += w & 0xFFFFu;
-                s_buf[cnt_slot(t * rake + j)] = e0 | (acc << 16);
-                acc += w >> 16;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < kItems; ++it) {
-            if (i0 + it < m) {
-                const uint32_t e = ((k[it] >> shift) & mask) * 256u + t;
-                const uint32_t first = (s_buf[cnt_slot(e >> 1)] >> (16u * (e & 1u))) & 0xFFFFu;
-                r2[it >> 1] += first << (16 * (it & 1));  // no carry: every rank is below 2^16
-            }
-        }
-        if (t < bins) dstart[t] = s_buf[cnt_slot(t * 128u)] & 0xFFFFu;
-        if (t == 0) dstart[bins] = m;
-        __syncthreads();  // every counter read is done before the keys overwrite them
-        if (t < bins) {
-            gbase[t] = run[t];
-            run[t] += dstart[t + 1] - dstart[t];
-        }
-#pragma unroll
-        for (int it = 0; it < kItems; ++it) {
-            if (i0 + it < m) {
-                const uint32_t rk = (r2[it >> 1] >> (16 * (it & 1))) & 0xFFFFu;
-                s_keys[rk] = k[it];
-                s_vals[rk] = v[it];
-            }
-        }
-        __syncthreads();
-        for (uint32_t p = t; p < m; p += 256) {
-            const uint32_t kk = s_keys[p];
-            const uint32_t d = (kk >> shift) & mask;
-            const uint32_t o = gbase[d] + (p - dstart[d]);
-            if (o < n) {  // always true for consistent counts; keeps every write in bounds
-                kout[o] = kk;
-                vout[o] = s_vals[p];
-            }
-        }
-        __syncthreads();
+        // The next sub-chunk's first barrier comes before any write to the
+        // LDS that is read here.
     }
 }
 
@@ -540,9 +399,14 @@ __global__ __launch_bounds__(kBlockThreads) void k_rs_block(uint32_t* keys, cons
     }
 }
 
-uint32_t rs_grid(int64_t n_cap, int items) {
-    const int64_t g = ceil_div(n_cap > 0 ? n_cap : 1, 256 * items);
-    return (uint32_t)(g < kRsGrid ? g : kRsGrid);
+template <int kThreads, int kItems>
+void launch_rs_pass(const uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint32_t* vo, uint32_t n, int shift, int bits,
+                    uint32_t* counts, uint32_t* totals, hipStream_t s) {
+    const dim3 grid(kRsGrid), wg(kThreads);
+    hipLaunchKernelGGL((k_rs_hist<kThreads, kItems>), grid, wg, 0, s, ki, n, shift, bits, counts);
+    hipLaunchKernelGGL(k_rs_scan, dim3(1u << bits), dim3(256), 0, s, counts, (uint32_t)kRsGrid, totals);
+    hipLaunchKernelGGL((k_rs_scatter<kThreads, kItems>), grid, wg, 0, s, ki, vi, ko, vo, n, shift, bits, counts,
+                       totals);
 }
 
 }  // namespace
@@ -570,39 +434,19 @@ hipError_t radix_sort(uint32_t* ka, uint32_t* va, uint32_t* kb, uint32_t* vb, in
             hipLaunchKernelGGL(k_rs_block<16>, one, wg, 0, s, ka, vin, va, (uint32_t)n, key_bits);
         return hipGetLastError();
     }
-    // Small sorts (keys per block of the full grid below 1024): 1024-key
-    // sub-chunks.
-    const bool small = n <= (int64_t)kRsGrid * 256 * kRsItemsSmall;
-    const uint32_t grid = small ? kRsSmallGrid : rs_grid(n, kRsItemsBig);
     uint32_t* counts = (uint32_t*)tmp;
-    uint32_t* totals = counts + (size_t)kRsBins * kRsGrid;  // past the largest count table
+    uint32_t* totals = counts + (size_t)kRsBins * kRsGrid;
     const int passes = (key_bits + kRsMaxBits - 1) / kRsMaxBits;
     const int per = (key_bits + passes - 1) / passes;
-    // The counter-ranked scatter loads 16-byte vectors.
-    const auto a16 = [](const void* p) { return ((uintptr_t)p & 15u) == 0; };
-    const bool aligned = a16(ka) && a16(kb) && a16(va) && a16(vb);
     uint32_t *ki = ka, *ko = kb, *vo = vb;
     const uint32_t* vi = iota ? nullptr : va;
     bool cur_b = false;
     for (int shift = 0; shift < key_bits; shift += per) {
         const int bits = key_bits - shift < per ? key_bits - shift : per;
-        if (small)
-            hipLaunchKernelGGL(k_rs_hist<kRsItemsSmall>, dim3(grid), dim3(256), 0, s, ki, (uint32_t)n, shift, bits, counts);
-        else
-            hipLaunchKernelGGL(k_rs_hist<kRsItemsBig>, dim3(grid), dim3(256), 0, s, ki, (uint32_t)n, shift, bits, counts);
-        hipLaunchKernelGGL(k_rs_scan, dim3(1u << bits), dim3(256), 0, s, counts, grid, totals);
-        if (small)
-            hipLaunchKernelGGL(k_rs_scatter<kRsItemsSmall>, dim3(grid), dim3(256), 0, s, ki, vi, ko, vo, (uint32_t)n,
-                               shift, bits, counts, totals);
-        else if (bits <= 6 && aligned)
-            hipLaunchKernelGGL(k_rs_scatter_cnt<6>, dim3(grid), dim3(256), 0, s, ki, vi, ko, vo, (uint32_t)n, shift,
-                               bits, counts, totals);
-        else if (bits <= kRsCntMaxBits && aligned)
-            hipLaunchKernelGGL(k_rs_scatter_cnt<kRsCntMaxBits>, dim3(grid), dim3(256), 0, s, ki, vi, ko, vo,
-                               (uint32_t)n, shift, bits, counts, totals);
-        else
-            hipLaunchKernelGGL(k_rs_scatter<kRsItemsBig>, dim3(grid), dim3(256), 0, s, ki, vi, ko, vo, (uint32_t)n,
-                               shift, bits, counts, totals);
+        const auto pass = n <= kRsSmall    ? launch_rs_pass<256, 4>
+                          : n <= kRsMedium ? launch_rs_pass<256, 8>
+                                           : launch_rs_pass<512, 8>;
+        pass(ki, vi, ko, vo, (uint32_t)n, shift, bits, counts, totals, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         cur_b = !cur_b;
