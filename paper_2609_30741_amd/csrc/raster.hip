@@ -1322,7 +1322,9 @@ struct TileGeom {
 // Alpha of one (pixel, surfel) pair (Eq. 2 with the plane homography of the
 // record): alpha = min(alpha_max, o * max(G3, G2)), and the depth the pair
 // adds to the proxy (the ray-plane depth where G3 wins, else the centre
-// depth).
+// depth).  kPlane: of a pair whose record is plane-only in the wave's region
+// (record_in_region), which leaves out what cannot matter there.
+template <bool kPlane>
 __device__ __forceinline__ void pair_alpha(const float4& r0, const float4& r1, const float4& r2, float fpx, float fpy,
                                            const BlendArgs& a, float& al, float& dsel) {
     const float dx = fpx - r0.x, dy = fpy - r0.y;
@@ -1336,7 +1338,13 @@ __device__ __forceinline__ void pair_alpha(const float4& r0, const float4& r1, c
     // fmaxf then keeps the low-pass term.
     // The record's u and v coefficients carry a factor sqrt(1/2), so
     // -(u^2 + v^2) here is the G3 exponent -(u^2 + v^2) / 2 of the plane.
-    const float e3 = lam > a.z_near ? -fmaf(u, u, v * v) : -INFINITY;
+    const float eq = -fmaf(u, u, v * v);
+    if (kPlane) {
+        al = fminf(a.alpha_max, r2.z * __expf(eq));
+        dsel = lam;
+        return;
+    }
+    const float e3 = lam > a.z_near ? eq : -INFINITY;
     const float e2 = a.lowpass ? -fmaf(dx, dx, dy * dy) : -INFINITY;
     al = fminf(a.alpha_max, r2.z * __expf(fmaxf(e3, e2)));
     dsel = (e3 >= e2) ? lam : r2.y;
@@ -1370,21 +1378,33 @@ __device__ __forceinline__ void accumulate(float al, float dsel, const float4& r
     }
 }
 
-// Whether a record whose band meets the wave's 8x8 region (centre offset
-// dx, dy from the projected centre) still misses every pixel of it.  The
-// band bounds the footprint across its narrowest direction only; along the
-// others the region may lie past the footprint's end.  In plane coordinates
-// (u, v) = (nu, nv) / den the footprint is the disc u^2 + v^2 <= ln(o /
-// alpha_min); over the region |(nu, nv)| falls below its value at the centre
-// by at most the larger half diagonal of the region's image, and den rises
-// by at most 3.5 (|N1| + |N2|).  The low-pass disc must be missed too.
+// What a record whose band meets the wave's 8x8 region (centre offset dx, dy
+// from the projected centre) can do there.
+//
+// kMisses: nothing at any pixel.  The band bounds the footprint across its
+// narrowest direction only; along the others the region may lie past the
+// footprint's end.  In plane coordinates (u, v) = (nu, nv) / den the
+// footprint is the disc u^2 + v^2 <= ln(o / alpha_min); over the region
+// |(nu, nv)| falls below its value at the centre by at most the larger half
+// diagonal of the region's image, and den rises by at most
+// 3.5 (|N1| + |N2|).  The low-pass disc must be missed too.
+//
+// kPlane: the low-pass disc is missed, so at every pixel where the pair counts
+// (alpha >= alpha_min) G3 is the larger term and gives the depth, and the
+// plane is in front of z_near all over the region: the walk then needs
+// neither the low-pass term nor the selections between the two, nor the
+// test against z_near.  den is bounded away from 0, so that the depth is
+// finite also where the pair does not count and enters with weight 0.  Most
+// (record, region) pairs of surfels larger than a tile are of this kind.
+//
 // Every bound is widened far beyond the rounding of these sums and of
-// pair_alpha's, so a record dropped here would have got alpha < alpha_min at
-// every pixel and changed nothing.  (One lane tests one record, so this
-// costs each wave less than one of the evaluations it saves.)
-__device__ __forceinline__ bool region_misses(const float4& r0, const float4& r1, float op, float dx, float dy,
-                                              const BlendArgs& a) {
-    const float lr = __logf(op * __builtin_amdgcn_rcpf(a.alpha_min)) + 1e-3f;
+// pair_alpha's, so neither case changes a bit of the image.  (One lane
+// tests one record, so this costs each wave less than one of the evaluations
+// it saves.)
+enum { kMisses, kPlane, kGeneral };
+__device__ __forceinline__ int record_in_region(const float4& r0, const float4& r1, const float4& r2, float dx, float dy,
+                                                const BlendArgs& a) {
+    const float lr = __logf(r2.z * __builtin_amdgcn_rcpf(a.alpha_min)) + 1e-3f;
     const float cx = r0.z * dx, cy = r0.w * dy, ex = r1.x * dx, ey = r1.y * dy, nx = r1.z * dx, ny = r1.w * dy;
     const float nu = cx + cy, nv = ex + ey;
     const float dden = 3.5f * (fabsf(r1.z) + fabsf(r1.w)) + 1e-5f * (1.f + fabsf(nx) + fabsf(ny));
@@ -1393,13 +1413,37 @@ __device__ __forceinline__ bool region_misses(const float4& r0, const float4& r1
     const float reach = 3.5f * __builtin_amdgcn_sqrtf(fmaxf(fmaf(pu, pu, pv * pv), fmaf(qu, qu, qv * qv))) * 1.0001f +
                         1e-5f * (fabsf(cx) + fabsf(cy) + fabsf(ex) + fabsf(ey));
     const float rest = __builtin_amdgcn_sqrtf(fmaf(nu, nu, nv * nv)) * 0.9999f - reach, far = den + dden;
-    const bool plane = rest > 0.f && den > 2.f * dden && rest * rest * 0.9999f > lr * far * far;
     const float lx = fmaxf(fabsf(dx) - 3.5f, 0.f), ly = fmaxf(fabsf(dy) - 3.5f, 0.f);
-    return plane && (!a.lowpass || fmaf(lx, lx, ly * ly) * 0.9999f > lr);
+    if (!(den > 2.f * dden) || (a.lowpass && !(fmaf(lx, lx, ly * ly) * 0.9999f > lr))) return kGeneral;
+    if (rest > 0.f && rest * rest * 0.9999f > lr * far * far) return kMisses;
+    return r2.x * 0.9999f > a.z_near * far ? kPlane : kGeneral;
+}
+
+// One trip of the walk: the records at the LDS offsets off.
+template <bool kPlane, bool kCount, bool kXfer>
+__device__ __forceinline__ void walk_trip(const char* s_bytes, const uint32_t (&off)[kTrip], const float4* s_xc,
+                                          uint32_t nvalid, const TileGeom& g, const BlendArgs& a, PixelState& p,
+                                          WalkCounts& wc) {
+    float al[kTrip], ds[kTrip];
+#pragma unroll
+    for (int i = 0; i < kTrip; ++i) {
+        const float4* r = reinterpret_cast<const float4*>(s_bytes + off[i]);
+        pair_alpha<kPlane>(r[0], r[1], r[2], g.fpx, g.fpy, a, al[i], ds[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < kTrip; ++i) {
+        const float4* r = reinterpret_cast<const float4*>(s_bytes + off[i]);
+        const float4 xc = kXfer ? s_xc[off[i] >> 6] : make_float4(0.f, 0.f, 0.f, 0.f);
+        accumulate<kXfer>(al[i], ds[i], r[3], xc, a, p, wc, kCount, (uint32_t)i < nvalid);
+    }
 }
 
 // Region test, compaction and compositing of one staged batch of nb records
-// by one wave (no block barriers).
+// by one wave (no block barriers).  A list entry is a record's LDS offset,
+// and its top bit is set unless the record is plane-only in the region; a
+// trip of plane-only records takes the shorter evaluation.
+constexpr uint32_t kGeneralBit = 0x8000u;
+static_assert(kDummy * 64 < (int)kGeneralBit, "offsets leave the top bit free");
 template <bool kCount, bool kXfer = false>
 __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uint16_t* s_list, const TileGeom& g,
                                            const BlendArgs& a, PixelState& p, WalkCounts& wc,
@@ -1410,20 +1454,24 @@ __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uin
     for (int q = 0; q < kBatch / 64; ++q) {
         const uint32_t j = (uint32_t)(q * 64 + g.lane);
         bool h = false;
+        uint32_t entry = j * 64u;
         if (j < nb) {
             const uint32_t nq = __float_as_uint(s_rec[4 * j + 2].w), bq = __float_as_uint(s_rec[4 * j + 3].w);
             const float nx = snorm16_value((int)(int16_t)(nq & 0xFFFFu));
             const float ny = snorm16_value((int)(int16_t)(nq >> 16));
             const float4 r0 = s_rec[4 * j];
             const float pr = fmaf(nx, g.scx - r0.x, ny * (g.scy - r0.y)) - half_value(bq);
-            h = fabsf(pr) <= half_value(bq >> 16) + 3.5f * (fabsf(nx) + fabsf(ny)) &&
-                !region_misses(r0, s_rec[4 * j + 1], s_rec[4 * j + 2].z, g.scx - r0.x, g.scy - r0.y, a);
+            if (fabsf(pr) <= half_value(bq >> 16) + 3.5f * (fabsf(nx) + fabsf(ny))) {
+                const int c = record_in_region(r0, s_rec[4 * j + 1], s_rec[4 * j + 2], g.scx - r0.x, g.scy - r0.y, a);
+                h = c != kMisses;
+                entry |= c == kGeneral ? kGeneralBit : 0u;
+            }
         }
         const uint64_t m = __ballot(h);
         if (h) {
             const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            s_list[nhit + below] = (uint16_t)(j * 64u);
+            s_list[nhit + below] = (uint16_t)entry;
         }
         nhit += (uint32_t)__popcll(m);
     }
@@ -1437,30 +1485,13 @@ __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uin
     }
     for (uint32_t k = 0; k < nhit; k += kTrip) {
         if (__ballot(live(p)) == 0ull) break;
-        uint32_t off[kTrip];
-        if (kTrip == 4) {
-            const uint2 o = *reinterpret_cast<const uint2*>(s_list + k);
-            off[0] = o.x & 0xFFFFu;
-            off[1] = o.x >> 16;
-            off[2 % kTrip] = o.y & 0xFFFFu;
-            off[3 % kTrip] = o.y >> 16;
-        } else {
-            const uint32_t o = *reinterpret_cast<const uint32_t*>(s_list + k);
-            off[0] = o & 0xFFFFu;
-            off[1 % kTrip] = o >> 16;
-        }
-        float al[kTrip], ds[kTrip];
-#pragma unroll
-        for (int i = 0; i < kTrip; ++i) {
-            const float4* r = reinterpret_cast<const float4*>(s_bytes + off[i]);
-            pair_alpha(r[0], r[1], r[2], g.fpx, g.fpy, a, al[i], ds[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < kTrip; ++i) {
-            const float4* r = reinterpret_cast<const float4*>(s_bytes + off[i]);
-            const float4 xc = kXfer ? s_xc[off[i] >> 6] : make_float4(0.f, 0.f, 0.f, 0.f);
-            accumulate<kXfer>(al[i], ds[i], r[3], xc, a, p, wc, kCount, k + i < nhit);
-        }
+        static_assert(kTrip == 4, "a trip's entries are one 8-byte read");
+        const uint2 o = *reinterpret_cast<const uint2*>(s_list + k);
+        const uint32_t off[kTrip] = {o.x & 0x7FFFu, (o.x >> 16) & 0x7FFFu, o.y & 0x7FFFu, (o.y >> 16) & 0x7FFFu};
+        if (__ballot((((o.x | o.y) & (kGeneralBit << 16 | kGeneralBit)) != 0u)) == 0ull)
+            walk_trip<true, kCount, kXfer>(s_bytes, off, s_xc, nhit - k, g, a, p, wc);
+        else
+            walk_trip<false, kCount, kXfer>(s_bytes, off, s_xc, nhit - k, g, a, p, wc);
     }
 }
 
