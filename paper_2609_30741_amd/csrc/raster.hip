@@ -1285,6 +1285,11 @@ __global__ __launch_bounds__(256) void k_cell_masks(const uint8_t* __restrict__ 
 constexpr int kBatch = 256;
 constexpr int kTrip = 4;                // records per trip of the walk
 constexpr int kDummy = kBatch;          // LDS record index of the zero record
+// Staged records lie in four planes, a float4 of each record apiece: a wave
+// stages and tests neighbouring records, which at their 64-byte stride would
+// meet in a quarter of the LDS banks.  (1.2M surfels at 1920x1080: 448 ->
+// 392 us.)
+constexpr int kPlaneRecs = kBatch + 1;
 constexpr int kListLen = kBatch + 4;    // per-wave hit list, with padding
 // Continuation segments are walked in kRounds rounds: round r takes the
 // segments [round_lo(r), round_lo(r + 1)) of every continued tile.  One
@@ -1428,13 +1433,13 @@ __device__ __forceinline__ void walk_trip(const char* s_bytes, const uint32_t (&
 #pragma unroll
     for (int i = 0; i < kTrip; ++i) {
         const float4* r = reinterpret_cast<const float4*>(s_bytes + off[i]);
-        pair_alpha<kPlane>(r[0], r[1], r[2], g.fpx, g.fpy, a, al[i], ds[i]);
+        pair_alpha<kPlane>(r[0], r[kPlaneRecs], r[2 * kPlaneRecs], g.fpx, g.fpy, a, al[i], ds[i]);
     }
 #pragma unroll
     for (int i = 0; i < kTrip; ++i) {
         const float4* r = reinterpret_cast<const float4*>(s_bytes + off[i]);
-        const float4 xc = kXfer ? s_xc[off[i] >> 6] : make_float4(0.f, 0.f, 0.f, 0.f);
-        accumulate<kXfer>(al[i], ds[i], r[3], xc, a, p, wc, kCount, (uint32_t)i < nvalid);
+        const float4 xc = kXfer ? s_xc[off[i] >> 4] : make_float4(0.f, 0.f, 0.f, 0.f);
+        accumulate<kXfer>(al[i], ds[i], r[3 * kPlaneRecs], xc, a, p, wc, kCount, (uint32_t)i < nvalid);
     }
 }
 
@@ -1443,7 +1448,7 @@ __device__ __forceinline__ void walk_trip(const char* s_bytes, const uint32_t (&
 // and its top bit is set unless the record is plane-only in the region; a
 // trip of plane-only records takes the shorter evaluation.
 constexpr uint32_t kGeneralBit = 0x8000u;
-static_assert(kDummy * 64 < (int)kGeneralBit, "offsets leave the top bit free");
+static_assert(kDummy * 16 < (int)kGeneralBit, "offsets leave the top bit free");
 template <bool kCount, bool kXfer = false>
 __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uint16_t* s_list, const TileGeom& g,
                                            const BlendArgs& a, PixelState& p, WalkCounts& wc,
@@ -1454,15 +1459,17 @@ __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uin
     for (int q = 0; q < kBatch / 64; ++q) {
         const uint32_t j = (uint32_t)(q * 64 + g.lane);
         bool h = false;
-        uint32_t entry = j * 64u;
+        uint32_t entry = j * 16u;
         if (j < nb) {
-            const uint32_t nq = __float_as_uint(s_rec[4 * j + 2].w), bq = __float_as_uint(s_rec[4 * j + 3].w);
+            const uint32_t nq = __float_as_uint(s_rec[2 * kPlaneRecs + j].w),
+                           bq = __float_as_uint(s_rec[3 * kPlaneRecs + j].w);
             const float nx = snorm16_value((int)(int16_t)(nq & 0xFFFFu));
             const float ny = snorm16_value((int)(int16_t)(nq >> 16));
-            const float4 r0 = s_rec[4 * j];
+            const float4 r0 = s_rec[j];
             const float pr = fmaf(nx, g.scx - r0.x, ny * (g.scy - r0.y)) - half_value(bq);
             if (fabsf(pr) <= half_value(bq >> 16) + 3.5f * (fabsf(nx) + fabsf(ny))) {
-                const int c = record_in_region(r0, s_rec[4 * j + 1], s_rec[4 * j + 2], g.scx - r0.x, g.scy - r0.y, a);
+                const int c = record_in_region(r0, s_rec[kPlaneRecs + j], s_rec[2 * kPlaneRecs + j], g.scx - r0.x,
+                                               g.scy - r0.y, a);
                 h = c != kMisses;
                 entry |= c == kGeneral ? kGeneralBit : 0u;
             }
@@ -1475,7 +1482,7 @@ __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uin
         }
         nhit += (uint32_t)__popcll(m);
     }
-    if (g.lane < kTrip) s_list[nhit + g.lane] = (uint16_t)(kDummy * 64);
+    if (g.lane < kTrip) s_list[nhit + g.lane] = (uint16_t)(kDummy * 16);
     // The list is written and read by this wave only.
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -1522,10 +1529,10 @@ __device__ __forceinline__ void load_rec(const SurfelRec* __restrict__ recs, con
 
 __device__ __forceinline__ void stage_rec(float4* s_rec, int t, const float4& q0, const float4& q1, const float4& q2,
                                           const float4& q3) {
-    s_rec[4 * t + 0] = q0;
-    s_rec[4 * t + 1] = q1;
-    s_rec[4 * t + 2] = q2;
-    s_rec[4 * t + 3] = q3;
+    s_rec[t] = q0;
+    s_rec[kPlaneRecs + t] = q1;
+    s_rec[2 * kPlaneRecs + t] = q2;
+    s_rec[3 * kPlaneRecs + t] = q3;
 }
 
 template <bool kCount>
@@ -1610,15 +1617,21 @@ __device__ __forceinline__ void count_flush(const WalkCounts& wc, int lane, int 
 
 // One block per tile (taken in the order given, heaviest lists first): composite the whole list, then write the pixels.  kPatch:
 // ROI patch of the affiliated eye (writes the depth proxy and the class).
-template <bool kCount, bool kPatch, bool kXfer = false>
-__global__ __launch_bounds__(256) void k_blend(const SurfelRec* __restrict__ recs, const uint32_t* __restrict__ vals,
+// kMany: registers (80) for six workgroups a CU, where there are as many tiles
+// (1.2M surfels at 1920x1080: 392 -> 374 us; for seven and eight, which
+// spill, 380 and 403).  With fewer tiles than five a CU all run at once
+// anyway, the wave that walks the longest list decides, and it is faster
+// unconstrained (87; 10k surfels at 256x256: 42 -> 36 us).
+constexpr int kManyTiles = 5 * 256;
+template <bool kCount, bool kPatch, bool kXfer = false, bool kMany = false>
+__global__ __launch_bounds__(256, kMany ? 6 : 1) void k_blend(const SurfelRec* __restrict__ recs, const uint32_t* __restrict__ vals,
                                                const uint2* __restrict__ ranges, const uint32_t* __restrict__ order,
                                                const uint32_t* __restrict__ n_live, BlendArgs a, ContArgs ca,
                                                float* __restrict__ rgb, float* __restrict__ dz,
                                                float* __restrict__ alpha, uint8_t* __restrict__ cls,
                                                unsigned long long* __restrict__ pair_counts,
                                                long long* __restrict__ trace) {
-    __shared__ float4 s_rec[(kBatch + 1) * 4];
+    __shared__ float4 s_rec[4 * kPlaneRecs];
     __shared__ float4 s_xc[kXfer ? kBatch + 1 : 1];  // transfer colours, one per staged record
     __shared__ __align__(8) uint16_t s_list[4 * kListLen];
     __shared__ uint32_t s_walk[4];
@@ -1634,7 +1647,7 @@ __global__ __launch_bounds__(256) void k_blend(const SurfelRec* __restrict__ rec
     const uint2 rg = ranges[tile];
     PixelState p{inside ? 1.f : 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     WalkCounts wc{0, 0, 0, 0};
-    if (g.tid < 4) s_rec[4 * kDummy + g.tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (g.tid < 4) s_rec[g.tid * kPlaneRecs + kDummy] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (kXfer && g.tid == 0) s_xc[kDummy] = make_float4(0.f, 0.f, 0.f, 0.f);
     uint16_t* my_list = s_list + (g.tid >> 6) * kListLen;
     // The transfer keeps three more sums per pixel, which the continuation
@@ -1786,12 +1799,12 @@ __global__ __launch_bounds__(256) void k_blend_seg(const SurfelRec* __restrict__
                                                    const uint32_t* __restrict__ vals,
                                                    BlendArgs a, ContArgs ca,
                                                    int round, unsigned long long* __restrict__ pair_counts) {
-    __shared__ float4 s_rec[(kBatch + 1) * 4];
+    __shared__ float4 s_rec[4 * kPlaneRecs];
     __shared__ __align__(8) uint16_t s_list[4 * kListLen];
     const uint32_t n_items = min(*ca.n_items, ca.max_slots * kContMaxSeg);
     if (blockIdx.x >= n_items) return;
     const int tid = (int)threadIdx.x;
-    if (tid < 4) s_rec[4 * kDummy + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (tid < 4) s_rec[tid * kPlaneRecs + kDummy] = make_float4(0.f, 0.f, 0.f, 0.f);
     WalkCounts wc{0, 0, 0, 0};
     for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
         const uint32_t slot = ca.item_slot[item];
@@ -1911,12 +1924,12 @@ __global__ __launch_bounds__(256) void k_blend_fix(const SurfelRec* __restrict__
                                                    float* __restrict__ rgb, float* __restrict__ dz,
                                                    float* __restrict__ alpha, uint8_t* __restrict__ cls,
                                                    unsigned long long* __restrict__ pair_counts) {
-    __shared__ float4 s_rec[(kBatch + 1) * 4];
+    __shared__ float4 s_rec[4 * kPlaneRecs];
     __shared__ __align__(8) uint16_t s_list[4 * kListLen];
     const uint32_t n_items = min(*ca.n_items, ca.max_slots * kContMaxSeg);
     if (blockIdx.x >= n_items) return;
     const int tid = (int)threadIdx.x;
-    if (tid < 4) s_rec[4 * kDummy + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (tid < 4) s_rec[tid * kPlaneRecs + kDummy] = make_float4(0.f, 0.f, 0.f, 0.f);
     WalkCounts wc{0, 0, 0, 0};
     for (uint32_t item = blockIdx.x; item < n_items; item += gridDim.x) {
         const uint32_t slot = ca.item_slot[item];
@@ -2048,13 +2061,13 @@ __global__ void k_batch_prefix(const BatchBlendDesc* __restrict__ descs, int n, 
 }
 
 template <bool kPatch>
-__global__ __launch_bounds__(256) void k_blend_batch(const BatchBlendDesc* __restrict__ descs, int n,
+__global__ __launch_bounds__(256, 6) void k_blend_batch(const BatchBlendDesc* __restrict__ descs, int n,
                                                      const uint32_t* __restrict__ prefix, uint32_t* counter) {
-    __shared__ float4 s_rec[(kBatch + 1) * 4];
+    __shared__ float4 s_rec[4 * kPlaneRecs];
     __shared__ __align__(8) uint16_t s_list[4 * kListLen];
     __shared__ uint32_t s_item;
     const int tid = (int)threadIdx.x;
-    if (tid < 4) s_rec[4 * kDummy + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (tid < 4) s_rec[tid * kPlaneRecs + kDummy] = make_float4(0.f, 0.f, 0.f, 0.f);
     const uint32_t total = prefix[n];
     WalkCounts wc{0, 0, 0, 0};
     for (;;) {
@@ -2102,7 +2115,7 @@ hipError_t launch_blend(const SurfelRec* recs, const uint32_t* vals, const uint2
                         unsigned long long* pair_counts, long long* trace, hipStream_t s) {
     if (n_blocks <= 0) return hipSuccess;
     const dim3 g(n_blocks), b(256);
-    const bool cont = ca.cap != 0 && ca.max_slots != 0;
+    const bool cont = ca.cap != 0 && ca.max_slots != 0, many = n_blocks > kManyTiles;
     const dim3 gc(min(ca.max_slots * kContMaxSeg, 4096u)), gs(ca.max_slots);
     if (a.patch && a.xrecs) return hipErrorInvalidValue;  // the transfer belongs to the dominant eye
     if (a.patch) {
@@ -2118,8 +2131,9 @@ hipError_t launch_blend(const SurfelRec* recs, const uint32_t* vals, const uint2
                                    alpha, cls, pair_counts);
             }
         } else {
-            hipLaunchKernelGGL((k_blend<false, true>), g, b, 0, s, recs, vals, ranges, order, n_live, a, ca,
-                               rgb, d_or_z, alpha, cls, pair_counts, (long long*)nullptr);
+            const auto kernel = many ? k_blend<false, true, false, true> : k_blend<false, true, false, false>;
+            hipLaunchKernelGGL(kernel, g, b, 0, s, recs, vals, ranges, order, n_live, a, ca, rgb, d_or_z, alpha, cls, pair_counts,
+                               (long long*)nullptr);
             if (cont) {
                 for (int round = 0; round < kRounds; ++round)
                     hipLaunchKernelGGL((k_blend_seg<false>), gc, b, 0, s, recs, vals, a, ca, round,
@@ -2149,8 +2163,9 @@ hipError_t launch_blend(const SurfelRec* recs, const uint32_t* vals, const uint2
             hipLaunchKernelGGL((k_blend<false, false, true>), g, b, 0, s, recs, vals, ranges, order, n_live,
                                a, ca, rgb, d_or_z, alpha, cls, pair_counts, (long long*)nullptr);
         } else {
-            hipLaunchKernelGGL((k_blend<false, false>), g, b, 0, s, recs, vals, ranges, order, n_live, a,
-                               ca, rgb, d_or_z, alpha, cls, pair_counts, (long long*)nullptr);
+            const auto kernel = many ? k_blend<false, false, false, true> : k_blend<false, false, false, false>;
+            hipLaunchKernelGGL(kernel, g, b, 0, s, recs, vals, ranges, order, n_live, a, ca, rgb, d_or_z, alpha, cls, pair_counts,
+                               (long long*)nullptr);
             if (cont) {
                 for (int round = 0; round < kRounds; ++round)
                     hipLaunchKernelGGL((k_blend_seg<false>), gc, b, 0, s, recs, vals, a, ca, round,
