@@ -483,12 +483,27 @@ __global__ __launch_bounds__(256) void k_preprocess(SceneArgs sc, PreCam cam, Pr
     if (kTwo) sh_basis(sc.sh_degree, d2[0], d2[1], d2[2], Y2);
     const int nc = (sc.sh_degree + 1) * (sc.sh_degree + 1);
     float acc1[3] = {0.f, 0.f, 0.f}, acc2[3] = {0.f, 0.f, 0.f};
-    for (int c = 0; c < nc; ++c) {
+    // Eight coefficients' loads are in flight together: a wave that waits for
+    // each in turn pays the memory's latency nc times.  (1.2M surfels of degree
+    // 3, one eye: 115 -> 106 us; 1M, both eyes: 113 -> 90.  All sixteen, with
+    // their registers: 214.)
+    constexpr int kAhead = 8;
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            const float q = sc.sh[(int64_t)(c * 3 + ch) * n + k];
-            acc1[ch] += Y1[c] * q;
-            if (kTwo) acc2[ch] += Y2[c] * q;
+    for (int c0 = 0; c0 < 16; c0 += kAhead) {
+        if (c0 >= nc) break;
+        float q[kAhead][3];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j)
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) q[j][ch] = c0 + j < nc ? sc.sh[(int64_t)((c0 + j) * 3 + ch) * n + k] : 0.f;
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            if (c0 + j >= nc) break;
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                acc1[ch] += Y1[c0 + j] * q[j][ch];
+                if (kTwo) acc2[ch] += Y2[c0 + j] * q[j][ch];
+            }
         }
     }
     if (col1) {
