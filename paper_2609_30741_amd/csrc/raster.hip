@@ -1000,29 +1000,75 @@ __device__ __forceinline__ void expand_quarter(const ExpandStage& s, int t, uint
 // The lanes whose mask has bit l.
 __device__ __forceinline__ uint64_t tile_lanes(uint32_t m, int l) { return __ballot((m & (1u << l)) != 0u); }
 
-// Keys of each tile in each chunk.
+// Transposes the wave's 64x64 bit matrix (row = lane, column = bit of w):
+// swaps of the off-diagonal blocks of 32, 16 .. 1, each a value of the lane
+// across and, per 32-bit word, a rotation and a bit select.
+struct BitTranspose {
+    uint32_t keep[5], rot[5];  // for blocks of 16, 8, 4, 2, 1
+    bool upper;                // lane >= 32
+    __device__ __forceinline__ explicit BitTranspose(int lane) : upper(lane >= 32) {
+        constexpr uint32_t low[5] = {0x0000FFFFu, 0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {
+            const bool set = (lane & (16 >> i)) != 0;
+            keep[i] = set ? ~low[i] : low[i];
+            rot[i] = set ? (uint32_t)(16 >> i) : 32u - (uint32_t)(16 >> i);  // right
+        }
+    }
+    // The value of lane ^ (16 >> i).
+    template <int i>
+    static __device__ __forceinline__ uint32_t across(uint32_t x) {
+        if (i == 0) return (uint32_t)__shfl_xor((int)x, 16, 64);
+        if (i == 1) return dpp<0x128>(x);               // row_ror:8
+        if (i == 2) return dpp<0x1B>(dpp<0x141>(x));    // ^ 7 (row_half_mirror), then ^ 3
+        if (i == 3) return dpp<0x4E>(x);                // quad_perm [2, 3, 0, 1]
+        return dpp<0xB1>(x);                            // quad_perm [1, 0, 3, 2]
+    }
+    template <int kCtrl>
+    static __device__ __forceinline__ uint32_t dpp(uint32_t x) {
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, kCtrl, 0xF, 0xF, true);
+    }
+    template <int i>
+    __device__ __forceinline__ void step(uint32_t& x) const {
+        const uint32_t y = across<i>(x);
+        x = (x & keep[i]) | (__builtin_amdgcn_alignbit(y, y, rot[i]) & ~keep[i]);
+    }
+    __device__ __forceinline__ uint64_t operator()(uint64_t w) const {
+        uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+        const uint32_t y = (uint32_t)__shfl_xor((int)(upper ? lo : hi), 32, 64);
+        lo = upper ? y : lo;
+        hi = upper ? hi : y;
+        step<0>(lo), step<0>(hi);
+        step<1>(lo), step<1>(hi);
+        step<2>(lo), step<2>(hi);
+        step<3>(lo), step<3>(hi);
+        step<4>(lo), step<4>(hi);
+        return (uint64_t)hi << 32 | lo;
+    }
+};
+
+// Keys of each tile in each chunk: a wave per chunk.  The four masks of a
+// lane are added as bit planes (the sum of a tile's four bits is 0 .. 4) and
+// the planes are transposed, which leaves lane l the entries of tile l to
+// count.  Bound by the reading of the masks; with a ballot per tile and mask
+// it was bound by their instructions (1.2M surfels at 1920x1080: 34 us, now
+// 10).
 __global__ __launch_bounds__(256) void k_tile_count(BinArgs a) {
+    static_assert(kChunk == 256, "four masks a lane");
     extern __shared__ uint32_t s_cp[];  // n_cells + 1 words
     const int lane = threadIdx.x & 63;
-    const ExpandPlan pl(a.cpre[a.n_cells]);
-    if (blockIdx.x >= pl.nq) return;
+    const uint32_t nq = a.cpre[a.n_cells], q0 = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (blockIdx.x * 4 >= nq) return;
     for (uint32_t c = threadIdx.x; c <= a.n_cells; c += 256) s_cp[c] = a.cpre[c];
     __syncthreads();
-    for (uint32_t q = pl.q0; q < pl.nq; q += pl.step) {
+    const BitTranspose tr(lane);
+    for (uint32_t q = q0; q < nq; q += gridDim.x * 4) {
         ExpandStage s;
         expand_load(a, s_cp, q, lane, s);
-        for (int t = pl.t0; t < pl.t1; ++t) {
-            uint32_t m[kChunk / 64], cnt = 0;
-            expand_quarter(s, t, m);
-#pragma unroll
-            for (int l = 0; l < 16; ++l) {
-                uint32_t k = 0;
-#pragma unroll
-                for (int g = 0; g < kChunk / 64; ++g) k += (uint32_t)__popcll(tile_lanes(m[g], l));
-                if (lane == l) cnt = k;
-            }
-            if (lane < 16) a.tcount[(size_t)q * 64 + 16 * t + lane] = cnt;
-        }
+        const uint64_t x = s.m[0] ^ s.m[1], one = x ^ s.m[2], c0 = (s.m[0] & s.m[1]) | (x & s.m[2]);
+        const uint64_t b0 = one ^ s.m[3], c1 = one & s.m[3], b1 = c0 ^ c1, b2 = c0 & c1;
+        a.tcount[(size_t)q * 64 + lane] =
+            (uint32_t)(__popcll(tr(b0)) + 2 * __popcll(tr(b1)) + 4 * __popcll(tr(b2)));
     }
 }
 
