@@ -560,12 +560,16 @@ struct BinStage {
     uint32_t wsum[4];
 };
 
-__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = __shfl_up(v, off, 64);
-        if (lane >= off) v += y;
-    }
+// Inclusive scan over the wave by DPP: within rows of 16 lanes, then the last
+// lane of each row and of the lower half into what follows.
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+    const auto add = [&](uint32_t x) { v += x; };
+    add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false));  // row_shr:1
+    add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false));
+    add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false));
+    add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false));
+    add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));  // row_bcast:31
     return v;
 }
 
@@ -573,7 +577,7 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v, int lane) {
 // after the next barrier); *total gets the sum.
 __device__ __forceinline__ uint32_t block_scan_256(uint32_t v, uint32_t* w4, uint32_t* total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint32_t x = wave_scan_u32(v, lane);
+    const uint32_t x = wave_scan_u32(v);
     if (lane == 63) w4[w] = x;
     __syncthreads();
     uint32_t before = 0, sum = 0;
@@ -1164,6 +1168,7 @@ __global__ __launch_bounds__(1024) void k_tile_plan(BinArgs a, uint32_t n_tiles,
     constexpr int kPlanHeld = 1024 * kPlanRegs;
     constexpr int kPer = (kPlanCounters + 1023) / 1024;  // counters per thread of their scan
     __shared__ uint32_t hist[1024 * kPer];
+    __shared__ uint16_t s_order[kPlanHeld];  // gathered here, written in order
     __shared__ uint32_t wsum[2][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t sub = (uint32_t)tid & (kPlanSub - 1);
@@ -1180,31 +1185,34 @@ __global__ __launch_bounds__(1024) void k_tile_plan(BinArgs a, uint32_t n_tiles,
     int buf = 0;
     __syncthreads();
     for (uint32_t base = 0; base < n_tiles; base += kPlanHeld, buf ^= 1) {
-        uint32_t v[kPlanRegs], sum = 0;
-        const uint32_t t0 = base + (uint32_t)tid * kPlanRegs;
+        // A wave takes consecutive tiles, 64 at a time, so that what it reads
+        // and writes is contiguous.
+        uint32_t v[kPlanRegs], x[kPlanRegs], sum = 0;
+        const uint32_t t0 = base + (uint32_t)wave * (64 * kPlanRegs) + (uint32_t)lane;
+#pragma unroll
+        for (int u = 0; u < kPlanRegs; ++u) v[u] = t0 + 64 * u < n_tiles ? a.ttot[t0 + 64 * u] : 0u;
 #pragma unroll
         for (int u = 0; u < kPlanRegs; ++u) {
-            v[u] = t0 + u < n_tiles ? a.ttot[t0 + u] : 0u;
-            sum += v[u];
+            x[u] = sum + wave_scan_u32(v[u]);
+            sum = (uint32_t)__builtin_amdgcn_readlane((int)x[u], 63);
         }
-        const uint32_t x = wave_scan_u32(sum, lane);
-        if (lane == 63) wsum[buf][wave] = x;
+        if (lane == 0) wsum[buf][wave] = sum;
         __syncthreads();
-        uint32_t run = carry + x - sum;
+        uint32_t before = carry;
 #pragma unroll
         for (int w = 0; w < 16; ++w) {
             const uint32_t y = wsum[buf][w];
-            run += w < wave ? y : 0u;
+            before += w < wave ? y : 0u;
             carry += y;
         }
 #pragma unroll
         for (int u = 0; u < kPlanRegs; ++u) {
-            const uint32_t r0 = min(run, a.cap), r1 = min(run + v[u], a.cap);
-            run += v[u];
+            const uint32_t t = t0 + 64 * u, end = before + x[u];
+            const uint32_t r0 = min(end - v[u], a.cap), r1 = min(end, a.cap);
             bk[u] = 0xFFFFFFFFu;
-            if (t0 + u < n_tiles) {
-                ranges[t0 + u] = make_uint2(r0, r1);
-                if (live(t0 + u)) {
+            if (t < n_tiles) {
+                ranges[t] = make_uint2(r0, r1);
+                if (live(t)) {
                     bk[u] = order_bucket(r1 - r0) * kPlanSub + sub;
                     atomicAdd(&hist[bk[u]], 1u);
                 }
@@ -1219,7 +1227,7 @@ __global__ __launch_bounds__(1024) void k_tile_plan(BinArgs a, uint32_t n_tiles,
         hv[j] = hist[tid * kPer + j];
         sum += hv[j];
     }
-    const uint32_t x = wave_scan_u32(sum, lane);
+    const uint32_t x = wave_scan_u32(sum);
     if (lane == 63) wsum[buf][wave] = x;
     __syncthreads();
     uint32_t before = x - sum, n_live = 0;
@@ -1242,12 +1250,15 @@ __global__ __launch_bounds__(1024) void k_tile_plan(BinArgs a, uint32_t n_tiles,
     if (n_tiles <= (uint32_t)kPlanHeld) {
 #pragma unroll
         for (int u = 0; u < kPlanRegs; ++u)
-            if (bk[u] != 0xFFFFFFFFu) order[atomicAdd(&hist[bk[u]], 1u)] = (uint32_t)tid * kPlanRegs + u;
+            if (bk[u] != 0xFFFFFFFFu)
+                s_order[atomicAdd(&hist[bk[u]], 1u)] = (uint16_t)(wave * (64 * kPlanRegs) + 64 * u + lane);
+        __syncthreads();
+        for (uint32_t i = tid; i < n_live; i += 1024) order[i] = s_order[i];
     } else {
         // The counter of a tile is that of the thread that counted it.
         for (uint32_t base = 0; base < n_tiles; base += kPlanHeld)
             for (int u = 0; u < kPlanRegs; ++u) {
-                const uint32_t t = base + (uint32_t)tid * kPlanRegs + u;
+                const uint32_t t = base + (uint32_t)wave * (64 * kPlanRegs) + 64 * u + (uint32_t)lane;
                 if (!live(t)) continue;
                 const uint2 r = ranges[t];  // written above by this thread
                 order[atomicAdd(&hist[order_bucket(r.y - r.x) * kPlanSub + sub], 1u)] = t;
