@@ -610,8 +610,8 @@ def main():
                 "largest_stage": max(stage_ms, key=lambda k: stage_ms[k])}
 
     # ---- HBM efficiency of the sorts and the reprojection by algorithmic
-    # bytes: one read and one write of every key (and value) per sort, 4 B
-    # each way when a tile key and its surfel share one word; 20 B read
+    # bytes: one read and one write of every key and value of the depth sort;
+    # one write of 4 B per (surfel, tile) key of the tile lists; 20 B read
     # (colour, depth, alpha) + 21 B written (colour, z, alpha, hole mask) per
     # pixel of the forward warp ----
     def hbm(stage, nbytes):
@@ -620,10 +620,8 @@ def main():
         return {"stage": stage, "bound": "hbm", "achieved": round(gbs, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
                 "frac": round(gbs / PEAK_HBM_GBS, 4), "bytes_per_launch": int(nbytes), "avg_ms": round(ms, 4)}
 
-    bits = lambda x: max(1, int(math.ceil(math.log2(max(x, 2)))))
-    key_b = 8.0 if bits(wl.n_tiles) + bits(wl.scene.n) <= 32 else 16.0
-    hbm_stages = [hbm("tile_sort_dom", key_b * head["frame"]["keys_dom"]), hbm("depth_sort_dom", 16.0 * wl.scene.n),
-                  hbm("tile_sort_roi", key_b * head["frame"]["keys_roi"]), hbm("reproject", 41.0 * wl.W * wl.H)]
+    hbm_stages = [hbm("tile_sort_dom", 4.0 * head["frame"]["keys_dom"]), hbm("depth_sort_dom", 16.0 * wl.scene.n),
+                  hbm("tile_sort_roi", 4.0 * head["frame"]["keys_roi"]), hbm("reproject", 41.0 * wl.W * wl.H)]
 
     cpu = None
     if not args.no_cpu_baseline:
