@@ -1362,7 +1362,7 @@ constexpr int kDummy = kBatch;          // LDS record index of the zero record
 // meet in a quarter of the LDS banks.  (1.2M surfels at 1920x1080: 448 ->
 // 392 us.)
 constexpr int kPlaneRecs = kBatch + 1;
-constexpr int kListLen = kBatch + 4;    // per-wave hit list, with padding
+constexpr int kListLen = kBatch + 8;    // per-wave hit list, with padding and the trip after it
 // Continuation segments are walked in kRounds rounds: round r takes the
 // segments [round_lo(r), round_lo(r + 1)) of every continued tile.  One
 // round: a second one (the later segments walked from the exact
@@ -1491,9 +1491,9 @@ __device__ __forceinline__ int record_in_region(const float4& r0, const float4& 
                         1e-5f * (fabsf(cx) + fabsf(cy) + fabsf(ex) + fabsf(ey));
     const float rest = __builtin_amdgcn_sqrtf(fmaf(nu, nu, nv * nv)) * 0.9999f - reach, far = den + dden;
     const float lx = fmaxf(fabsf(dx) - 3.5f, 0.f), ly = fmaxf(fabsf(dy) - 3.5f, 0.f);
-    if (!(den > 2.f * dden) || (a.lowpass && !(fmaf(lx, lx, ly * ly) * 0.9999f > lr))) return kGeneral;
-    if (rest > 0.f && rest * rest * 0.9999f > lr * far * far) return kMisses;
-    return r2.x * 0.9999f > a.z_near * far ? kPlane : kGeneral;
+    const bool plane = den > 2.f * dden && !(a.lowpass && !(fmaf(lx, lx, ly * ly) * 0.9999f > lr));
+    const bool misses = rest > 0.f && rest * rest * 0.9999f > lr * far * far;
+    return !plane ? kGeneral : misses ? kMisses : r2.x * 0.9999f > a.z_near * far ? kPlane : kGeneral;
 }
 
 // One trip of the walk: the records at the LDS offsets off.
@@ -1521,31 +1521,41 @@ __device__ __forceinline__ void walk_trip(const char* s_bytes, const uint32_t (&
 // trip of plane-only records takes the shorter evaluation.
 constexpr uint32_t kGeneralBit = 0x8000u;
 static_assert(kDummy * 16 < (int)kGeneralBit, "offsets leave the top bit free");
-template <bool kCount, bool kXfer = false>
+// kAhead: for launches of few waves, where nothing else hides a wave's own
+// latencies: the next trip's entries are read during this one, and the four
+// tests of a batch run side by side without branches (10k surfels at 256x256:
+// 36.2 -> 33.5 us; 50k at 120x150: 148 -> 135).  The registers that this
+// takes cost more where waves are many (1.2M at 1920x1080: 374 -> 383 us; the
+// continuation of 800x600: 53 -> 60).
+template <bool kCount, bool kXfer = false, bool kAhead = false>
 __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uint16_t* s_list, const TileGeom& g,
                                            const BlendArgs& a, PixelState& p, WalkCounts& wc,
                                            const float4* s_xc = nullptr) {
     const char* s_bytes = reinterpret_cast<const char*>(s_rec);
     uint32_t nhit = 0;
+    const auto kind = [&](uint32_t j) {
+        const uint32_t nq = __float_as_uint(s_rec[2 * kPlaneRecs + j].w), bq = __float_as_uint(s_rec[3 * kPlaneRecs + j].w);
+        const float nx = snorm16_value((int)(int16_t)(nq & 0xFFFFu));
+        const float ny = snorm16_value((int)(int16_t)(nq >> 16));
+        const float4 r0 = s_rec[j];
+        const float pr = fmaf(nx, g.scx - r0.x, ny * (g.scy - r0.y)) - half_value(bq);
+        const bool band = fabsf(pr) <= half_value(bq >> 16) + 3.5f * (fabsf(nx) + fabsf(ny));
+        if (!kAhead && !band) return (int)kMisses;
+        const int c = record_in_region(r0, s_rec[kPlaneRecs + j], s_rec[2 * kPlaneRecs + j], g.scx - r0.x,
+                                       g.scy - r0.y, a);
+        return band ? c : (int)kMisses;
+    };
+    int ahead[kBatch / 64];  // few waves: the four tests side by side, without branches
+    if (kAhead) {
+#pragma unroll
+        for (int q = 0; q < kBatch / 64; ++q) ahead[q] = kind((uint32_t)(q * 64 + g.lane));
+    }
 #pragma unroll
     for (int q = 0; q < kBatch / 64; ++q) {
         const uint32_t j = (uint32_t)(q * 64 + g.lane);
-        bool h = false;
-        uint32_t entry = j * 16u;
-        if (j < nb) {
-            const uint32_t nq = __float_as_uint(s_rec[2 * kPlaneRecs + j].w),
-                           bq = __float_as_uint(s_rec[3 * kPlaneRecs + j].w);
-            const float nx = snorm16_value((int)(int16_t)(nq & 0xFFFFu));
-            const float ny = snorm16_value((int)(int16_t)(nq >> 16));
-            const float4 r0 = s_rec[j];
-            const float pr = fmaf(nx, g.scx - r0.x, ny * (g.scy - r0.y)) - half_value(bq);
-            if (fabsf(pr) <= half_value(bq >> 16) + 3.5f * (fabsf(nx) + fabsf(ny))) {
-                const int c = record_in_region(r0, s_rec[kPlaneRecs + j], s_rec[2 * kPlaneRecs + j], g.scx - r0.x,
-                                               g.scy - r0.y, a);
-                h = c != kMisses;
-                entry |= c == kGeneral ? kGeneralBit : 0u;
-            }
-        }
+        const int c = j >= nb ? (int)kMisses : kAhead ? ahead[q] : kind(j);
+        const bool h = c != kMisses;
+        const uint32_t entry = j * 16u | (c == kGeneral ? kGeneralBit : 0u);
         const uint64_t m = __ballot(h);
         if (h) {
             const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
@@ -1562,10 +1572,13 @@ __device__ __forceinline__ void walk_batch(const float4* s_rec, uint32_t nb, uin
         wc.walk += nb;
         wc.test += nhit;
     }
+    static_assert(kTrip == 4, "a trip's entries are one 8-byte read");
+    uint2 next = make_uint2(0u, 0u);
+    if (kAhead) next = *reinterpret_cast<const uint2*>(s_list);
     for (uint32_t k = 0; k < nhit; k += kTrip) {
         if (__ballot(live(p)) == 0ull) break;
-        static_assert(kTrip == 4, "a trip's entries are one 8-byte read");
-        const uint2 o = *reinterpret_cast<const uint2*>(s_list + k);
+        const uint2 o = kAhead ? next : *reinterpret_cast<const uint2*>(s_list + k);
+        if (kAhead) next = *reinterpret_cast<const uint2*>(s_list + k + kTrip);
         const uint32_t off[kTrip] = {o.x & 0x7FFFu, (o.x >> 16) & 0x7FFFu, o.y & 0x7FFFu, (o.y >> 16) & 0x7FFFu};
         if (__ballot((((o.x | o.y) & (kGeneralBit << 16 | kGeneralBit)) != 0u)) == 0ull)
             walk_trip<true, kCount, kXfer>(s_bytes, off, s_xc, nhit - k, g, a, p, wc);
@@ -1746,7 +1759,7 @@ __global__ __launch_bounds__(256, kMany ? 6 : 1) void k_blend(const SurfelRec* _
         }
         __syncthreads();
         if (base + nb + g.tid < rg.y) load_rec<kXfer>(recs, vals, base + nb + g.tid, a, q0, q1, q2, q3, qx);
-        walk_batch<kCount, kXfer>(s_rec, nb, my_list, g, a, p, wc, s_xc);
+        walk_batch<kCount, kXfer, !kMany>(s_rec, nb, my_list, g, a, p, wc, s_xc);
         base += nb;
         if (!half_taken && base >= mid) {
             half_taken = true;
