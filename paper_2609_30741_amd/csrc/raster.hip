@@ -204,7 +204,8 @@ struct BandRows {
 // counting and the emission spend their time (vector instructions, in fp64),
 // so there is one path for both kinds of bands, without branches: a whole
 // row's interval is [0, kFar], or a row out of the band (|k| > rv).  (1.2M
-// surfels at 1920x1080: counting 78 -> 68 us, emission 90 -> 77.)
+// surfels at 1920x1080: counting 78 -> 68 us, emission 90 -> 77; with the
+// wave scans by DPP 64 and 74.)
 struct BandRect {
     static constexpr double kFar = 1e9;
     double k0, k16, r, inv, rv, far, x0, x1;
@@ -539,7 +540,7 @@ __global__ __launch_bounds__(256) void k_preprocess(SceneArgs sc, PreCam cam, Pr
 // entry, which several tiles share.  Emitting the keys one by one and
 // sorting them by tile id wrote them, read them for a histogram and moved
 // them once per digit, 16 bytes a key and pass: binning took 1220 us of the
-// 1.2M-surfel 1920x1080 frame (8.7e7 keys) and takes 310.
+// 1.2M-surfel 1920x1080 frame (8.3e7 keys) and takes 240.
 // ---------------------------------------------------------------------------
 constexpr int kBinWin = 1024;   // cells per bitmap window of the emission (32 KiB of LDS)
 constexpr int kBinKeep = 1536;  // entries of 256 surfels that the emission keeps in LDS between its two steps
@@ -1269,8 +1270,8 @@ __global__ __launch_bounds__(1024) void k_tile_plan(BinArgs a, uint32_t n_tiles,
 // Writes the tile lists.  A tile's lanes are a ballot of its mask bit; they
 // store their surfels at consecutive places of the tile's list, so a store
 // leaves as one run of a line or two, without a pass through LDS (appending
-// through an LDS buffer, 17 KiB a wave, took 242 us where this takes 89, on
-// 8.7e7 keys of a 1920x1080 frame: 3.9 TB/s written).
+// through an LDS buffer, 17 KiB a wave, took 242 us where this takes 77, on
+// 8.3e7 keys of a 1920x1080 frame: 4.3 TB/s written).
 __global__ __launch_bounds__(256) void k_tile_write(BinArgs a, const uint2* __restrict__ ranges) {
     extern __shared__ uint32_t s_cp[];  // n_cells + 1 words
     const int lane = threadIdx.x & 63;
