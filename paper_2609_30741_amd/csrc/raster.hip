@@ -870,6 +870,7 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
         }
         for (uint32_t w0 = 0; w0 < a.n_cells; w0 += kBinWin) {
             const uint32_t nw = min((uint32_t)kBinWin, a.n_cells - w0);
+            if (w0) __syncthreads();  // the last window's bits have been counted into s_base
             for (uint32_t i = t; i < 8 * nw; i += 256) s_bits[i] = 0u;
             if (t == 0) s_n = 0u;
             __syncthreads();
