@@ -78,7 +78,7 @@ struct BinArgs {
     uint4* band;       // per position of the order: rect, band direction and interval (empty rect: no entries)
     float2* mu;        // and the projected centre
     uint32_t* matrix;  // [n_cells][chunks] entries, then their exclusive scan over the chunks
-    uint2* kpart;      // per chunk: keys (then their running sum), entries
+    uint2* kpart;      // per chunk: keys (then their running sum, at most 2^32 - 1), whether it has any
     uint32_t* ctot;    // per cell: entries
     uint32_t* cstart;  // n_cells + 1: first entry
     uint32_t* cpre;    // n_cells + 1: first expansion chunk (kBinChunk entries each)

@@ -673,11 +673,16 @@ __device__ __forceinline__ void bin_item(const BinArgs& a, const BinStage& s, ui
     surfel_cells(a, s, lo, cr, [&](int cx, uint64_t m) { f(lo, (uint32_t)(cr * a.cells_x + cx), m); });
 }
 
+// Sums of keys that stop at 2^32 - 1 (4097 surfels across a 16384x16384 image
+// have more): such a frame is past any capacity, and reports that.
+__device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+
 // Entries per (cell, chunk of the order), and the keys and entries of each
 // chunk (k_bin_scan makes the keys a running sum).  One workgroup per chunk.
 __global__ __launch_bounds__(256) void k_bin_count(BinArgs a) {
     extern __shared__ uint32_t s_cnt[];  // a.n_cells words
     __shared__ BinStage s;
+    __shared__ uint32_t s_keys[4];
     const int t = threadIdx.x;
     for (uint32_t c = t; c < a.n_cells; c += 256) s_cnt[c] = 0u;
     int64_t p0, p1;
@@ -689,21 +694,24 @@ __global__ __launch_bounds__(256) void k_bin_count(BinArgs a) {
         for (uint32_t it = t; it < items; it += 256)
             bin_item(a, s, it, [&](int, uint32_t cell, uint64_t m) {
                 atomicAdd(&s_cnt[cell], 1u);
-                keys += (uint32_t)__popcll(m);
+                keys = add_sat(keys, (uint32_t)__popcll(m));
             });
     }
     __syncthreads();
-    uint32_t ents = 0;
+    bool any = false;
     for (uint32_t c = t; c < a.n_cells; c += 256) {
         const uint32_t v = s_cnt[c];
         a.matrix[(size_t)c * a.chunks + blockIdx.x] = v;
-        ents += v;
+        any = any || v != 0;
     }
-    uint32_t nk, ne;
-    (void)block_scan_256(keys, s.wsum, &nk);
-    __syncthreads();
-    (void)block_scan_256(ents, s.wsum, &ne);
-    if (t == 0) a.kpart[blockIdx.x] = make_uint2(nk, ne);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) keys = add_sat(keys, (uint32_t)__shfl_xor((int)keys, off, 64));
+    if ((t & 63) == 0) s_keys[t >> 6] = keys;
+    const int ne = __syncthreads_or(any);
+    if (t == 0) {
+        const uint32_t nk = add_sat(add_sat(s_keys[0], s_keys[1]), add_sat(s_keys[2], s_keys[3]));
+        a.kpart[blockIdx.x] = make_uint2(nk, ne ? 1u : 0u);
+    }
 }
 
 // The pass's key count (one thread) and the counters that a pass starts
@@ -730,18 +738,23 @@ __global__ __launch_bounds__(256) void k_bin_scan(BinArgs a, DevStatus* st, int 
     const uint32_t per = (a.chunks + 255) / 256, c0 = t * per;
     uint32_t v[kPer], sum = 0;
     if (blockIdx.x == a.n_cells) {
+        uint64_t keys = 0;  // below 2^36: scanned in two parts
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             v[j] = ((uint32_t)j < per && c0 + j < a.chunks) ? a.kpart[c0 + j].x : 0u;
-            sum += v[j];
+            keys += v[j];
         }
-        uint32_t run = block_scan_256(sum, w4, &total);
+        uint32_t total_hi;
+        const uint64_t lo = block_scan_256((uint32_t)keys & 0xFFFFFu, w4, &total);
+        __syncthreads();
+        uint64_t run = ((uint64_t)block_scan_256((uint32_t)(keys >> 20), w4, &total_hi) << 20) + lo;
+        constexpr uint64_t kMost = 0xFFFFFFFFull;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             run += v[j];
-            if ((uint32_t)j < per && c0 + j < a.chunks) a.kpart[c0 + j].x = run;
+            if ((uint32_t)j < per && c0 + j < a.chunks) a.kpart[c0 + j].x = (uint32_t)min(run, kMost);
         }
-        if (t == 0) bin_status(a, st, which, total);
+        if (t == 0) bin_status(a, st, which, (uint32_t)min(((uint64_t)total_hi << 20) + total, kMost));
         return;
     }
     uint32_t* row = a.matrix + (size_t)blockIdx.x * a.chunks;
@@ -792,13 +805,13 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
             uint32_t pre = 0, tot = 0;
             for (uint32_t q = t & 63; q < a.chunks; q += 64) {
                 const uint32_t v = c < a.n_cells ? row[q] : a.kpart[q].x;
-                pre += q < blockIdx.x ? v : 0u;
-                tot += v;
+                pre = add_sat(pre, q < blockIdx.x ? v : 0u);
+                tot = add_sat(tot, v);
             }
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
-                pre += (uint32_t)__shfl_xor((int)pre, off, 64);
-                tot += (uint32_t)__shfl_xor((int)tot, off, 64);
+                pre = add_sat(pre, (uint32_t)__shfl_xor((int)pre, off, 64));
+                tot = add_sat(tot, (uint32_t)__shfl_xor((int)tot, off, 64));
             }
             if ((t & 63) == 0 && c < a.n_cells) {
                 s_base[c] = pre;
@@ -811,7 +824,7 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
         __syncthreads();
         ctot = s_tot;
         key0 = s_kpos[0];
-        key1 = key0 + a.kpart[blockIdx.x].x;
+        key1 = add_sat(key0, a.kpart[blockIdx.x].x);
         if (blockIdx.x == 0 && t == 0) bin_status(a, st, which, s_kpos[1]);
     } else {
         if (blockIdx.x != 0) key0 = a.kpart[blockIdx.x - 1].x;
@@ -863,9 +876,9 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
                 bin_item(a, s, it, [&](int j, uint32_t, uint64_t m) { atomicAdd(&s_kpos[j], (uint32_t)__popcll(m)); });
             __syncthreads();
             uint32_t total;
-            const uint32_t first = key0 + block_scan_256(s_kpos[t], s.wsum, &total);
+            const uint32_t first = add_sat(key0, block_scan_256(s_kpos[t], s.wsum, &total));
             s_kpos[t] = first;
-            key0 += total;
+            key0 = add_sat(key0, total);
             if (t == 0) s_kpos[256] = key0;
         }
         for (uint32_t w0 = 0; w0 < a.n_cells; w0 += kBinWin) {
