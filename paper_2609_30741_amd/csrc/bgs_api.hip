@@ -136,10 +136,10 @@ Layout make_layout(int64_t n, int64_t W, int64_t H, int64_t kc) {
     L.recs2 = take(sizeof(SurfelRec) * n);
     L.zkeys2 = take(4 * n);
     L.rects2 = take(8 * n);
-    // An entry holds at least one key, so there are no more of them than keys.
-    L.emask = take(8 * kc);
-    L.eid = take(4 * kc);
-    L.tcount = take(256 * (size_t)bin_max_expand_chunks((uint64_t)kc, (uint64_t)nc));
+    const uint64_t ne = bin_max_entries((uint64_t)kc, (uint64_t)nc);
+    L.emask = take(8 * ne);
+    L.eid = take(4 * ne);
+    L.tcount = take(256 * (size_t)bin_max_expand_chunks(ne, (uint64_t)nc));
     L.vals = take(4 * kc);
     L.radix = take(radix_tmp_bytes(n));
     L.trace = take(6 * 8 * nt);
@@ -415,6 +415,7 @@ int raster_pass(bgs_ctx* ctx, const Layout& L, void* ws, int64_t kc, const bgs_s
     b.n_cells = (uint32_t)n_cells_of(cam.width, cam.height);
     bin_split(n, b.n_cells, &b.chunks, &b.fine, &b.per);
     b.cap = (uint32_t)kc;
+    b.ecap = (uint32_t)bin_max_entries((uint64_t)kc, b.n_cells);
     b.mask = mask;
     b.band = at<uint4>(ws, L.band);
     b.mu = at<float2>(ws, L.mu);

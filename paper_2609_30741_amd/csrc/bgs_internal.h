@@ -73,7 +73,8 @@ struct BinArgs {
     int per;           //   the others this many (a multiple of 256)
     int tiles_x, tiles_y, cells_x;
     uint32_t n_cells;
-    uint32_t cap;      // key capacity: list words, and at most as many entries
+    uint32_t cap;      // key capacity: list words
+    uint32_t ecap;     // entry capacity (bin_max_entries)
     CellMask mask;
     uint4* band;       // per position of the order: rect, band direction and interval (empty rect: no entries)
     float2* mu;        // and the projected centre
@@ -113,7 +114,12 @@ inline size_t bin_table_words(int64_t n, int64_t n_cells) {
     const int64_t w = n_cells * c, b = n_cells * 256 > (1 << 20) ? n_cells * 256 : (1 << 20);
     return (size_t)(w < b ? w : b);
 }
-inline uint64_t bin_max_expand_chunks(uint64_t cap, uint64_t n_cells) { return cap / kBinChunk + n_cells; }
+// Every entry holds a key, except those of the one surfel that the capacity
+// cuts, which has at most one per cell.
+inline uint64_t bin_max_entries(uint64_t key_cap, uint64_t n_cells) {
+    return key_cap + n_cells < 0xFFFFFFFFull ? key_cap + n_cells : 0xFFFFFFFFull;
+}
+inline uint64_t bin_max_expand_chunks(uint64_t entry_cap, uint64_t n_cells) { return entry_cap / kBinChunk + n_cells; }
 
 struct BlendArgs {
     int W, H, tiles_x;

@@ -778,9 +778,11 @@ __global__ __launch_bounds__(256) void k_bin_scan(BinArgs a, DevStatus* st, int 
 // compositing order without a sort.  The first workgroup also writes the
 // cells' first entries and first expansion chunks.  A pass with more keys
 // than the capacity reports the overflow and keeps the first of them, in
-// compositing order and within a surfel in row order of its tiles: the
-// masks of the entries past it lose their bits.  (Entries past the capacity
-// are dropped.)  kScan: a small count table is read whole by every
+// compositing order and within a surfel in row order of its tiles: only
+// surfels that keep a key are placed (every workgroup counts the chunk that
+// the capacity cuts again for that), so that those in front keep theirs
+// wherever their cells lie, and of the surfel that the capacity cuts the masks
+// lose the bits past it.  kScan: a small count table is read whole by every
 // workgroup, which takes what it needs of k_bin_scan's sums itself, so that
 // small frames save that launch.
 template <bool kScan>
@@ -797,7 +799,8 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
     if (blockIdx.x != 0 && a.kpart[blockIdx.x].y == 0) return;
     // ctot[c]: the entries of cell c; pre(c): those of earlier chunks.
     const uint32_t* ctot = a.ctot;
-    uint32_t key0 = 0, key1;  // the chunk's keys, counted through the order
+    uint32_t key0 = 0;  // the chunk's first key, counted through the order
+    uint32_t all_keys;
     if (kScan) {
         uint32_t* s_tot = s_dyn + a.n_cells;  // the bitmap's words, not in use yet
         for (uint32_t c = t >> 6; c <= a.n_cells; c += 4) {  // the last: the chunks' keys
@@ -824,62 +827,117 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
         __syncthreads();
         ctot = s_tot;
         key0 = s_kpos[0];
-        key1 = add_sat(key0, a.kpart[blockIdx.x].x);
-        if (blockIdx.x == 0 && t == 0) bin_status(a, st, which, s_kpos[1]);
+        all_keys = s_kpos[1];
+        if (blockIdx.x == 0 && t == 0) bin_status(a, st, which, all_keys);
     } else {
         if (blockIdx.x != 0) key0 = a.kpart[blockIdx.x - 1].x;
-        key1 = a.kpart[blockIdx.x].x;
+        all_keys = a.kpart[a.chunks - 1].x;
     }
-    const bool over = key1 > a.cap;  // uniform; so is key0
+    int64_t p0, p1;
+    bool over = false;  // does the capacity cut this chunk?  (uniform)
+    // Past the capacity: the first keys of the staged surfels, from `first` on,
+    // into s_kpos; returns the key after them.
+    const auto stage_keys = [&](uint32_t items, uint32_t first) {
+        s_kpos[t] = 0u;
+        __syncthreads();
+        for (uint32_t it = t; it < items; it += 256)
+            bin_item(a, s, it, [&](int j, uint32_t, uint64_t m) { atomicAdd(&s_kpos[j], (uint32_t)__popcll(m)); });
+        __syncthreads();
+        uint32_t total;
+        const uint32_t at = add_sat(first, block_scan_256(s_kpos[t], s.wsum, &total));
+        s_kpos[t] = at;
+        if (t == 0) s_kpos[256] = add_sat(first, total);
+        __syncthreads();
+        return add_sat(first, total);
+    };
+    const uint32_t per = (a.n_cells + 255) / 256, c0 = min(a.n_cells, t * per), c1 = min(a.n_cells, c0 + per);
+    if (all_keys > a.cap) {  // uniform over the grid
+        // The chunk that the capacity cuts: the first that does not keep all of
+        // its keys.  Later ones place nothing.
+        const auto chunk_keys = [&](uint32_t q) {
+            return a.kpart[q].x - (kScan || q == 0 ? 0u : a.kpart[q - 1].x);
+        };
+        const uint32_t run = (a.chunks + 255) / 256;
+        uint32_t sum = 0;
+        for (uint32_t j = 0; j < run; ++j) sum = add_sat(sum, t * run + j < a.chunks ? chunk_keys(t * run + j) : 0u);
+        __syncthreads();  // key0 and all_keys have been read
+        s_kpos[t] = sum;
+        __syncthreads();
+        if (t == 0) {
+            uint32_t first = 0, i = 0;
+            while (i < 255 && add_sat(first, s_kpos[i]) <= a.cap) first += s_kpos[i++];
+            uint32_t q = min(i * run, a.chunks - 1);
+            while (q + 1 < a.chunks && add_sat(first, chunk_keys(q)) <= a.cap) first += chunk_keys(q++);
+            s_n = q;
+            s_kpos[256] = first;
+        }
+        __syncthreads();
+        const uint32_t cut = s_n;
+        uint32_t key = s_kpos[256];
+        if (blockIdx.x > cut) return;
+        over = blockIdx.x == cut;
+        // The cells' entries: all of the chunks before it, and of its surfels
+        // those whose first key is kept.
+        uint32_t* kept = kScan ? s_dyn + a.n_cells : s_base;
+        if (kScan) {
+            for (uint32_t c = t >> 6; c < a.n_cells; c += 4) {
+                uint32_t v = 0;
+                for (uint32_t q = t & 63; q < cut; q += 64) v += a.matrix[(size_t)c * a.chunks + q];
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) v += (uint32_t)__shfl_xor((int)v, off, 64);
+                if ((t & 63) == 0) kept[c] = v;
+            }
+        } else {
+            for (uint32_t c = t; c < a.n_cells; c += 256) kept[c] = a.matrix[(size_t)c * a.chunks + cut];
+        }
+        bin_chunk(a, cut, &p0, &p1);
+        for (int64_t p = p0; p < p1 && key < a.cap; p += 256) {
+            __syncthreads();
+            const uint32_t items = bin_stage<false>(a, p, (int)min((int64_t)256, p1 - p), s);
+            if (items == 0) continue;  // uniform
+            key = stage_keys(items, key);
+            for (uint32_t it = t; it < items; it += 256)
+                bin_item(a, s, it, [&](int j, uint32_t cell, uint64_t) {
+                    if (s_kpos[j] < a.cap) atomicAdd(&kept[cell], 1u);
+                });
+        }
+        __syncthreads();
+        ctot = kept;
+    }
     {
-        const uint32_t per = (a.n_cells + 255) / 256, c0 = min(a.n_cells, t * per), c1 = min(a.n_cells, c0 + per);
         uint32_t sum = 0, total;
         for (uint32_t c = c0; c < c1; ++c) sum += ctot[c];
         uint32_t run = block_scan_256(sum, s.wsum, &total);
         if (blockIdx.x == 0) {
             uint32_t at = run, nq = 0, all;
-            for (uint32_t c = c0; c < c1; ++c) {
-                const uint32_t e = at + ctot[c];
-                nq += (min(e, a.cap) - min(at, a.cap) + kChunk - 1) / kChunk;
-                at = e;
-            }
+            for (uint32_t c = c0; c < c1; ++c) nq += (ctot[c] + kChunk - 1) / kChunk;
             __syncthreads();
             uint32_t q = block_scan_256(nq, s.wsum, &all);
-            at = run;
             for (uint32_t c = c0; c < c1; ++c) {
-                const uint32_t e = at + ctot[c];
-                a.cstart[c] = min(at, a.cap);
+                a.cstart[c] = at;
                 a.cpre[c] = q;
-                q += (min(e, a.cap) - min(at, a.cap) + kChunk - 1) / kChunk;
-                at = e;
+                q += (ctot[c] + kChunk - 1) / kChunk;
+                at += ctot[c];
             }
             if (t == 0) {
-                a.cstart[a.n_cells] = min(total, a.cap);
+                a.cstart[a.n_cells] = total;
                 a.cpre[a.n_cells] = all;
             }
         }
         for (uint32_t c = c0; c < c1; ++c) {
+            const uint32_t v = ctot[c];  // may lie where the base goes
             s_base[c] = run + (kScan ? s_base[c] : a.matrix[(size_t)c * a.chunks + blockIdx.x]);
-            run += ctot[c];
+            run += v;
         }
     }
-    int64_t p0, p1;
     bin_chunk(a, blockIdx.x, &p0, &p1);
     for (int64_t p = p0; p < p1; p += 256) {
         __syncthreads();
         const uint32_t items = bin_stage<false>(a, p, (int)min((int64_t)256, p1 - p), s);
         if (items == 0) continue;  // uniform
         if (over) {
-            s_kpos[t] = 0u;
-            __syncthreads();
-            for (uint32_t it = t; it < items; it += 256)
-                bin_item(a, s, it, [&](int j, uint32_t, uint64_t m) { atomicAdd(&s_kpos[j], (uint32_t)__popcll(m)); });
-            __syncthreads();
-            uint32_t total;
-            const uint32_t first = add_sat(key0, block_scan_256(s_kpos[t], s.wsum, &total));
-            s_kpos[t] = first;
-            key0 = add_sat(key0, total);
-            if (t == 0) s_kpos[256] = key0;
+            if (key0 >= a.cap) break;  // uniform
+            key0 = stage_keys(items, key0);
         }
         for (uint32_t w0 = 0; w0 < a.n_cells; w0 += kBinWin) {
             const uint32_t nw = min((uint32_t)kBinWin, a.n_cells - w0);
@@ -902,8 +960,8 @@ __global__ __launch_bounds__(256) void k_bin_emit(BinArgs a, DevStatus* st, int 
                 const uint32_t* b = s_bits + 8 * (cell - w0);
                 uint32_t pos = s_base[cell] + (uint32_t)__popc(b[j >> 5] & ((1u << (j & 31)) - 1u));
                 for (int q = 0; q < (j >> 5); ++q) pos += (uint32_t)__popc(b[q]);
-                if (over && s_kpos[j] >= a.cap) m = 0ull;
-                if (pos < a.cap) {
+                if (over && s_kpos[j] >= a.cap) return;
+                if (pos < a.ecap) {  // always true for consistent counts; keeps every write in bounds
                     a.emask[pos] = m;
                     a.eid[pos] = s.id[j];
                 }
@@ -2104,7 +2162,7 @@ hipError_t launch_bin_entries(const BinArgs& a, DevStatus* st, int which, hipStr
 // Grid of the chunk-strided kernels: enough workgroups for the chunks that
 // the key capacity allows, at most eight per CU.
 static unsigned expand_grid(const BinArgs& a) {
-    return (unsigned)std::min<uint64_t>(2048, bin_max_expand_chunks(a.cap, a.n_cells));
+    return (unsigned)std::min<uint64_t>(2048, bin_max_expand_chunks(a.ecap, a.n_cells));
 }
 
 hipError_t launch_tile_plan(const BinArgs& a, uint2* ranges, uint32_t* order, DevStatus* st, hipStream_t s) {

@@ -8,8 +8,9 @@ pytestmark = pytest.mark.gpu
 
 
 # 2^20 tiles of 16384x16384, each met by every surfel: the disc of one that
-# reaches behind the camera is bounded by the whole image.
-@pytest.mark.parametrize("n", [4100])
+# reaches behind the camera is bounded by the whole image.  (262200: more
+# than 2^32 entries too, one per surfel and cell.)
+@pytest.mark.parametrize("n", [4100, 262_200])
 def test_more_keys_than_a_word_counts(n):
     W = H = 16384
     sc = synth.scene_uniform_cube(2, n, log_scale=(3.0, 0.1))
