@@ -1110,23 +1110,39 @@ __device__ inline int find_root_lds(int* L, int x) {
 // In global memory.  Parents only ever get smaller and every value a node
 // has had is an ancestor of it, so a read that another XCD's unions have
 // overtaken still leads towards the root: it may come out of this XCD's
-// cache.
-__device__ inline int find_root_g(const int* L, int x) {
-    int p = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+// cache (kScope: the scope of the reads).
+template <int kScope = __HIP_MEMORY_SCOPE_WORKGROUP>
+__device__ inline int find_root_g(const int* L, int x, int* hops = nullptr) {
+    int p = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, kScope);
     while (p != x) {
         x = p;
-        p = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (hops) ++*hops;
+        p = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, kScope);
     }
     return x;
 }
 
+// The same for a union; where the path was long, the next finds from this
+// tile's piece (x's parent) go straight to the root.
+template <int kScope>
+__device__ inline int find_root_union(int* L, int x) {
+    const int piece = __hip_atomic_load(&L[x], __ATOMIC_RELAXED, kScope);
+    int hops = 0;
+    const int r = find_root_g<kScope>(L, piece, &hops);
+    if (hops > 1) (void)__hip_atomic_fetch_min(&L[piece], r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return r;
+}
+
 // Ends whatever the finds read: the atomic returns the current parent, and
-// the larger index strictly falls from round to round.
+// the larger index strictly falls from round to round.  The first finds may
+// read this XCD's cache; one whose root turns out to have a parent is
+// repeated past it, or each step of the path since would take an atomic that
+// fails (a serpentine of one-pixel lines, 1503x1001: 110-250 -> 65 us in
+// all; nothing changes where components are small).
 __device__ inline void unite_g(int* L, int a, int b) {
-    while (true) {
-        a = find_root_g(L, a);
-        b = find_root_g(L, b);
-        if (a == b) return;
+    a = find_root_union<__HIP_MEMORY_SCOPE_WORKGROUP>(L, a);
+    b = find_root_union<__HIP_MEMORY_SCOPE_WORKGROUP>(L, b);
+    while (a != b) {
         if (a < b) {
             int t = a;
             a = b;
@@ -1134,7 +1150,9 @@ __device__ inline void unite_g(int* L, int a, int b) {
         }
         const int old = atomicMin(&L[a], b);
         if (old == a) return;
-        a = old;  // a had gained a parent meanwhile; unite that one with b
+        // a had gained a parent meanwhile; unite that one with b
+        a = find_root_union<__HIP_MEMORY_SCOPE_AGENT>(L, old);
+        b = find_root_union<__HIP_MEMORY_SCOPE_AGENT>(L, b);
     }
 }
 
