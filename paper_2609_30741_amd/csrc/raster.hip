@@ -563,8 +563,9 @@ struct BinStage {
 
 // Inclusive scan over the wave by DPP: within rows of 16 lanes, then the last
 // lane of each row and of the lower half into what follows.
-__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
-    const auto add = [&](uint32_t x) { v += x; };
+template <typename Add>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v, Add&& sum) {
+    const auto add = [&](uint32_t x) { v = sum(v, x); };
     add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false));  // row_shr:1
     add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false));
     add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false));
@@ -573,6 +574,14 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
     add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));  // row_bcast:31
     return v;
 }
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+    return wave_scan(v, [](uint32_t a, uint32_t b) { return a + b; });
+}
+
+// Sums of keys that stop at 2^32 - 1 (4097 surfels across a 16384x16384 image
+// have more): such a frame is past any capacity, and reports that.
+__device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+__device__ __forceinline__ uint32_t wave_scan_sat(uint32_t v) { return wave_scan(v, add_sat); }
 
 // Exclusive scan over a 256-thread block (w4: 4 words of LDS, free again
 // after the next barrier); *total gets the sum.
@@ -673,10 +682,6 @@ __device__ __forceinline__ void bin_item(const BinArgs& a, const BinStage& s, ui
     surfel_cells(a, s, lo, cr, [&](int cx, uint64_t m) { f(lo, (uint32_t)(cr * a.cells_x + cx), m); });
 }
 
-// Sums of keys that stop at 2^32 - 1 (4097 surfels across a 16384x16384 image
-// have more): such a frame is past any capacity, and reports that.
-__device__ __forceinline__ uint32_t add_sat(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
-
 // Entries per (cell, chunk of the order), and the keys and entries of each
 // chunk (k_bin_scan makes the keys a running sum).  One workgroup per chunk.
 __global__ __launch_bounds__(256) void k_bin_count(BinArgs a) {
@@ -697,20 +702,13 @@ __global__ __launch_bounds__(256) void k_bin_count(BinArgs a) {
                 keys = add_sat(keys, (uint32_t)__popcll(m));
             });
     }
+    keys = wave_scan_sat(keys);
+    if ((t & 63) == 63) s_keys[t >> 6] = keys;
     __syncthreads();
-    bool any = false;
-    for (uint32_t c = t; c < a.n_cells; c += 256) {
-        const uint32_t v = s_cnt[c];
-        a.matrix[(size_t)c * a.chunks + blockIdx.x] = v;
-        any = any || v != 0;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) keys = add_sat(keys, (uint32_t)__shfl_xor((int)keys, off, 64));
-    if ((t & 63) == 0) s_keys[t >> 6] = keys;
-    const int ne = __syncthreads_or(any);
+    for (uint32_t c = t; c < a.n_cells; c += 256) a.matrix[(size_t)c * a.chunks + blockIdx.x] = s_cnt[c];
     if (t == 0) {
         const uint32_t nk = add_sat(add_sat(s_keys[0], s_keys[1]), add_sat(s_keys[2], s_keys[3]));
-        a.kpart[blockIdx.x] = make_uint2(nk, ne ? 1u : 0u);
+        a.kpart[blockIdx.x] = make_uint2(nk, nk ? 1u : 0u);  // an entry has a key at least
     }
 }
 
