@@ -487,7 +487,7 @@ __global__ __launch_bounds__(256) void k_preprocess(SceneArgs sc, PreCam cam, Pr
     // Eight coefficients' loads are in flight together: a wave that waits for
     // each in turn pays the memory's latency nc times.  (1.2M surfels of degree
     // 3, one eye: 115 -> 106 us; 1M, both eyes: 113 -> 90.  All sixteen, with
-    // their registers: 214.)
+    // their registers: 214 and 196.)
     constexpr int kAhead = 8;
 #pragma unroll
     for (int c0 = 0; c0 < 16; c0 += kAhead) {
@@ -1777,7 +1777,14 @@ __device__ __forceinline__ void count_flush(const WalkCounts& wc, int lane, int 
 // (1.2M surfels at 1920x1080: 392 -> 374 us; for seven and eight, which
 // spill, 380 and 403).  With fewer tiles than five a CU all run at once
 // anyway, the wave that walks the longest list decides, and it is faster
-// unconstrained (87; 10k surfels at 256x256: 42 -> 36 us).
+// unconstrained (87; 10k surfels at 256x256: 42 -> 36 us).  The host knows
+// the image's tiles only, so an ROI patch takes its image's form.  Against the
+// other form, 1M surfels: 300 to 680 live tiles at 1600x1064, 19.0, 39.6, 31.4
+// and 32.7 us (18.1, 38.0, 31.6, 32.8); 1656 and 1986 at 2064x2208, 37.9 and
+// 25.0 (41.3, 28.5); 11166 there, 225 (249); but 1972 tiles of a 300k shell's
+// silhouette at 1600x1064, 192 (185).  The view-colour transfer has the
+// unconstrained form only: 463 us at 800x600, 183 at 1600x1064, 429 at
+// 2064x2208 (with registers for six: 504, 167, 386).
 constexpr int kManyTiles = 5 * 256;
 template <bool kCount, bool kPatch, bool kXfer = false, bool kMany = false>
 __global__ __launch_bounds__(256, kMany ? 6 : 1) void k_blend(const SurfelRec* __restrict__ recs, const uint32_t* __restrict__ vals,
