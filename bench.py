@@ -64,13 +64,13 @@ PEAK_VALU_TLANEOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 # every evaluated pair.
 FLOPS_PER_PAIR = 38
 # HBM bytes of one dominant-eye blend stage (all its launches: on
-# unbounded1600 the one k_blend launch, on sphere800 the capped walk, two
-# segment rounds, chain and fix-up) per workload, mean over the workload's
+# unbounded1600 the one k_blend launch, on sphere800 the capped walk, the
+# segments, chain and fix-up) per workload, mean over the workload's
 # poses, FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (factors from a 512 MiB copy),
 # each valid while raster.hip and bgs_api.hip hash (sha1 over the two files
 # in that order) to its value.
-BLEND_TRAFFIC = {"sphere800": {"source_sha1": "0af4458268b320b8d65f9a62d78b33d448c618fd", "bytes": 126.9e6},
-                 "unbounded1600": {"source_sha1": "0af4458268b320b8d65f9a62d78b33d448c618fd", "bytes": 131.8e6}}
+BLEND_TRAFFIC = {"sphere800": {"source_sha1": "36feff71730f6cf12ae7c6248d1ab2d3c5bde2d6", "bytes": 125.1e6},
+                 "unbounded1600": {"source_sha1": "36feff71730f6cf12ae7c6248d1ab2d3c5bde2d6", "bytes": 131.2e6}}
 
 
 def log(*a):

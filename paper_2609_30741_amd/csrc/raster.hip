@@ -1777,7 +1777,7 @@ __device__ __forceinline__ void count_flush(const WalkCounts& wc, int lane, int 
 // (1.2M surfels at 1920x1080: 392 -> 374 us; for seven and eight, which
 // spill, 380 and 403).  With fewer tiles than five a CU all run at once
 // anyway, the wave that walks the longest list decides, and it is faster
-// unconstrained (87; 10k surfels at 256x256: 42 -> 36 us).  The host knows
+// unconstrained (109; 10k surfels at 256x256: 42 -> 36 us).  The host knows
 // the image's tiles only, so an ROI patch takes its image's form.  Against the
 // other form, 1M surfels: 300 to 680 live tiles at 1600x1064, 19.0, 39.6, 31.4
 // and 32.7 us (18.1, 38.0, 31.6, 32.8); 1656 and 1986 at 2064x2208, 37.9 and
