@@ -26,7 +26,8 @@ constexpr int kBinFine = 64;         // surfels per chunk at the front of the or
 // surfel-plane coordinates of pixel (i, j), times sqrt(1/2), are
 // u = (C1 dx + C2 dy)/den, v = (D1 dx + D2 dy)/den and the ray meets the
 // plane at depth
-// lam_num/den (lam_num < 0 marks a surfel seen exactly edge-on).  The
+// lam_num/den (lam_num < 0 marks a surfel seen exactly edge-on, or one
+// without extent: only its low-pass term counts).  The
 // strip band bounds every pixel x the surfel can reach by
 // |n.(x - mu) - c| <= w, with n a pair of snorm16 (x low, y high) and c, w
 // a pair of fp16 (c low, w high).

@@ -385,7 +385,12 @@ __device__ __forceinline__ void surfel_view(const PreCam& cam, float px, float p
             D2 = (float)(kRootHalf * (pzc * bs[1] / cam.fy - n2 * pb));
             N1 = (float)n1;
             N2 = (float)n2;
-            lam_num = (float)pzc;
+            // A surfel without extent (scale 0) has coefficients that are no
+            // numbers: it counts as edge-on, so that the blend takes its
+            // low-pass term everywhere.  (Below 1e28 no product with a pixel
+            // offset overflows, which could make one plane coordinate NaN.)
+            const float most = 1e28f;
+            if (fabsf(C1) < most && fabsf(C2) < most && fabsf(D1) < most && fabsf(D2) < most) lam_num = (float)pzc;
         }
     }
     v.rec.a = make_float4((float)mux, (float)muy, C1, C2);
@@ -1542,7 +1547,9 @@ __device__ __forceinline__ void accumulate(float al, float dsel, const float4& r
 // plane is in front of z_near all over the region: the walk then needs
 // neither the low-pass term nor the selections between the two, nor the
 // test against z_near.  den is bounded away from 0, so that the depth is
-// finite also where the pair does not count and enters with weight 0.  Most
+// finite also where the pair does not count and enters with weight 0; u and v
+// are numbers, since the coefficients of a record that is not edge-on are
+// finite with room to spare.  Most
 // (record, region) pairs of surfels larger than a tile are of this kind.
 //
 // Every bound is widened far beyond the rounding of these sums and of
