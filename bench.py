@@ -69,8 +69,8 @@ FLOPS_PER_PAIR = 38
 # poses, FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (factors from a 512 MiB copy),
 # each valid while raster.hip and bgs_api.hip hash (sha1 over the two files
 # in that order) to its value.
-BLEND_TRAFFIC = {"sphere800": {"source_sha1": "36feff71730f6cf12ae7c6248d1ab2d3c5bde2d6", "bytes": 125.1e6},
-                 "unbounded1600": {"source_sha1": "36feff71730f6cf12ae7c6248d1ab2d3c5bde2d6", "bytes": 131.2e6}}
+BLEND_TRAFFIC = {"sphere800": {"source_sha1": "330ef186038565d09f13aefb13a6f25ed7fb576f", "bytes": 125.1e6},
+                 "unbounded1600": {"source_sha1": "330ef186038565d09f13aefb13a6f25ed7fb576f", "bytes": 131.1e6}}
 
 
 def log(*a):
